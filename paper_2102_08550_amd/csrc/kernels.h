@@ -149,7 +149,8 @@ enum BackwardMode { BACKWARD_AUTO = 0, BACKWARD_SEPARATE = 1, BACKWARD_FUSED = 2
 // Softmax cross-entropy on logits [slot][B][ld]: delta = (softmax - onehot)/B
 // stored as bf16 or fp32 into delta [slot][B][ld] (columns C..ld-1 zeroed),
 // per-row loss into loss[slot][B]; if correct != nullptr, correct[slot][B] =
-// 1 where the label's logit is the largest (ties count), else 0.
+// 1 where the label's logit is the largest (ties count), else 0.  gather ==
+// nullptr: row b has label y[b]; delta == nullptr: no gradient is stored.
 hipError_t launch_softmax_ce(const float* logits, int64_t ld, int64_t slot_stride, int C, int B,
                              const int32_t* y, const int32_t* gather, int64_t gather_slot,
                              void* delta, bool delta_bf16, float* loss, int64_t loss_slot,
@@ -159,6 +160,63 @@ hipError_t launch_softmax_ce(const float* logits, int64_t ld, int64_t slot_strid
 hipError_t launch_cast_bf16(const float* master, int64_t master_slot, const int32_t* order,
                             uint16_t* wcopy, int64_t wcopy_slot, int64_t n, int n_slots,
                             hipStream_t s);
+
+// ---- fp32 MLPs (f32_kernels.hip) ----
+// Forward or backward-data of one layer (no rows_out, no split); tiling L, M
+// or S: 64 x 64, 32 x 32 or 16 x 16 outputs per workgroup, the same bits.
+hipError_t launch_f32_gemm(const GemmArgs& g, GemmMode mode, int n_slots, hipStream_t s,
+                           int tiling);
+
+// The classifier head in one launch (up to F32_HEAD_CLASSES classes): logits
+// of the last layer, softmax cross-entropy, and, with `below`, the delta of
+// the layer below.  Slot z works on replica order[z].
+constexpr int F32_HEAD_CLASSES = 64;
+struct F32HeadArgs {
+  int B, K, C;  // batch rows, inputs of the last layer, classes
+  const float* act;  // activations below [B][act_ld] per slot, or dataset rows
+  int64_t act_ld, act_slot;
+  int act_gather;  // act holds dataset rows: row gather[b] of it
+  const float* master_in;  // fp32 parameters (replica order[z])
+  int64_t master_in_slot, w_off, b_off;
+  const int32_t* order;
+  const int32_t* y;
+  const int32_t* gather;  // dataset row of batch row b (labels); nullptr: b itself
+  int64_t gather_slot;
+  float* delta;  // (softmax - onehot) / B [B][delta_ld], or nullptr
+  int64_t delta_ld, delta_slot;
+  float* loss;  // [B] per slot
+  int64_t loss_slot;
+  int32_t* correct;  // as launch_softmax_ce, or nullptr
+  float* below;  // delta of the layer below [B][below_ld], or nullptr
+  int64_t below_ld, below_slot;
+};
+hipError_t launch_f32_head(const F32HeadArgs& h, int n_slots, hipStream_t s);
+
+// Backward-weight and the SGD update of every layer of an fp32 MLP in one
+// launch: W_l[o][i] -= lr sum_b delta_l[b][o] act_{l-1}[b][i], and the biases.
+constexpr int F32_UPDATE_LAYERS = 16;
+struct F32UpdateLayer {
+  int M, N;  // inputs, outputs
+  const float* a;  // activations below [B][a_ld]; layer 0: row gather[b] if gather is set
+  int64_t a_ld, a_slot;
+  const float* d;  // delta [B][d_ld], rows padded to 64
+  int64_t d_ld, d_slot;
+  int64_t w_off, b_off;
+  int first_wg;  // set by the launcher
+};
+struct F32UpdateArgs {
+  F32UpdateLayer layer[F32_UPDATE_LAYERS];
+  int n_layers, B;
+  const int32_t* gather;
+  int64_t gather_slot;
+  float* master;
+  int64_t master_slot;
+  const float* master_in;
+  int64_t master_in_slot;
+  const int32_t* order;
+  float lr;
+};
+hipError_t launch_f32_update(const F32UpdateArgs& u, int n_slots, hipStream_t s);
 
 // Held-out evaluation: the row table [64 slot entries = 0][i = 0 .. n-1]
 // that the forward pass gathers through, and the reduction of the per-row

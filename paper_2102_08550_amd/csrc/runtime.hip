@@ -54,7 +54,7 @@ constexpr float kBackwardMargin = 0.05f;
 // the process ends.  Host code never uses this name as an address: it takes
 // the device address each GPU reports for it (scratch_address).
 constexpr size_t kNoAllocScratchBytes =
-    256 + (64 + OSCARS_EVAL_NOALLOC_MAX_ROWS) * 4 + 2 * OSCARS_EVAL_NOALLOC_MAX_ROWS * 4;
+    256 + (128 + OSCARS_EVAL_NOALLOC_MAX_ROWS) * 4 + 2 * (64 + OSCARS_EVAL_NOALLOC_MAX_ROWS) * 4;
 static_assert(OSCARS_EVAL_NOALLOC_MAX_ROWS % 64 == 0, "whole 256-byte parts");
 static __device__ __align__(256) unsigned char scratch[kNoAllocScratchBytes];
 
@@ -129,6 +129,11 @@ struct oscars_ctx {
   hipEvent_t cal_ev[2] = {nullptr, nullptr};
 
   void* noalloc_scratch = nullptr;   // this device's `scratch` (oscars_evaluate_noalloc)
+  // Evaluation of an MLP: rows per pass, and (where that is more than the
+  // K * max_batch rows of act) two activation buffers and logits of its own.
+  int64_t eval_rows = 0;
+  void* eval_act[2] = {nullptr, nullptr};  // [eval_rows][widest hidden ld]
+  float* eval_logits = nullptr;            // [eval_rows][ld[L]]
   // Convolutional model (oscars_create_cnn): conv layers l = 1..L-1, the
   // classifier is layer L.  geometry[l] for l = 0 (the image) .. L-1.
   bool cnn = false;
@@ -169,6 +174,34 @@ void free_ctx(oscars_ctx* c) {
   for (hipEvent_t e : c->ev_pool) (void)hipEventDestroy(e);
   gemm_tuner_destroy(c->tuner);
   delete c;
+}
+
+// Evaluation forward passes take as many rows as they can: the launches of a
+// pass cost their latency whatever its rows.  An evaluation of an MLP runs
+// kEvalRows rows per pass in up to kEvalBytes of buffers of its own where the
+// local steps' activations (K * max_batch rows) hold fewer.
+constexpr int64_t kEvalRows = 8192;
+constexpr int64_t kEvalBytes = int64_t{32} << 20;
+
+hipError_t alloc_eval(oscars_ctx* c) {
+  const int64_t have = static_cast<int64_t>(c->K) * c->max_batch;
+  int64_t ld = 64;
+  for (int l = 1; l < c->L; ++l) ld = std::max(ld, c->ld[l]);
+  const int64_t act = ld * static_cast<int64_t>(c->esize), logits = c->ld[c->L] * 4;
+  c->eval_rows = std::min(kEvalRows, kEvalBytes / (2 * act + logits));
+  if (c->eval_rows <= have) {
+    c->eval_rows = have;
+    return hipSuccess;
+  }
+  void* p = nullptr;
+  const hipError_t e = hipMalloc(&p, static_cast<size_t>(c->eval_rows * (2 * act + logits)));
+  if (e != hipSuccess) return e;
+  c->allocs.push_back(p);
+  char* base = static_cast<char*>(p);
+  c->eval_act[0] = base;
+  c->eval_act[1] = base + c->eval_rows * act;
+  c->eval_logits = reinterpret_cast<float*>(base + 2 * c->eval_rows * act);
+  return hipSuccess;
 }
 
 hipError_t dev_alloc(oscars_ctx* c, size_t bytes, void** out) {
@@ -333,7 +366,7 @@ oscars_status oscars_create(oscars_ctx** out, const oscars_model* m, int32_t K, 
   }
   c->act.assign(c->L + 1, nullptr);
   c->delta.assign(c->L + 1, nullptr);
-  if (e == hipSuccess)  // act[0]: the gathered batch rows of the current step
+  if (e == hipSuccess && c->bf16)  // act[0]: the gathered batch rows of the current step
     e = dev_alloc(c, static_cast<size_t>(K) * c->act_slot(0) * c->esize, &c->act[0]);
   for (int l = 1; l <= c->L && e == hipSuccess; ++l) {
     const size_t n = static_cast<size_t>(K) * c->act_slot(l);
@@ -348,7 +381,7 @@ oscars_status oscars_create(oscars_ctx** out, const oscars_model* m, int32_t K, 
   // Split-K partials ([slot][chunk][batch][ld] fp32) for launches of every
   // active replica; the kernels split only whole-batch tiles (batches above
   // 128) whose K has more than one chunk.
-  if (e == hipSuccess && max_batch > 128) {
+  if (e == hipSuccess && c->bf16 && max_batch > 128) {
     constexpr int64_t kChunk = GEMM_KCHUNK;
     const int64_t kSplitSlots = K;
     int64_t need = 0;
@@ -370,6 +403,7 @@ oscars_status oscars_create(oscars_ctx** out, const oscars_model* m, int32_t K, 
     const int64_t rows = static_cast<int64_t>(K) * kPreTau * max_batch;
     e = ensure_tables(c, 64 + rows, rows);
   }
+  if (e == hipSuccess) e = alloc_eval(c);
   if (e == hipSuccess) e = alloc_calibration(c);
   if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
   if (e != hipSuccess) {
@@ -882,6 +916,154 @@ hipError_t choose_backward(oscars_ctx* c, int ns, const GemmArgs& gf, const Gemm
   return hipSuccess;
 }
 
+// Forward of layer l of an MLP over N rows: inputs `in` ([N][in_ld], or
+// dataset rows through `gather`), outputs `out`; params replica rep = order[z]
+// at master_in + rep * master_in_slot.
+GemmArgs f32_layer_args(const oscars_ctx* c, int l, const float* master_in, int64_t master_in_slot,
+                        const int32_t* order) {
+  GemmArgs g{};
+  g.a = master_in + c->w_off[l];
+  g.a_ld = c->dims[l - 1];
+  g.a_slot = master_in_slot;
+  g.a_by_order = 1;
+  g.master_in = master_in;
+  g.master_in_slot = master_in_slot;
+  g.w_off = c->w_off[l];
+  g.b_off = c->b_off[l];
+  g.order = order;
+  return g;
+}
+
+GemmArgs f32_forward_args(const oscars_ctx* c, int l, const float* master_in,
+                          int64_t master_in_slot, const int32_t* order, int N) {
+  GemmArgs g = f32_layer_args(c, l, master_in, master_in_slot, order);
+  g.M = c->dims[l];
+  g.N = N;
+  g.K = c->dims[l - 1];
+  g.a_ext = g.b_ext = g.K;
+  g.relu = l < c->L;
+  g.out_ld = c->ld[l];
+  return g;
+}
+
+F32HeadArgs f32_head_args(const oscars_ctx* c, const float* master_in, int64_t master_in_slot,
+                          const int32_t* order, int B) {
+  const int L = c->L;
+  F32HeadArgs h{};
+  h.B = B;
+  h.K = c->dims[L - 1];
+  h.C = c->dims[L];
+  h.act_ld = c->ld[L - 1];
+  h.master_in = master_in;
+  h.master_in_slot = master_in_slot;
+  h.w_off = c->w_off[L];
+  h.b_off = c->b_off[L];
+  h.order = order;
+  return h;
+}
+
+// One local step of the ns active slots of an fp32 MLP: forward, loss
+// gradient, backward-data, then every layer's update in one launch (after the
+// last launch that reads the weights).  With few classes the last layer's
+// forward, the softmax and its backward-data are one launch.
+hipError_t f32_step(oscars_ctx* c, float* replicas, const float* master_in, int64_t master_in_slot,
+                    const int32_t* order, const float* x, const int32_t* y, const int32_t* rows,
+                    int64_t rows_slot, int B, int ns, float lr, float* loss) {
+  const int L = c->L;
+  hipError_t e = hipSuccess;
+  const bool head = c->dims[L] <= F32_HEAD_CLASSES;
+  auto fact = [&](int l) { return static_cast<float*>(c->act[l]); };
+  auto fdelta = [&](int l) { return static_cast<float*>(c->delta[l]); };
+  for (int l = 1; l <= (head ? L - 1 : L) && e == hipSuccess; ++l) {
+    GemmArgs g = f32_forward_args(c, l, master_in, master_in_slot, order, B);
+    if (l == 1) {
+      g.b = x;
+      g.b_ld = c->dims[0];
+      g.gather = rows;
+      g.gather_slot = rows_slot;
+    } else {
+      g.b = c->act[l - 1];
+      g.b_ld = c->ld[l - 1];
+      g.b_slot = c->act_slot(l - 1);
+    }
+    g.out = l < L ? c->act[l] : static_cast<void*>(c->logits);
+    g.out_slot = c->act_slot(l);
+    e = timed(c, OSCARS_KERNEL_FWD,
+              [&] { return launch_gemm(g, GEMM_FWD, false, ns, c->stream, c->tuner); });
+  }
+  if (e != hipSuccess) return e;
+  if (head) {
+    F32HeadArgs h = f32_head_args(c, master_in, master_in_slot, order, B);
+    h.act = L > 1 ? fact(L - 1) : x;
+    h.act_slot = L > 1 ? c->act_slot(L - 1) : 0;
+    h.act_gather = L == 1;
+    h.y = y;
+    h.gather = rows;
+    h.gather_slot = rows_slot;
+    h.delta = fdelta(L);
+    h.delta_ld = c->ld[L];
+    h.delta_slot = c->act_slot(L);
+    h.loss = loss;
+    h.loss_slot = rows_slot;
+    if (L > 1) {
+      h.below = fdelta(L - 1);
+      h.below_ld = c->ld[L - 1];
+      h.below_slot = c->act_slot(L - 1);
+    }
+    e = timed(c, OSCARS_KERNEL_SOFTMAX, [&] { return launch_f32_head(h, ns, c->stream); });
+  } else {
+    e = timed(c, OSCARS_KERNEL_SOFTMAX, [&] {
+      return launch_softmax_ce(c->logits, c->ld[L], c->act_slot(L), c->dims[L], B, y, rows,
+                               rows_slot, c->delta[L], false, loss, rows_slot, ns, c->stream);
+    });
+  }
+  for (int l = head ? L - 1 : L; l > 1 && e == hipSuccess; --l) {
+    GemmArgs g = f32_layer_args(c, l, master_in, master_in_slot, order);
+    g.M = c->dims[l - 1];
+    g.N = B;
+    g.K = c->dims[l];
+    g.a_ext = g.M;
+    g.b_ext = static_cast<int>(round_up(g.K, 8));  // delta rows are zero-padded
+    g.b = c->delta[l];
+    g.b_ld = c->ld[l];
+    g.b_slot = c->act_slot(l);
+    g.out = c->delta[l - 1];
+    g.out_ld = c->ld[l - 1];
+    g.out_slot = c->act_slot(l - 1);
+    g.mask = c->act[l - 1];
+    g.mask_ld = c->ld[l - 1];
+    g.mask_slot = c->act_slot(l - 1);
+    e = timed(c, OSCARS_KERNEL_DGRAD,
+              [&] { return launch_gemm(g, GEMM_DGRAD, false, ns, c->stream, c->tuner); });
+  }
+  if (e != hipSuccess) return e;
+  F32UpdateArgs u{};
+  u.n_layers = L;
+  u.B = B;
+  u.gather = rows;
+  u.gather_slot = rows_slot;
+  u.master = replicas;
+  u.master_slot = c->n_pad;
+  u.master_in = master_in;
+  u.master_in_slot = master_in_slot;
+  u.order = order;
+  u.lr = lr;
+  for (int l = 1; l <= L; ++l) {
+    F32UpdateLayer& f = u.layer[l - 1];
+    f.M = c->dims[l - 1];
+    f.N = c->dims[l];
+    f.a = l == 1 ? x : fact(l - 1);
+    f.a_ld = c->ld[l - 1];
+    f.a_slot = l == 1 ? 0 : c->act_slot(l - 1);
+    f.d = fdelta(l);
+    f.d_ld = c->ld[l];
+    f.d_slot = c->act_slot(l);
+    f.w_off = c->w_off[l];
+    f.b_off = c->b_off[l];
+  }
+  return timed(c, OSCARS_KERNEL_WGRAD, [&] { return launch_f32_update(u, ns, c->stream); });
+}
+
 // tau_k local steps of every worker.  start == nullptr: worker k starts from
 // replica k.  Otherwise every worker starts from `start` (the global model of
 // a round): the first step reads `start` and writes replica k; workers with
@@ -988,6 +1170,21 @@ oscars_status run_local_steps(oscars_ctx* c, float* replicas, const float* start
       if (e == hipSuccess)
         e = cnn_backward(c, replicas, min, min_slot, d_order, s->x, rows_j, rows_slot, B, ns, lr,
                          fused_head ? &head : nullptr);
+      if (e != hipSuccess) return hip_fail(e);
+    }
+    for (int k = 0; k < K; ++k) c->cursors[k] += tau[k];
+    return OSCARS_OK;
+  }
+
+  if (!c->bf16) {
+    for (int j = 0; j < tau_max; ++j) {
+      int ns = 0;
+      while (ns < n_slots && tau[order[ns]] > j) ++ns;
+      const bool from_start = start && j == 0;
+      e = f32_step(c, replicas, from_start ? start : replicas, from_start ? 0 : c->n_pad, d_order,
+                   static_cast<const float*>(s->x), s->y, d_rows + static_cast<int64_t>(j) * B,
+                   static_cast<int64_t>(tau_max) * B, B, ns, lr,
+                   c->loss_dev + static_cast<int64_t>(j) * B);
       if (e != hipSuccess) return hip_fail(e);
     }
     for (int k = 0; k < K; ++k) c->cursors[k] += tau[k];
@@ -1240,22 +1437,24 @@ oscars_status check_evaluate(const oscars_ctx* c, const float* params, const voi
 }
 
 // Device bytes of an evaluation's temporaries: results (double loss, int64
-// count), then the row table [64 + n] int32, per-row losses [n] fp32 and
-// correct flags [n] int32, each part 256-byte aligned.
+// count), then the row table [64 + n + 64] int32, per-row losses [n + 64] fp32
+// and correct flags [n + 64] int32 (the last pass of a convolutional model
+// rounds its rows up to whole slots), each part 256-byte aligned.
 struct EvalLayout {  // kNoAllocScratchBytes holds it for OSCARS_EVAL_NOALLOC_MAX_ROWS rows
   int64_t table, loss, hit, end;
   explicit EvalLayout(int64_t n) {
     table = 256;
-    loss = table + round_up((64 + n) * 4, 256);
-    hit = loss + round_up(n * 4, 256);
-    end = hit + round_up(n * 4, 256);
+    loss = table + round_up((128 + n) * 4, 256);
+    hit = loss + round_up((64 + n) * 4, 256);
+    end = hit + round_up((64 + n) * 4, 256);
   }
 };
 
 size_t eval_bytes(int64_t n_rows) { return static_cast<size_t>(EvalLayout(n_rows).end); }
 
-// The forward pass of the local steps over rows 0 .. n_rows-1, max_batch rows
-// at a time, into the temporaries at `buf` (eval_bytes(n_rows) bytes of
+// The forward pass of the local steps over rows 0 .. n_rows-1, as many rows at
+// a time as the workspace holds (eval_rows; a row's result does not depend on
+// the rows it shares a launch with), into the temporaries at `buf` (eval_bytes(n_rows) bytes of
 // device memory); then the fixed-order reduction and a copy of its two
 // results to the host.  tune = false: no GEMM tiling is timed (no events are
 // created); the tilings the context has decided, else the fixed rule.  Every
@@ -1272,60 +1471,66 @@ hipError_t run_evaluate(oscars_ctx* c, const float* params, const void* x, const
   int32_t* d_tab = reinterpret_cast<int32_t*>(base + lay.table);
   float* d_loss = reinterpret_cast<float*>(base + lay.loss);
   int32_t* d_hit = reinterpret_cast<int32_t*>(base + lay.hit);
-  const int L = c->L, Bmax = c->max_batch;
+  const int L = c->L;
   const uint32_t prof_mask = c->prof_mask;  // evaluation launches are never profiled
   c->prof_mask = 0;
   hipError_t e = launch_eval_rows(d_tab, n_rows, c->stream);
-  // Weights as the forward pass reads them: the bf16 copy of params (one
-  // cast into the start-model buffer) or params themselves.
-  if (e == hipSuccess && c->bf16)
-    e = launch_cast_bf16(params, 0, d_tab, c->gq, 0, c->n_pad, 1, c->stream);
-  for (int64_t i0 = 0; i0 < n_rows && e == hipSuccess; i0 += Bmax) {
-    const int N = static_cast<int>(std::min<int64_t>(Bmax, n_rows - i0));
-    const int32_t* rows = d_tab + 64 + i0;
-    if (c->cnn) {
-      e = cnn_forward(c, params, 0, d_tab, x, rows, 0, N, 1);
+  if (c->cnn) {
+    // K x max_batch rows per pass, in up to K slots of equal size that all
+    // read the same parameters (the last pass repeats the last row to fill
+    // its slots)
+    for (int64_t i0 = 0; i0 < n_rows && e == hipSuccess;) {
+      const int64_t left = n_rows - i0;
+      const int ns = static_cast<int>(
+          std::min<int64_t>(c->K, (left + c->max_batch - 1) / c->max_batch));
+      const int B = static_cast<int>(std::min<int64_t>(c->max_batch, (left + ns - 1) / ns));
+      const int32_t* rows = d_tab + 64 + i0;
+      e = cnn_forward(c, params, 0, d_tab, x, rows, B, B, ns);
       if (e == hipSuccess)
-        e = launch_softmax_ce(c->logits, c->ld[L], c->act_slot(L), c->dims[L], N, y, rows, 0,
-                              c->delta[L], false, d_loss + i0, 0, 1, c->stream, d_hit + i0);
-      continue;
+        e = launch_softmax_ce(c->logits, c->ld[L], c->act_slot(L), c->dims[L], B, y, rows, B,
+                              nullptr, false, d_loss + i0, B, ns, c->stream, d_hit + i0);
+      i0 += static_cast<int64_t>(ns) * B;
     }
-    for (int l = 1; l <= L && e == hipSuccess; ++l) {
-      GemmArgs g{};
-      g.M = c->dims[l];
-      g.N = N;
-      g.K = c->dims[l - 1];
-      g.a_ext = g.K;
-      g.b_ext = g.K;
-      g.a = c->bf16 ? static_cast<const void*>(c->gq + c->w_off[l])
-                    : static_cast<const void*>(params + c->w_off[l]);
-      g.a_ld = c->dims[l - 1];
-      if (l == 1) {
-        g.b = x;
-        g.b_ld = c->dims[0];
-        g.gather = rows;
-        g.rows_out = c->act[0];
-        g.rows_out_ld = c->ld[0];
-      } else {
-        g.b = c->act[l - 1];
-        g.b_ld = c->ld[l - 1];
+  } else {
+    // Weights as the forward pass reads them: the bf16 copy of params (one
+    // cast into the start-model buffer) or params themselves.
+    if (e == hipSuccess && c->bf16)
+      e = launch_cast_bf16(params, 0, d_tab, c->gq, 0, c->n_pad, 1, c->stream);
+    const bool own = c->eval_act[0] != nullptr;
+    auto act = [&](int l) { return own ? c->eval_act[l & 1] : c->act[l]; };
+    float* logits = own ? c->eval_logits : c->logits;
+    const bool head = !c->bf16 && c->dims[L] <= F32_HEAD_CLASSES;
+    for (int64_t i0 = 0; i0 < n_rows && e == hipSuccess; i0 += c->eval_rows) {
+      const int N = static_cast<int>(std::min<int64_t>(c->eval_rows, n_rows - i0));
+      const void* rows0 = static_cast<const char*>(x) +
+                          i0 * c->dims[0] * static_cast<int64_t>(c->esize);
+      for (int l = 1; l <= (head ? L - 1 : L) && e == hipSuccess; ++l) {
+        GemmArgs g = f32_forward_args(c, l, params, 0, d_tab, N);
+        if (c->bf16) {
+          g.a = c->gq + c->w_off[l];
+          g.part = c->part;
+          g.part_cap = c->part_cap;
+        }
+        g.master = const_cast<float*>(params);  // not written by the forward pass
+        g.b = l == 1 ? rows0 : act(l - 1);
+        g.b_ld = l == 1 ? c->dims[0] : c->ld[l - 1];
+        g.out = l < L ? act(l) : static_cast<void*>(logits);
+        g.out_bf16 = l < L && c->bf16;
+        e = launch_gemm(g, GEMM_FWD, c->bf16, 1, c->stream, c->tuner, tune);
       }
-      g.master = const_cast<float*>(params);  // not written by the forward pass
-      g.master_in = params;
-      g.b_off = c->b_off[l];
-      g.w_off = c->w_off[l];
-      g.order = d_tab;
-      g.part = c->part;
-      g.part_cap = c->part_cap;
-      g.out = l < L ? c->act[l] : static_cast<void*>(c->logits);
-      g.relu = l < L;
-      g.out_bf16 = l < L && c->bf16;
-      g.out_ld = c->ld[l];
-      e = launch_gemm(g, GEMM_FWD, c->bf16, 1, c->stream, c->tuner, tune);
+      if (e != hipSuccess) break;
+      if (head) {
+        F32HeadArgs h = f32_head_args(c, params, 0, d_tab, N);
+        h.act = static_cast<const float*>(L > 1 ? act(L - 1) : rows0);
+        h.y = y + i0;
+        h.loss = d_loss + i0;
+        h.correct = d_hit + i0;
+        e = launch_f32_head(h, 1, c->stream);
+      } else {
+        e = launch_softmax_ce(logits, c->ld[L], 0, c->dims[L], N, y + i0, nullptr, 0, nullptr,
+                              c->bf16, d_loss + i0, 0, 1, c->stream, d_hit + i0);
+      }
     }
-    if (e == hipSuccess)
-      e = launch_softmax_ce(c->logits, c->ld[L], c->act_slot(L), c->dims[L], N, y, rows, 0,
-                            c->delta[L], c->bf16, d_loss + i0, 0, 1, c->stream, d_hit + i0);
   }
   c->prof_mask = prof_mask;
   if (e == hipSuccess)
