@@ -7,11 +7,12 @@
 // the waves read their MFMA operands straight from memory (L1 / L2) into
 // registers, one or more K groups ahead of the products: no LDS staging and
 // no barrier in any K loop, and waves drift freely.  LDS is used once, to add
-// the four K slices of an output tile.
+// the K slices of an output tile.
 //
 // K order of forward and backward-data: slice j = 0..3 sums the 32-wide K
 // tiles j, j + 4, j + 8, ... from zero in K order (one wave per slice), the
-// output is ((s0 + s1) + s2) + s3.  It depends only on K, not on the tile
+// output is ((s0 + s1) + s2) + s3 (the classifier head: eight slices).  It
+// depends only on K, not on the tile
 // shape or on how many replicas share a launch, so every tiling gives the
 // same bits.  Backward-weight sums the batch in row order.
 //
@@ -31,8 +32,10 @@ namespace {
 
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int SLICES = 4;  // K slices of forward / backward-data = waves per workgroup
+constexpr int HEAD_SLICES = 8;  // of the classifier head
 constexpr int KTILE = 32;  // K tile dealt to the slices in turn
 
 template <int W> struct Vec;
@@ -43,6 +46,17 @@ template <> struct Vec<4> { typedef f32x4 T; };
 // Lanes with nothing to load read these zeros (no branch around a load).
 __device__ __attribute__((aligned(16))) float f32_zero[4];
 
+// a * b elements in one instruction (rows and strides are below 2^31).
+__device__ __forceinline__ int64_t offset_of(int a, int64_t b) {
+  return static_cast<int64_t>(static_cast<uint64_t>(static_cast<uint32_t>(a)) *
+                              static_cast<uint32_t>(b));
+}
+
+// Keeps the loads issued before it above the products that follow: the
+// scheduler otherwise moves them down to their first use, which then waits
+// out the whole latency.
+__device__ __forceinline__ void loads_first() { __builtin_amdgcn_sched_barrier(0); }
+
 // Flattened workgroup id -> work item: the workgroups that the hardware puts
 // on one XCD (id mod 8) take one contiguous range of the T work items.
 __device__ __forceinline__ int xcd_item(int id, int T) {
@@ -51,13 +65,15 @@ __device__ __forceinline__ int xcd_item(int id, int T) {
 }
 
 // K groups (16 deep) a wave loads at once: enough bytes in flight for small
-// tiles, few registers for large ones.
+// tiles, few registers for large ones.  A slice is summed in whole pairs of
+// such loads (zeros past K): with a test between the products the compiler
+// sinks the loads of the next groups behind it, next to their use.
 template <int MI, int NJ> struct Depth {
-  static constexpr int G = MI + NJ >= 8 ? 1 : (MI + NJ >= 5 ? 2 : (MI + NJ >= 4 ? 3 : 6));
+  static constexpr int G = MI + NJ >= 8 ? 1 : (MI + NJ >= 4 ? 2 : 4);
 };
 
 // The operands of G consecutive K groups of one slice.
-template <bool TRANS, int MI, int NJ, int G>
+template <bool TRANS, int MI, int NJ, int G, int S>
 struct Frags {
   float a[G][MI][4], b[G][NJ][4];
 
@@ -72,7 +88,7 @@ struct Frags {
 #pragma unroll
     for (int g = 0; g < G; ++g) {
       const int q = q0 + g;
-      const int k = KTILE * (slice + SLICES * (q >> 1)) + 16 * (q & 1) + kq;
+      const int k = KTILE * (slice + S * (q >> 1)) + 16 * (q & 1) + kq;
       if constexpr (!TRANS) {
         const bool ok = k < K;  // K is a multiple of 4: whole chunks
 #pragma unroll
@@ -84,7 +100,8 @@ struct Frags {
       } else {
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
-          const float* p = k + t < K ? a_row[0] + static_cast<int64_t>(k + t) * a_ld : f32_zero;
+          const float* row = a_row[0] + offset_of(k + t, a_ld);
+          const float* p = k + t < K ? row : f32_zero;
           const typename Vec<MI>::T v = *reinterpret_cast<const typename Vec<MI>::T*>(p);
           if constexpr (MI == 1) a[g][0][t] = v;
           else {
@@ -103,11 +120,9 @@ struct Frags {
     }
   }
 
-  // Products of the groups below nq.
-  __device__ __forceinline__ void mma(f32x4 (&acc)[MI][NJ], int q0, int nq) const {
+  __device__ __forceinline__ void mma(f32x4 (&acc)[MI][NJ]) const {
 #pragma unroll
     for (int g = 0; g < G; ++g) {
-      if (q0 + g >= nq) break;
 #pragma unroll
       for (int t = 0; t < 4; ++t)
 #pragma unroll
@@ -121,7 +136,7 @@ struct Frags {
 };
 
 // One K slice of a 16 MI x 16 NJ tile.
-template <bool TRANS, int MI, int NJ>
+template <bool TRANS, int S, int MI, int NJ>
 __device__ __forceinline__ void slice_products(f32x4 (&acc)[MI][NJ],
                                                const float* const (&a_row)[MI],
                                                const float* const (&b_row)[NJ], int64_t a_ld, int K,
@@ -131,15 +146,17 @@ __device__ __forceinline__ void slice_products(f32x4 (&acc)[MI][NJ],
 #pragma unroll
     for (int j = 0; j < NJ; ++j) acc[i][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
   const int tiles = (K + KTILE - 1) / KTILE;
-  const int nq = tiles > slice ? 2 * ((tiles - slice + SLICES - 1) / SLICES) : 0;
+  const int nq = tiles > slice ? 2 * ((tiles - slice + S - 1) / S) : 0;
   constexpr int G = Depth<MI, NJ>::G;
-  Frags<TRANS, MI, NJ, G> f0, f1;
+  Frags<TRANS, MI, NJ, G, S> f0, f1;
   f0.load(a_row, b_row, a_ld, K, b_ext, slice, 0, lane);
   for (int q0 = 0; q0 < nq; q0 += 2 * G) {
     f1.load(a_row, b_row, a_ld, K, b_ext, slice, q0 + G, lane);
-    f0.mma(acc, q0, nq);
+    loads_first();
+    f0.mma(acc);
     f0.load(a_row, b_row, a_ld, K, b_ext, slice, q0 + 2 * G, lane);
-    f1.mma(acc, q0 + G, nq);
+    loads_first();
+    f1.mma(acc);
   }
 }
 
@@ -164,8 +181,11 @@ __device__ __forceinline__ int quad_row(int qd, int lane) {
 template <int MODE, int MI, int NJ>
 __global__ __launch_bounds__(64 * SLICES) void f32_gemm_kernel(GemmArgs g) {
   constexpr bool TRANS = MODE == GEMM_DGRAD;
+  // The slices meet in LDS, at most 32 columns at a time (64 x 64 tiles: two
+  // phases of 70 KB).
   constexpr int TM = 16 * MI, TN = 16 * NJ, LD = TM + 4;
-  __shared__ __attribute__((aligned(16))) float red[SLICES][TN][LD];
+  constexpr int NP = NJ > 2 ? 2 : 1, PN = TN / NP;  // phases, columns per phase
+  __shared__ __attribute__((aligned(16))) float red[SLICES][PN][LD];
   const int lane = threadIdx.x & 63;
   const int slice = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
   const int work = xcd_item(blockIdx.y * gridDim.x + blockIdx.x, gridDim.x * gridDim.y);
@@ -194,54 +214,60 @@ __global__ __launch_bounds__(64 * SLICES) void f32_gemm_kernel(GemmArgs g) {
     b_row[j] = B + row * g.b_ld;
   }
   f32x4 acc[MI][NJ];
-  slice_products<TRANS>(acc, a_row, b_row, g.a_ld, g.K, g.b_ext, slice, lane);
+  slice_products<TRANS, SLICES>(acc, a_row, b_row, g.a_ld, g.K, g.b_ext, slice, lane);
 
-  // The slices' sums through LDS, added in slice order; a thread takes four
-  // consecutive rows m of column n.
-  constexpr int QUADS = MI * 4 * TN / (64 * SLICES);  // per thread
-  constexpr int PER = QUADS > 0 ? QUADS : 1;
-  f32x4 aux[PER];  // bias, or the activations that mask the delta
+  // A thread takes four consecutive rows m of column n.
+  constexpr int PER = (MI * 4 * PN + 64 * SLICES - 1) / (64 * SLICES);  // per thread and phase
+  f32x4 aux[NP][PER];  // bias, or the activations that mask the delta
   const float* bias = g.master_in + static_cast<int64_t>(rep) * g.master_in_slot + g.b_off;
 #pragma unroll
-  for (int p = 0; p < PER; ++p) {
-    const int c = threadIdx.x + 64 * SLICES * p;
-    const int n = min(n0 + c / (4 * MI), g.N - 1), m = min(m0 + 4 * (c % (4 * MI)), (g.M - 1) & ~3);
-    // bias segments and activation rows are padded to 64 elements
-    aux[p] = *reinterpret_cast<const f32x4*>(
-        MODE == GEMM_FWD ? bias + m
-                         : static_cast<const float*>(g.mask) + z * g.mask_slot +
-                               static_cast<int64_t>(n) * g.mask_ld + m);
-  }
+  for (int ph = 0; ph < NP; ++ph)
 #pragma unroll
-  for (int j = 0; j < NJ; ++j)
-#pragma unroll
-    for (int qd = 0; qd < MI; ++qd)
-      *reinterpret_cast<f32x4*>(&red[slice][16 * j + (lane & 15)][quad_row<TRANS, MI>(qd, lane)]) =
-          acc_quad<TRANS>(acc, j, qd);
-  __syncthreads();
-#pragma unroll
-  for (int p = 0; p < PER; ++p) {
-    const int c = threadIdx.x + 64 * SLICES * p;
-    const int n = c / (4 * MI), m = 4 * (c % (4 * MI));
-    if (n >= TN || n0 + n >= g.N || m0 + m >= g.M) continue;
-    f32x4 v = *reinterpret_cast<const f32x4*>(&red[0][n][m]);
-#pragma unroll
-    for (int s = 1; s < SLICES; ++s) v = v + *reinterpret_cast<const f32x4*>(&red[s][n][m]);
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      if constexpr (MODE == GEMM_FWD) {
-        v[e] += aux[p][e];
-        if (g.relu) v[e] = fmaxf(v[e], 0.0f);
-      } else {
-        v[e] = aux[p][e] > 0.0f ? v[e] : 0.0f;
-      }
+    for (int p = 0; p < PER; ++p) {
+      const int c = threadIdx.x + 64 * SLICES * p;
+      const int n = min(n0 + ph * PN + c / (4 * MI), g.N - 1);
+      const int m = min(m0 + 4 * (c % (4 * MI)), (g.M - 1) & ~3);
+      // bias segments and activation rows are padded to 64 elements
+      aux[ph][p] = *reinterpret_cast<const f32x4*>(
+          MODE == GEMM_FWD ? bias + m
+                           : static_cast<const float*>(g.mask) + z * g.mask_slot +
+                                 static_cast<int64_t>(n) * g.mask_ld + m);
     }
-    float* o = static_cast<float*>(g.out) + z * g.out_slot +
-               static_cast<int64_t>(n0 + n) * g.out_ld + m0 + m;
-    if (m0 + m + 4 <= g.M) {
-      *reinterpret_cast<f32x4*>(o) = v;
-    } else {
-      for (int e = 0; m0 + m + e < g.M; ++e) o[e] = v[e];
+#pragma unroll
+  for (int ph = 0; ph < NP; ++ph) {
+    if (ph > 0) __syncthreads();
+#pragma unroll
+    for (int j = 0; j < NJ / NP; ++j)
+#pragma unroll
+      for (int qd = 0; qd < MI; ++qd)
+        *reinterpret_cast<f32x4*>(
+            &red[slice][16 * j + (lane & 15)][quad_row<TRANS, MI>(qd, lane)]) =
+            acc_quad<TRANS>(acc, ph * (NJ / NP) + j, qd);
+    __syncthreads();
+#pragma unroll
+    for (int p = 0; p < PER; ++p) {
+      const int c = threadIdx.x + 64 * SLICES * p;
+      const int nl = c / (4 * MI), n = n0 + ph * PN + nl, m = 4 * (c % (4 * MI));
+      if (nl >= PN || n >= g.N || m0 + m >= g.M) continue;
+      f32x4 v = *reinterpret_cast<const f32x4*>(&red[0][nl][m]);
+#pragma unroll
+      for (int s = 1; s < SLICES; ++s) v = v + *reinterpret_cast<const f32x4*>(&red[s][nl][m]);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        if constexpr (MODE == GEMM_FWD) {
+          v[e] += aux[ph][p][e];
+          if (g.relu) v[e] = fmaxf(v[e], 0.0f);
+        } else {
+          v[e] = aux[ph][p][e] > 0.0f ? v[e] : 0.0f;
+        }
+      }
+      float* o = static_cast<float*>(g.out) + z * g.out_slot + static_cast<int64_t>(n) * g.out_ld +
+                 m0 + m;
+      if (m0 + m + 4 <= g.M) {
+        *reinterpret_cast<f32x4*>(o) = v;
+      } else {
+        for (int e = 0; m0 + m + e < g.M; ++e) o[e] = v[e];
+      }
     }
   }
 }
@@ -252,9 +278,9 @@ __global__ __launch_bounds__(64 * SLICES) void f32_gemm_kernel(GemmArgs g) {
 // layer below (as f32_gemm_kernel's backward-data).  One launch instead of
 // three whose own latency was all they cost.
 template <int MI, bool DGRAD>
-__global__ __launch_bounds__(64 * SLICES) void f32_head_kernel(F32HeadArgs h) {
+__global__ __launch_bounds__(64 * HEAD_SLICES) void f32_head_kernel(F32HeadArgs h) {
   constexpr int TM = 16 * MI, LD = TM + 4, ROWS = 16;
-  __shared__ __attribute__((aligned(16))) float red[SLICES][ROWS][LD];
+  __shared__ __attribute__((aligned(16))) float red[HEAD_SLICES][ROWS][LD];
   __shared__ __attribute__((aligned(16))) float dl[ROWS][LD];
   const int lane = threadIdx.x & 63, c16 = lane & 15, gq = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
@@ -270,28 +296,28 @@ __global__ __launch_bounds__(64 * SLICES) void f32_head_kernel(F32HeadArgs h) {
              (h.act_gather ? static_cast<int64_t>(h.gather[z * h.gather_slot + nb])
                            : static_cast<int64_t>(nb)) * h.act_ld;
   // labels and bias before the products: their latency is hidden
-  int label[ROWS / SLICES];
+  int label[ROWS / HEAD_SLICES];
 #pragma unroll
-  for (int r = 0; r < ROWS / SLICES; ++r) {
-    const int b = min(n0 + wave * (ROWS / SLICES) + r, h.B - 1);
+  for (int r = 0; r < ROWS / HEAD_SLICES; ++r) {
+    const int b = min(n0 + wave * (ROWS / HEAD_SLICES) + r, h.B - 1);
     label[r] = h.y[h.gather ? h.gather[z * h.gather_slot + b] : b];
   }
   const float bias = master[h.b_off + min(lane, h.C - 1)];
   f32x4 acc[MI][1];
-  slice_products<false>(acc, a_row, b_row, h.K, h.K, h.K, wave, lane);
+  slice_products<false, HEAD_SLICES>(acc, a_row, b_row, h.K, h.K, h.K, wave, lane);
 #pragma unroll
   for (int i = 0; i < MI; ++i)
     *reinterpret_cast<f32x4*>(&red[wave][c16][16 * i + 4 * gq]) = acc[i][0];
   __syncthreads();
-  // A wave takes four rows, lane c the class c (the sums as softmax_ce_kernel).
+  // A wave takes two rows, lane c the class c (the sums as softmax_ce_kernel).
   const float invB = 1.0f / static_cast<float>(h.B);
 #pragma unroll
-  for (int r = 0; r < ROWS / SLICES; ++r) {
-    const int row = wave * (ROWS / SLICES) + r, b = n0 + row;
+  for (int r = 0; r < ROWS / HEAD_SLICES; ++r) {
+    const int row = wave * (ROWS / HEAD_SLICES) + r, b = n0 + row;
     const int cl = min(lane, TM - 1);
     float v = red[0][row][cl];
 #pragma unroll
-    for (int s = 1; s < SLICES; ++s) v += red[s][row][cl];
+    for (int s = 1; s < HEAD_SLICES; ++s) v += red[s][row][cl];
     v += bias;
     const bool in = lane < h.C;
     if (!in) v = -INFINITY;
@@ -326,7 +352,7 @@ __global__ __launch_bounds__(64 * SLICES) void f32_head_kernel(F32HeadArgs h) {
       for (int t = 0; t < 4; ++t) bd[s][t] = v[t];
     }
     const int b = n0 + c16;
-    for (int m0 = 64 * wave; m0 < h.K; m0 += 64 * SLICES) {
+    for (int m0 = 64 * wave; m0 < h.K; m0 += 64 * HEAD_SLICES) {
       const int m = m0 + 4 * c16;
       const float* col = W + (m < h.K ? m : 0);
       f32x4 w[MI][4];
@@ -378,28 +404,56 @@ __global__ __launch_bounds__(64 * SLICES) void f32_head_kernel(F32HeadArgs h) {
 // Backward-weight and the SGD update of every layer in one launch (nothing
 // reads the weights after the last backward-data launch).  A workgroup of 2 x
 // 2 waves covers 32 T inputs x 32 T outputs of one layer, a wave 16 T x 16 T:
-// dW[o][i] over the batch, then W <- W - lr dW.  The bias gradient rides on
-// the waves of the first input tile as a product with ones, folded every 64
-// rows.
-template <int T, bool GATHER>
+// dW[o][i] over the batch, then W <- W - lr dW.  The biases have workgroups of
+// their own (64 outputs each): blocks of 64 batch rows row by row, the block
+// sums left to right.
+constexpr int UPDATE_ROWS = 1024 + 80;  // largest batch and the groups read ahead
+template <int T>
 __global__ __launch_bounds__(256) void f32_update_kernel(F32UpdateArgs u) {
-  __shared__ int32_t rows[GATHER ? 1024 : 1];
+  __shared__ __attribute__((aligned(16))) int32_t rows[UPDATE_ROWS];  // of the activations
+  __shared__ float bias_sum[16][64];  // of the blocks of 64 batch rows
   typedef typename Vec<T>::T V;
   const int lane = threadIdx.x & 63, c16 = lane & 15, gq = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
   const int work = xcd_item(blockIdx.y * gridDim.x + blockIdx.x, gridDim.x * gridDim.y);
   const int z = work / gridDim.x, wg = work % gridDim.x;
+  // one load of the whole table instead of one per layer, each waiting for
+  // the last (entries past the last layer are INT_MAX)
   int l = 0;
-  while (l + 1 < u.n_layers && wg >= u.layer[l + 1].first_wg) ++l;
+#pragma unroll
+  for (int i = 1; i < F32_UPDATE_LAYERS; ++i) l += wg >= u.first_wg[i] ? 1 : 0;
   const F32UpdateLayer& y = u.layer[l];
   const int rep = u.order[z];
-  const int gm = (y.M + 32 * T - 1) / (32 * T), tile = wg - y.first_wg;
+  const int gm = (y.M + 32 * T - 1) / (32 * T), tile = wg - u.first_wg[l];
   const int m0 = (tile % gm * 2 + (wave & 1)) * 16 * T;
   const int n0 = (tile / gm * 2 + (wave >> 1)) * 16 * T;
-  const bool gathered = GATHER && l == 0;
-  if (gathered) {
-    for (int b = threadIdx.x; b < u.B; b += 256) rows[b] = u.gather[z * u.gather_slot + b];
+  const bool gathered = l == 0 && u.gather != nullptr;
+  for (int b = threadIdx.x; b < UPDATE_ROWS; b += 256)
+    rows[b] = b >= u.B ? 0 : (gathered ? u.gather[z * u.gather_slot + b] : b);
+  __syncthreads();
+  if (tile >= y.tiles) {  // the biases of 64 outputs
+    const int n = (tile - y.tiles) * 64 + lane, blocks = (u.B + 63) / 64;
+    const float* D = y.d + z * y.d_slot + n;  // rows padded to 64
+    for (int b = wave; b < blocks; b += 4) {
+      float sum = 0.0f;
+      for (int k = 64 * b; k < 64 * b + 64; k += 16) {
+        float v[16];
+#pragma unroll
+        for (int e = 0; e < 16; ++e) v[e] = *(k + e < u.B ? D + offset_of(k + e, y.d_ld) : f32_zero);
+#pragma unroll
+        for (int e = 0; e < 16; ++e) sum += v[e];
+      }
+      bias_sum[b][lane] = sum;
+    }
     __syncthreads();
+    if (wave == 0 && n < y.N) {
+      float db = bias_sum[0][lane];
+      for (int b = 1; b < blocks; ++b) db += bias_sum[b][lane];
+      const int64_t at = static_cast<int64_t>(rep) * u.master_slot + y.b_off + n;
+      u.master[at] = fmaf(-u.lr, db, u.master_in[static_cast<int64_t>(rep) * u.master_in_slot +
+                                                 y.b_off + n]);
+    }
+    return;
   }
   if (m0 >= y.M || n0 >= y.N) return;
   // Columns past M repeat column 0 (never stored); delta rows are padded to 64.
@@ -407,14 +461,18 @@ __global__ __launch_bounds__(256) void f32_update_kernel(F32UpdateArgs u) {
   const float* A = y.a + z * y.a_slot + (ma < y.M ? ma : 0);
   const float* D = y.d + z * y.d_slot + n0 + T * c16;
   float a[2][T][4], b[2][T][4];
+  i32x4 row[2];  // of the group loaded next into each set
+  auto load_rows = [&](int set, int s) {
+    row[set] = *reinterpret_cast<const i32x4*>(&rows[16 * s + 4 * gq]);
+  };
   auto load = [&](int set, int s) {
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
       const int k = 16 * s + 4 * gq + t;
-      const bool ok = k < u.B;
-      const int64_t row = gathered ? rows[ok ? k : 0] : k;
-      const V va = *reinterpret_cast<const V*>(ok ? A + row * y.a_ld : f32_zero);
-      const V vb = *reinterpret_cast<const V*>(ok ? D + static_cast<int64_t>(k) * y.d_ld : f32_zero);
+      const float* pa = A + offset_of(row[set][t], y.a_ld);
+      const float* pd = D + offset_of(k, y.d_ld);
+      const V va = *reinterpret_cast<const V*>(k < u.B ? pa : f32_zero);
+      const V vb = *reinterpret_cast<const V*>(k < u.B ? pd : f32_zero);
 #pragma unroll
       for (int i = 0; i < T; ++i) {
         a[set][i][t] = va[i];
@@ -422,15 +480,12 @@ __global__ __launch_bounds__(256) void f32_update_kernel(F32UpdateArgs u) {
       }
     }
   };
-  f32x4 acc[T][T], bacc[T], btot[T];
+  f32x4 acc[T][T];
 #pragma unroll
-  for (int j = 0; j < T; ++j) {
-    bacc[j] = btot[j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+  for (int j = 0; j < T; ++j)
 #pragma unroll
     for (int i = 0; i < T; ++i) acc[i][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-  }
-  const bool with_bias = m0 == 0;
-  auto mma = [&](int set, int s) {
+  auto mma = [&](int set) {
 #pragma unroll
     for (int t = 0; t < 4; ++t)
 #pragma unroll
@@ -439,52 +494,47 @@ __global__ __launch_bounds__(256) void f32_update_kernel(F32UpdateArgs u) {
         for (int j = 0; j < T; ++j)
           acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[set][i][t], b[set][j][t], acc[i][j], 0,
                                                            0, 0);
-    if (with_bias) {
-#pragma unroll
-      for (int t = 0; t < 4; ++t)
-#pragma unroll
-        for (int j = 0; j < T; ++j)
-          bacc[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(1.0f, b[set][j][t], bacc[j], 0, 0, 0);
-      if ((s & 3) == 3) {
-#pragma unroll
-        for (int j = 0; j < T; ++j) {
-          btot[j] = btot[j] + bacc[j];
-          bacc[j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-        }
-      }
-    }
   };
   const int ns = (u.B + 15) / 16;
+  load_rows(0, 0);
+  load_rows(1, 1);
   load(0, 0);
-  for (int s = 0; s < ns; s += 2) {
-    load(1, s + 1);
-    mma(0, s);
-    load(0, s + 2);
-    if (s + 1 < ns) mma(1, s + 1);
-  }
-  // Update: lane (gq, c16) holds inputs m0 + 4 T gq .. + 4 T - 1 of outputs
-  // n0 + T c16 + j.
+  // The weights, needed after the products only.  Lane (gq, c16) holds inputs
+  // m0 + 4 T gq .. + 4 T - 1 of outputs n0 + T c16 + j.
   const float* win = u.master_in + static_cast<int64_t>(rep) * u.master_in_slot;
   float* wout = u.master + static_cast<int64_t>(rep) * u.master_slot;
   const int mo = m0 + 4 * T * gq;
+  f32x4 w[T][T];
+#pragma unroll
+  for (int j = 0; j < T; ++j) {
+    const int n = n0 + T * c16 + j < y.N ? n0 + T * c16 + j : 0;
+    const float* row = win + y.w_off + static_cast<int64_t>(n) * y.M;
+#pragma unroll
+    for (int qd = 0; qd < T; ++qd)
+      w[j][qd] = *reinterpret_cast<const f32x4*>(mo + 4 * qd < y.M ? row + mo + 4 * qd : f32_zero);
+  }
+  for (int s = 0; s < ns; s += 2) {
+    load_rows(0, s + 2);
+    load(1, s + 1);
+    loads_first();
+    mma(0);
+    load_rows(1, s + 3);
+    load(0, s + 2);
+    loads_first();
+    mma(1);  // zeros past the batch
+  }
 #pragma unroll
   for (int j = 0; j < T; ++j) {
     const int n = n0 + T * c16 + j;
-    const bool nok = n < y.N;
-    const int64_t at = y.w_off + static_cast<int64_t>(nok ? n : 0) * y.M;
-    f32x4 w[T];
-#pragma unroll
-    for (int qd = 0; qd < T; ++qd)
-      w[qd] = *reinterpret_cast<const f32x4*>(mo + 4 * qd < y.M ? win + at + mo + 4 * qd : f32_zero);
+    const int64_t at = y.w_off + static_cast<int64_t>(n < y.N ? n : 0) * y.M;
 #pragma unroll
     for (int qd = 0; qd < T; ++qd) {
       const f32x4 d = acc_quad<true>(acc, j, qd);
 #pragma unroll
-      for (int e = 0; e < 4; ++e) w[qd][e] = fmaf(-u.lr, d[e], w[qd][e]);
-      if (nok && mo + 4 * qd < y.M) *reinterpret_cast<f32x4*>(wout + at + mo + 4 * qd) = w[qd];
+      for (int e = 0; e < 4; ++e) w[j][qd][e] = fmaf(-u.lr, d[e], w[j][qd][e]);
+      if (n < y.N && mo + 4 * qd < y.M)
+        *reinterpret_cast<f32x4*>(wout + at + mo + 4 * qd) = w[j][qd];
     }
-    if (with_bias && gq == 0 && nok)
-      wout[y.b_off + n] = fmaf(-u.lr, (btot[j] + bacc[j])[0], win[y.b_off + n]);
   }
 }
 
@@ -519,7 +569,7 @@ hipError_t launch_f32_gemm(const GemmArgs& g, GemmMode mode, int n_slots, hipStr
 hipError_t launch_f32_head(const F32HeadArgs& h, int n_slots, hipStream_t s) {
   if (h.B < 1 || n_slots < 1) return hipSuccess;
   if (h.C < 1 || h.C > F32_HEAD_CLASSES) return hipErrorInvalidValue;
-  const dim3 grid((h.B + 15) / 16, n_slots), block(64 * SLICES);
+  const dim3 grid((h.B + 15) / 16, n_slots), block(64 * HEAD_SLICES);
 #define HEAD(mi)                                                                          \
   if (h.below) hipLaunchKernelGGL((f32_head_kernel<mi, true>), grid, block, 0, s, h);     \
   else hipLaunchKernelGGL((f32_head_kernel<mi, false>), grid, block, 0, s, h)
@@ -538,28 +588,31 @@ hipError_t launch_f32_update(const F32UpdateArgs& u_in, int n_slots, hipStream_t
   auto groups = [&](int t) {
     int64_t n = 0;
     for (int l = 0; l < u.n_layers; ++l) {
-      u.layer[l].first_wg = static_cast<int>(n);
-      n += static_cast<int64_t>((u.layer[l].M + 32 * t - 1) / (32 * t)) *
-           ((u.layer[l].N + 32 * t - 1) / (32 * t));
+      F32UpdateLayer& y = u.layer[l];
+      const int64_t tiles =
+          static_cast<int64_t>((y.M + 32 * t - 1) / (32 * t)) * ((y.N + 32 * t - 1) / (32 * t));
+      u.first_wg[l] = static_cast<int>(n);
+      y.tiles = static_cast<int>(tiles);
+      n += tiles + (y.N + 63) / 64;
     }
     return n;
   };
-  // 64 x 64 per wave where that still gives every CU a workgroup, else 32 x 32.
+  // 64 x 64 per wave, or 32 x 32, whose 8-byte loads take twice the L1 accesses
+  // per byte but whose waves are four times as many and start up sooner.
+  // Measured: 784-512-256-10, batch 64, 8 replicas (304 workgroups of the
+  // larger tile) 22.8 against 17.9 us; 1024-2048-2048-10, batch 512, 1 replica
+  // (465 workgroups) 83 against 102 us.
+  for (int l = u.n_layers; l < F32_UPDATE_LAYERS; ++l) u.first_wg[l] = 0x7FFFFFFF;
   int t = 4;
   int64_t gx = groups(4);
-  if (gx * n_slots < 256) {
+  if (u.B < 128 || gx * n_slots < 256) {
     t = 2;
     gx = groups(2);
   }
   if (gx * n_slots > 0x7FFFFFFF) return hipErrorInvalidValue;
   const dim3 grid(static_cast<unsigned>(gx), n_slots), block(256);
-  if (t == 4) {
-    if (u.gather) hipLaunchKernelGGL((f32_update_kernel<4, true>), grid, block, 0, s, u);
-    else hipLaunchKernelGGL((f32_update_kernel<4, false>), grid, block, 0, s, u);
-  } else {
-    if (u.gather) hipLaunchKernelGGL((f32_update_kernel<2, true>), grid, block, 0, s, u);
-    else hipLaunchKernelGGL((f32_update_kernel<2, false>), grid, block, 0, s, u);
-  }
+  if (t == 4) hipLaunchKernelGGL(f32_update_kernel<4>, grid, block, 0, s, u);
+  else hipLaunchKernelGGL(f32_update_kernel<2>, grid, block, 0, s, u);
   return hipGetLastError();
 }
 
