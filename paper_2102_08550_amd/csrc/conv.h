@@ -59,6 +59,15 @@ struct ConvArgs {
 
 hipError_t launch_conv(const ConvArgs& a, ConvPass pass, int n_slots, hipStream_t s);
 
+// Convolutions whose channel counts are multiples of 4 (conv_direct.hip):
+// forward, and backward-weight of w with (d != nullptr) backward-data of d in
+// one launch.  Weight-gradient partials are packed: per range [Co][9 C], then
+// the [Co] bias gradients.
+bool conv_direct(const ConvArgs& a);
+int conv_direct_range(const ConvArgs& a);  // output pixels per weight-gradient range
+hipError_t launch_conv_direct_fwd(const ConvArgs& a, int n_slots, hipStream_t s);
+hipError_t launch_conv_direct_bwd(const ConvArgs* d, const ConvArgs& w, int n_slots, hipStream_t s);
+
 // CONV_DGRAD of d and CONV_WGRAD of w (the same layer; each as launch_conv
 // takes it) in one launch, where that applies: channel counts multiples of 4
 // and no gathered rows (conv_pair_fits; otherwise hipErrorInvalidValue and
@@ -66,16 +75,18 @@ hipError_t launch_conv(const ConvArgs& a, ConvPass pass, int n_slots, hipStream_
 bool conv_pair_fits(const ConvArgs& d, const ConvArgs& w, int n_slots);
 hipError_t launch_conv_pair(const ConvArgs& d, const ConvArgs& w, int n_slots, hipStream_t s);
 
-// Output pixels per weight-gradient range of the 64 x 64 conv tiles.
+// Output pixels per weight-gradient range of the 64 x 64 conv tiles (channel
+// counts that are not multiples of 4).
 constexpr int CONV_WGRAD_PIXELS = 256;
 
 // The K ranges a CONV_WGRAD launch of these sizes expects (ConvArgs.splits,
 // ConvArgs.k_per_split): ranges of CONV_WGRAD_PIXELS output pixels, or, for
 // layers with at most three input channels whose staged input rows fit a
 // workgroup's LDS, of whole output rows (as many as fill 512 pixel slots of
-// the row width rounded up to 32).
+// the row width rounded up to 32), or of conv_direct_range pixels.
 void conv_wgrad_ranges(const ConvArgs& a, int* splits, int64_t* k_per_split);
-
+// The most ranges any batch up to a.B has.
+int conv_wgrad_max_splits(const ConvArgs& a);
 
 // pooled[z][b][c] = (sum over the H W positions of act[z][b][.][c]: eight
 // groups of consecutive positions, each in position order, the group sums in
@@ -131,6 +142,7 @@ struct UpdateBlock {
   const float* part;
   int64_t part_slot;
   int splits, M, N;
+  int packed;  // partials packed: [M][N - 1], then [M] biases
   int64_t w_off, b_off;
 };
 constexpr int MAX_UPDATE_BLOCKS = 4;

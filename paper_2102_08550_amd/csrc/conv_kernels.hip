@@ -46,24 +46,6 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 // A compile-time integer passed as an argument (static register indices).
 template <int U> struct Pi { static constexpr int value = U; };
 
-// Schedule of a K step with N MFMAs: each MFMA followed by a share of the
-// step's other work (its next operands' LDS reads, gather address
-// arithmetic, LDS stores, global loads), which then issues while the matrix
-// core runs.  Without it the compiler issued the MFMAs back to back and the
-// rest after them; with one or two waves per SIMD (one or two replicas)
-// nothing else hid that work.
-template <int N>
-__device__ __forceinline__ void interleave() {
-#pragma unroll
-  for (int u = 0; u < N; ++u) {
-    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // one MFMA
-    __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);  // LDS reads
-    __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);  // VALU
-    __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);  // LDS write
-    __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);  // global load
-  }
-}
-
 constexpr int CT = 64;       // tile rows and columns
 constexpr int CK = 16;       // K per step
 constexpr int CLD = CT + 4;  // LDS row pitch (floats)
@@ -117,13 +99,11 @@ __device__ __forceinline__ void dgrad_tap(const ConvArgs& a, int t, int& r, int&
   }
 }
 
-// A thread's K sequence k0, k0 + CK, k0 + 2 CK, ... (or another step) split
-// as k = q D + r: one division when constructed, then next() steps without
-// dividing (step = dq D + dr, split once).
+// A thread's sequence k0, k0 + step, ... split as k = q D + r: one division
+// when constructed, then next() steps without dividing.
 struct KCursor {
   int q, r, D, dq, dr;
-  __device__ KCursor() = default;
-  __device__ KCursor(int k0, int D_, int step = CK) : D(D_) {
+  __device__ KCursor(int k0, int D_, int step) : D(D_) {
     q = k0 / D;
     r = k0 - q * D;
     dq = step / D;
@@ -135,36 +115,6 @@ struct KCursor {
     const bool w = r >= D;
     r = w ? r - D : r;
     q = w ? q + 1 : q;
-  }
-};
-
-// The same for an output pixel k = (b Ho + i) Wo + j: a step of `step`
-// pixels is db whole images and a remainder of di rows and dj columns, so
-// that each coordinate wraps at most once per step (no loop, no branch).
-struct PixCursor {
-  int b, i, j, Ho, Wo, db, di, dj;
-  __device__ PixCursor() = default;
-  __device__ PixCursor(int k0, int Ho_, int Wo_, int step = CK) : Ho(Ho_), Wo(Wo_) {
-    const int hw = Ho * Wo;
-    b = k0 / hw;
-    const int p = k0 - b * hw;
-    i = p / Wo;
-    j = p - i * Wo;
-    db = step / hw;
-    const int rest = step - db * hw;
-    di = rest / Wo;
-    dj = rest - di * Wo;
-  }
-  __device__ __forceinline__ void next() {
-    j += dj;
-    i += di;
-    b += db;
-    const bool wj = j >= Wo;
-    j = wj ? j - Wo : j;
-    i = wj ? i + 1 : i;
-    const bool wi = i >= Ho;
-    i = wi ? i - Ho : i;
-    b = wi ? b + 1 : b;
   }
 };
 
@@ -283,42 +233,6 @@ struct ConvLoader {
                 : in + static_cast<int64_t>(b) * a.H * a.W * a.C;
   }
 
-  // Forward with channel counts a multiple of 4: four consecutive K of the A
-  // row are four channels of one input tap, of the B row four consecutive
-  // weights; one 16-byte load each.
-  __device__ __forceinline__ void fwd_a(int k, const KCursor& kc, float (&ra)[4]) const {
-    const int rs = kc.q, c = kc.r, r = rs / 3, hi = ah + r, wi = aw + rs - 3 * r;
-    // bitwise: every term evaluated, no branch (the short-circuit form became
-    // exec-mask branches that split the K loop into blocks)
-    const bool aok = am & (k < kend) & (hi >= 0) & (hi < a.H) & (wi >= 0) & (wi < a.W);
-    const f32x4 va =
-        *reinterpret_cast<const f32x4*>(aok ? arow + (hi * a.W + wi) * a.C + c : k_conv_zero);
-    for (int e = 0; e < 4; ++e) ra[e] = va[e];
-  }
-  __device__ __forceinline__ void fwd_b(int k, float (&rb)[4]) const {
-    const bool bok = bn & (k < kend);
-    const f32x4 vb = *reinterpret_cast<const f32x4*>(
-        bok ? Wt + static_cast<int64_t>(bn_idx) * 9 * a.C + k : k_conv_zero);
-    for (int e = 0; e < 4; ++e) rb[e] = vb[e];
-  }
-  __device__ __forceinline__ void fwd_vec(int k, const KCursor& kc, float (&ra)[4],
-                                          float (&rb)[4]) const {
-    fwd_a(k, kc, ra);
-    fwd_b(k, rb);
-  }
-  // Backward-data A with output channels a multiple of 4 (see dgrad_a).
-  __device__ __forceinline__ void dgrad_a_vec(int k, const KCursor& kc, float (&ra)[4]) const {
-    const int t = kc.q, o = kc.r;
-    int r, sc;
-    dgrad_tap_rs(t, r, sc);
-    const int ti = ah - r, tj = aw - sc;
-    const int i = a.stride == 2 ? ti >> 1 : ti, j = a.stride == 2 ? tj >> 1 : tj;
-    const bool ok = am & (k < kend) & (ti >= 0) & (tj >= 0) & (i < a.Ho) & (j < a.Wo);
-    const f32x4 v =
-        *reinterpret_cast<const f32x4*>(ok ? arow + (i * a.Wo + j) * a.Co + o : k_conv_zero);
-    for (int e = 0; e < 4; ++e) ra[e] = v[e];
-  }
-
   // Backward-data operands: A, the output-gradient taps of this input pixel
   // (four consecutive output channels of one tap); B, the weights of this
   // input channel (column) for four consecutive K.
@@ -341,20 +255,13 @@ struct ConvLoader {
       off = (i * a.Wo + j) * a.Co;
       return true;
     };
-    if ((a.Co & 3) == 0) {
-      f32x4 v = {0.0f, 0.0f, 0.0f, 0.0f};
+    int t2 = t, o2 = o;
+    for (int e = 0; e < 4; ++e) {
       int off = 0;
-      if (am && k < kend && tap(t, off)) v = *reinterpret_cast<const f32x4*>(arow + off + o);
-      for (int e = 0; e < 4; ++e) ra[e] = v[e];
-    } else {
-      int t2 = t, o2 = o;
-      for (int e = 0; e < 4; ++e) {
-        int off = 0;
-        ra[e] = (am && k + e < kend && tap(t2, off)) ? arow[off + o2] : 0.0f;
-        if (++o2 == a.Co) {
-          o2 = 0;
-          ++t2;
-        }
+      ra[e] = (am && k + e < kend && tap(t2, off)) ? arow[off + o2] : 0.0f;
+      if (++o2 == a.Co) {
+        o2 = 0;
+        ++t2;
       }
     }
   }
@@ -456,92 +363,6 @@ struct ConvLoader {
   }
 };
 
-// Backward-data weights gathered along N (input channels a multiple of 4): a
-// thread takes four consecutive input channels nq .. nq + 3 of one K element
-// (tap t, output channel o), W[o][r][s][nq .. nq + 3], one 16-byte load.
-struct DgradWeightLoader {
-  const ConvArgs& a;
-  int kend;
-  int nq;
-  bool bn;
-  const float* Wt;
-  __device__ DgradWeightLoader(const ConvArgs& a_, int kend_, int n, int N, const float* Wt_)
-      : a(a_), kend(kend_), nq(n), bn(n < N), Wt(Wt_) {}
-  __device__ __forceinline__ void fetch(int k, const KCursor& kc, float (&rb)[4]) const {
-    const int t = kc.q, o = kc.r;
-    int r, sc;
-    dgrad_tap(a, t, r, sc);
-    const bool ok = bn & (k < kend);
-    const f32x4 v = *reinterpret_cast<const f32x4*>(
-        ok ? Wt + static_cast<int64_t>(o) * 9 * a.C + (3 * r + sc) * a.C + nq : k_conv_zero);
-    for (int e = 0; e < 4; ++e) rb[e] = v[e];
-  }
-};
-
-// Backward-weight loader for channel counts that are multiples of 4.  Both
-// operands are contiguous along M or N (dZ is [pixel][Cout], an input tap
-// [pixel][Cin]), so a thread gathers, per K step, four consecutive rows of A
-// (output channels) and four consecutive columns of B (the channels of one
-// tap) of one K element, an output pixel whose position is decoded once for
-// both: one 16-byte load each.  With Cin a multiple of 4 a column group lies
-// inside one tap, or is the bias column's group (column 9 Cin: ones) or past
-// the end.
-template <bool GATHER>
-struct WgradLoader {
-  const ConvArgs& a;
-  int kend;
-  int mq, nq;         // the thread's first row and column
-  bool arow_ok;       // rows mq .. mq + 3 inside (Cout a multiple of 4)
-  bool btap, bbias;   // columns: four channels of one tap / the bias group
-  int br = 0, bs = 0, bc = 0;  // tap and channel of column nq
-  const float* in;
-  const int32_t* rows;
-  const float* dz;
-
-  __device__ WgradLoader(const ConvArgs& a_, int kend_, int m, int M, int n, int N,
-                         const float* in_, const int32_t* rows_, const float* dz_, const float*)
-      : a(a_), kend(kend_), mq(m), nq(n), in(in_), rows(rows_), dz(dz_) {
-    const int K9 = 9 * a.C;
-    arow_ok = mq < M;
-    btap = nq < K9;
-    bbias = nq == K9 && nq < N;
-    const int rs = nq / a.C;
-    bc = nq - rs * a.C;
-    br = rs / 3;
-    bs = rs - 3 * br;
-  }
-
-  __device__ __forceinline__ void fetch(int k, const PixCursor& pc, float (&ra)[4],
-                                        float (&rb)[4]) const {
-    const bool ok = k < kend;
-    const int b = ok ? pc.b : 0, i = pc.i, j = pc.j;  // a valid image past the end
-    const f32x4 va = *reinterpret_cast<const f32x4*>(
-        ok && arow_ok ? dz + static_cast<int64_t>(k) * a.Co + mq : k_conv_zero);
-    const int hi = a.stride * i + br - 1, wi = a.stride * j + bs - 1;
-    const bool tap_ok = ok & btap & (hi >= 0) & (hi < a.H) & (wi >= 0) & (wi < a.W);
-    // the gathered case is a template parameter: a branch on `rows` here made
-    // the compiler wait for every load in flight (the next steps' too) before
-    // each LDS store
-    const float* img;
-    if constexpr (GATHER)
-      img = in + static_cast<int64_t>(rows[b]) * a.in_ld;
-    else
-      img = in + static_cast<int64_t>(b) * a.H * a.W * a.C;
-    const f32x4 vb = *reinterpret_cast<const f32x4*>(
-        tap_ok ? img + (hi * a.W + wi) * a.C + bc : k_conv_zero);
-    for (int e = 0; e < 4; ++e) {
-      ra[e] = va[e];
-      rb[e] = vb[e];
-    }
-    rb[0] = ok && bbias ? 1.0f : rb[0];
-  }
-};
-
-// Channel counts for the vector loaders (conv_gemm_kernel<PASS, true>).
-__host__ __device__ inline bool vector_loaders(const ConvArgs& a) {
-  return (a.C & 3) == 0 && (a.Co & 3) == 0;
-}
-
 // Tiles of one stride-2 backward-data class.
 __host__ __device__ inline int64_t dgrad_class_tiles(ConvArgs a, int cls) {
   a.cls = cls;
@@ -552,21 +373,12 @@ __host__ __device__ inline int64_t dgrad_class_tiles(ConvArgs a, int cls) {
 // most taps (longest K) first, so that the short ones fill the last pass.
 __host__ __device__ inline int dgrad_class_at(int i) { return i == 0 ? 3 : i == 1 ? 1 : i == 2 ? 2 : 0; }
 
-// TR (channel counts multiples of 4, see vector_loaders): vector loaders
-// without branches around their loads -- the forward gathers along K as
-// ConvLoader does, backward-weight gathers both operands along M and N
-// (WgradLoader), backward-data its weights along N (DgradWeightLoader);
-// otherwise ConvLoader's general gathers along K.
-// One tile of the GEMM; `lds` holds 4 HALVES CK CLD floats (conv_gemm_kernel,
-// conv_bwd_pair_kernel).
-template <int PASS, bool TR, int HALVES, bool GATHER>
-__device__ __forceinline__ void conv_gemm_tile(ConvArgs a, int tile, float* lds) {
+// One tile of the GEMM.
+template <int PASS>
+__global__ __launch_bounds__(256) void conv_gemm_kernel(ConvArgs a) {
   constexpr bool WG = PASS == CONV_WGRAD || PASS == FC_WGRAD;
-  static_assert(HALVES == 1 || HALVES == 2, "K per step: CK or 2 CK");
-  constexpr int KS = HALVES * CK;  // K per step (one barrier)
-  typedef float Stage[2][KS][CLD];
-  Stage& As = *reinterpret_cast<Stage*>(lds);
-  Stage& Bs = *reinterpret_cast<Stage*>(lds + 2 * KS * CLD);
+  __shared__ __attribute__((aligned(16))) float As[2][CK][CLD], Bs[2][CK][CLD];
+  int tile = blockIdx.x;
   int split = 0;
   if constexpr (PASS == CONV_DGRAD) {
     if (a.stride == 2 && a.cls < 0) {
@@ -602,88 +414,34 @@ __device__ __forceinline__ void conv_gemm_tile(ConvArgs a, int tile, float* lds)
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave >> 1, wn = wave & 1, r = lane & 31, h = lane >> 5;
-  // a thread's share of each K step: one row of A and of B and four
-  // consecutive K (lr, lk .. lk + 3), or, for backward-weight, four
-  // consecutive rows and columns (lr .. lr + 3) and one K (lk)
-  static_assert(!TR || PASS == CONV_FWD || PASS == CONV_WGRAD || PASS == CONV_DGRAD,
-                "vector loaders: convolution passes");
-  constexpr bool TRA = TR && PASS == CONV_WGRAD;  // A gathered along M
-  constexpr bool TRB = TR && PASS != CONV_FWD;    // B gathered along N
-  // (lr, lk): the thread's A row and K offset, (lrb, lkb) its B row and K
-  // offset; four consecutive K of one row, or four consecutive rows of one K
-  const int lr = TRA ? 4 * (tid & 15) : tid >> 2;
-  const int lk = TRA ? tid >> 4 : (tid & 3) * 4;
-  const int lrb = TRB ? 4 * (tid & 15) : tid >> 2;
-  const int lkb = TRB ? tid >> 4 : (tid & 3) * 4;
-  typedef typename std::conditional<TRA, WgradLoader<GATHER>, ConvLoader<PASS>>::type Loader;
-  const Loader ld(a, kend, m0 + lr, M, n0 + lrb, N, in, rows, dz, par + a.w_off);
-  const DgradWeightLoader wl(a, kend, n0 + lrb, N, par + a.w_off);
-  // the vector loaders' K decode, stepped along with the loads (consecutive K
-  // steps; one cursor per half of a step)
-  const int kdiv = PASS == CONV_FWD ? a.C : a.Co;
-  const int ho = a.Ho > 0 ? a.Ho : 1, wo = a.Wo > 0 ? a.Wo : 1;
-  KCursor ka[HALVES] = {KCursor(kbeg + lk, kdiv, KS)};
-  KCursor kb[HALVES] = {KCursor(kbeg + lkb, a.Co, KS)};
-  PixCursor pc[HALVES] = {PixCursor(TRA ? kbeg + lk : 0, ho, wo, KS)};
-  if constexpr (HALVES == 2) {
-    ka[1] = KCursor(kbeg + CK + lk, kdiv, KS);
-    kb[1] = KCursor(kbeg + CK + lkb, a.Co, KS);
-    pc[1] = PixCursor(TRA ? kbeg + CK + lk : 0, ho, wo, KS);
-  }
-  float ra[2][HALVES][4], rb[2][HALVES][4];
+  // a thread's share of each K step: one row of A and of B (lr) and four
+  // consecutive K (lk .. lk + 3)
+  const int lr = tid >> 2, lk = (tid & 3) * 4;
+  const ConvLoader<PASS> ld(a, kend, m0 + lr, M, n0 + lr, N, in, rows, dz, par + a.w_off);
+  float ra[2][4], rb[2][4];
   auto load = [&](int k0, auto P) {
     constexpr int p = decltype(P)::value;
-#pragma unroll
-    for (int q = 0; q < HALVES; ++q) {
-      const int kq = k0 + q * CK;
-      if constexpr (TR && PASS == CONV_DGRAD) {
-        ld.dgrad_a_vec(kq + lk, ka[q], ra[p][q]);
-        wl.fetch(kq + lkb, kb[q], rb[p][q]);
-        ka[q].next();
-        kb[q].next();
-      } else if constexpr (TR && PASS == CONV_FWD) {
-        ld.fwd_vec(kq + lk, ka[q], ra[p][q], rb[p][q]);
-        ka[q].next();
-      } else if constexpr (TRA) {
-        ld.fetch(kq + lk, pc[q], ra[p][q], rb[p][q]);
-        pc[q].next();
-      } else {
-        ld.fetch(kq + lk, ra[p][q], rb[p][q]);
-      }
-    }
+    ld.fetch(k0 + lk, ra[p], rb[p]);
   };
   auto stash = [&](auto P) {
     constexpr int p = decltype(P)::value;  // register set p into LDS buffer p
 #pragma unroll
-    for (int q = 0; q < HALVES; ++q) {
-      const int kq = q * CK;
-      if constexpr (TRA) {
-        *reinterpret_cast<f32x4*>(&As[p][kq + lk][lr]) =
-            f32x4{ra[p][q][0], ra[p][q][1], ra[p][q][2], ra[p][q][3]};
-      } else {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) As[p][kq + lk + e][lr] = ra[p][q][e];
-      }
-      if constexpr (TRB) {
-        *reinterpret_cast<f32x4*>(&Bs[p][kq + lkb][lrb]) =
-            f32x4{rb[p][q][0], rb[p][q][1], rb[p][q][2], rb[p][q][3]};
-      } else {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) Bs[p][kq + lkb + e][lrb] = rb[p][q][e];
-      }
+    for (int e = 0; e < 4; ++e) {
+      As[p][lk + e][lr] = ra[p][e];
+      Bs[p][lk + e][lr] = rb[p][e];
     }
   };
 
   f32x16 acc;
 #pragma unroll
   for (int i = 0; i < 16; ++i) acc[i] = 0.0f;
-  const int nk = (kend - kbeg + KS - 1) / KS;
+  const int nk = (kend - kbeg + CK - 1) / CK;
   // Two register sets: step t + 2 is gathered while step t is multiplied and
   // step t + 1 (gathered a step earlier) goes into the other LDS buffer.
   // Gathers past kend read nothing and give zeros.
   load(kbeg, Pi<0>());
   stash(Pi<0>());
-  load(kbeg + KS, Pi<1>());
+  load(kbeg + CK, Pi<1>());
   __syncthreads();
   // a wave whose 32 x 32 block lies wholly past M or N (32-channel layers on
   // 64 x 64 tiles) skips its products and leaves the MFMA unit to the CU's
@@ -691,16 +449,15 @@ __device__ __forceinline__ void conv_gemm_tile(ConvArgs a, int tile, float* lds)
   const bool busy = m0 + wm * 32 < M && n0 + wn * 32 < N;
   auto step = [&](int t, auto P, auto MUL) {  // register set and LDS buffer p = t & 1
     constexpr int p = decltype(P)::value;
-    load(kbeg + (t + 2) * KS, P);
+    load(kbeg + (t + 2) * CK, P);
     // MFMA u contracts k = 2u (lanes 0-31) and 2u + 1 (lanes 32-63)
     if constexpr (decltype(MUL)::value) {
 #pragma unroll
-      for (int u = 0; u < KS / 2; ++u)
+      for (int u = 0; u < CK / 2; ++u)
         acc = __builtin_amdgcn_mfma_f32_32x32x2f32(As[p][2 * u + h][wm * 32 + r],
                                                    Bs[p][2 * u + h][wn * 32 + r], acc, 0, 0, 0);
     }
     stash(Pi<p ^ 1>());
-    if constexpr (decltype(MUL)::value) interleave<KS / 2>();
     __syncthreads();
   };
   auto steps = [&](auto MUL) {
@@ -749,353 +506,6 @@ __device__ __forceinline__ void conv_gemm_tile(ConvArgs a, int tile, float* lds)
     } else {
       a.part[z * a.part_slot + (static_cast<int64_t>(split) * M + row) * N + col] = v;
     }
-  }
-}
-
-template <int PASS, bool TR = false, int HALVES = 1, bool GATHER = false>
-__global__ __launch_bounds__(256) void conv_gemm_kernel(ConvArgs a) {
-  __shared__ __attribute__((aligned(16))) float lds[4 * HALVES * CK * CLD];
-  conv_gemm_tile<PASS, TR, HALVES, GATHER>(a, blockIdx.x, lds);
-}
-
-// ---------------------------------------------------------------------------
-// Backward-data with at most 32 input channels (a multiple of 4): 128 x 32
-// tiles, the four waves stacked along M, where a 64 x 64 tile would leave half
-// of its columns empty.  The operands are gathered as in
-// conv_gemm_kernel<CONV_DGRAD, true> (each thread two A rows, four
-// consecutive K of each; the first 128 threads four consecutive weight
-// columns of one K), the LDS tiles hold the same K steps, and so every sum
-// is the same.
-constexpr int NM = 128, NN = 32;
-
-__host__ __device__ inline bool dgrad_narrow(const ConvArgs& a) {
-  return (a.C & 3) == 0 && (a.Co & 3) == 0 && a.C >= 4 && a.C <= NN;
-}
-__host__ __device__ inline int64_t dgrad_narrow_tiles(const ConvArgs& a) {
-  const Dims d = pass_dims(a, CONV_DGRAD);
-  return ((d.M + NM - 1) / NM) * ((d.N + NN - 1) / NN);
-}
-
-// `lds` holds 2 CK (NM + NN + 8) floats.
-__device__ __forceinline__ void conv_dgrad_narrow_tile(ConvArgs a, int tile, float* lds) {
-  typedef float StageA[2][CK][NM + 4];
-  typedef float StageB[2][CK][NN + 4];
-  StageA& As = *reinterpret_cast<StageA*>(lds);
-  StageB& Bs = *reinterpret_cast<StageB*>(lds + 2 * CK * (NM + 4));
-  if (a.stride == 2 && a.cls < 0) {
-    int i = 0;
-    for (; i < 4; ++i) {
-      ConvArgs ac = a;
-      ac.cls = dgrad_class_at(i);
-      const int t = static_cast<int>(dgrad_narrow_tiles(ac));
-      if (tile < t) break;
-      tile -= t;
-    }
-    if (i == 4) return;  // past the last class (the grid is their sum)
-    a.cls = dgrad_class_at(i);
-  }
-  const Dims d = pass_dims(a, CONV_DGRAD);
-  const int M = static_cast<int>(d.M), N = static_cast<int>(d.N), K = static_cast<int>(d.K);
-  const int z = blockIdx.y;
-  const int rep = a.order[z];
-  const int gn = (N + NN - 1) / NN;
-  const int m0 = tile / gn * NM, n0 = (tile - tile / gn * gn) * NN;
-  const float* dz = a.dout + z * a.dout_slot;
-  const float* par = a.master_in + static_cast<int64_t>(rep) * a.master_in_slot;
-
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, r = lane & 31, h = lane >> 5;
-  const int lr = tid >> 2, lk = (tid & 3) * 4;      // A rows lr and lr + 64
-  const bool bload = tid < NN * CK / 4;             // B: four columns of one K
-  const int lrb = 4 * (tid & 7), lkb = (tid >> 3) & (CK - 1);
-  const ConvLoader<CONV_DGRAD> ld0(a, K, m0 + lr, M, n0, N, nullptr, nullptr, dz, par + a.w_off);
-  const ConvLoader<CONV_DGRAD> ld1(a, K, m0 + lr + 64, M, n0, N, nullptr, nullptr, dz,
-                                   par + a.w_off);
-  const DgradWeightLoader wl(a, K, n0 + lrb, N, par + a.w_off);
-  KCursor ka(lk, a.Co), kb(lkb, a.Co);  // stepped along with the loads
-  float ra0[4], ra1[4], rb[4];
-  auto load = [&](int k0) {
-    ld0.dgrad_a_vec(k0 + lk, ka, ra0);
-    ld1.dgrad_a_vec(k0 + lk, ka, ra1);
-    if (bload) wl.fetch(k0 + lkb, kb, rb);
-    ka.next();
-    kb.next();
-  };
-  auto stash = [&](int buf) {
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      As[buf][lk + e][lr] = ra0[e];
-      As[buf][lk + e][lr + 64] = ra1[e];
-    }
-    if (bload) *reinterpret_cast<f32x4*>(&Bs[buf][lkb][lrb]) = f32x4{rb[0], rb[1], rb[2], rb[3]};
-  };
-
-  f32x16 acc;
-#pragma unroll
-  for (int i = 0; i < 16; ++i) acc[i] = 0.0f;
-  const int nk = (K + CK - 1) / CK;
-  load(0);
-  stash(0);
-  __syncthreads();
-  for (int t = 0; t < nk; ++t) {
-    const int buf = t & 1;
-    if (t + 1 < nk) load((t + 1) * CK);
-#pragma unroll
-    for (int u = 0; u < CK / 2; ++u)
-      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(As[buf][2 * u + h][wave * 32 + r],
-                                                 Bs[buf][2 * u + h][r], acc, 0, 0, 0);
-    if (t + 1 < nk) stash(buf ^ 1);
-    interleave<CK / 2>();
-    __syncthreads();
-  }
-
-  const int col = n0 + r;
-  DgradRowWalker wk(a, m0 + wave * 32 + 4 * h);  // stepped as in conv_gemm_kernel
-#pragma unroll
-  for (int i = 0; i < 16; ++i) {
-    if (i > 0) wk.advance((i & 3) ? 1 : 5);
-    const int row = m0 + wave * 32 + 8 * (i >> 2) + 4 * h + (i & 3);
-    if (row >= M || col >= N) continue;
-    const int64_t at = wk.offset() + col;
-    const float g = a.skip ? acc[i] + a.skip[z * a.skip_slot + at] : acc[i];
-    a.out[z * a.out_slot + at] = a.mask[z * a.mask_slot + at] > 0.0f ? g : 0.0f;
-  }
-}
-
-__global__ __launch_bounds__(256) void conv_dgrad_narrow_kernel(ConvArgs a) {
-  __shared__ __attribute__((aligned(16))) float lds[2 * CK * (NM + NN + 8)];
-  conv_dgrad_narrow_tile(a, blockIdx.x, lds);
-}
-
-// ---------------------------------------------------------------------------
-// Forward into at most 32 output channels and backward-weight of at most 32
-// output channels (channel counts multiples of 4, at least 4 input channels),
-// where a 64 x 64 tile would leave half of its waves without products:
-//   forward          128 x 32 tiles (pixels x output channels), the four waves
-//                    stacked along M; each thread gathers two A rows and, in
-//                    the first 128 threads, one weight row, four consecutive K
-//                    each, as conv_gemm_kernel<CONV_FWD, true> does;
-//   backward-weight  32 x 128 tiles (output channels x weight columns), the
-//                    waves side by side along N; each thread takes one K (an
-//                    output pixel) and, as WgradLoader does, four output
-//                    channels (the first eight threads of each K) and two
-//                    groups of four weight columns.
-// Both keep the LDS layout of the 64 x 64 tiles (K steps of CK, [k][row]) and
-// the operand roles of every MFMA, and so every sum is the same.  Two
-// register sets as there: step t + 2 is gathered while step t is multiplied.
-__host__ __device__ inline bool conv_narrow(const ConvArgs& a) {
-  return (a.C & 3) == 0 && (a.Co & 3) == 0 && a.C >= 4 && a.Co <= NN;
-}
-__host__ __device__ inline int64_t fwd_narrow_tiles(const ConvArgs& a) {
-  const Dims d = pass_dims(a, CONV_FWD);
-  return ((d.M + NM - 1) / NM) * ((d.N + NN - 1) / NN);
-}
-__host__ __device__ inline int64_t wgrad_narrow_tiles(const ConvArgs& a) {
-  const Dims d = pass_dims(a, CONV_WGRAD);
-  return ((d.M + NN - 1) / NN) * ((d.N + NM - 1) / NM);
-}
-
-__global__ __launch_bounds__(256) void conv_fwd_narrow_kernel(ConvArgs a) {
-  __shared__ __attribute__((aligned(16))) float As[2][CK][NM + 4];
-  __shared__ __attribute__((aligned(16))) float Bs[2][CK][NN + 4];
-  const Dims d = pass_dims(a, CONV_FWD);
-  const int M = static_cast<int>(d.M), N = static_cast<int>(d.N), K = static_cast<int>(d.K);
-  const int z = blockIdx.y;
-  const int rep = a.order[z];
-  const int gn = (N + NN - 1) / NN;
-  const int tile = blockIdx.x;
-  const int m0 = tile / gn * NM, n0 = (tile - tile / gn * gn) * NN;
-  const float* in = a.in + z * a.in_slot;
-  const int32_t* rows = a.gather ? a.gather + z * a.gather_slot : nullptr;
-  const float* par = a.master_in + static_cast<int64_t>(rep) * a.master_in_slot;
-
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, r = lane & 31, h = lane >> 5;
-  // A rows lr and lr + 64, B row lr (threads below 128), K lk .. lk + 3
-  const int lr = tid >> 2, lk = (tid & 3) * 4;
-  const bool bload = tid < NN * CK / 4;
-  const ConvLoader<CONV_FWD> ld0(a, K, m0 + lr, M, n0 + lr, N, in, rows, nullptr, par + a.w_off);
-  const ConvLoader<CONV_FWD> ld1(a, K, m0 + lr + 64, M, n0 + lr, N, in, rows, nullptr,
-                                 par + a.w_off);
-  KCursor ka(lk, a.C);  // stepped along with the loads
-  float ra0[2][4], ra1[2][4], rb[2][4];
-  auto load = [&](int k0, auto P) {
-    constexpr int p = decltype(P)::value;
-    ld0.fwd_a(k0 + lk, ka, ra0[p]);
-    ld1.fwd_a(k0 + lk, ka, ra1[p]);
-    ld0.fwd_b(k0 + lk, rb[p]);  // rows past N (threads from 128 on) read zeros
-    ka.next();
-  };
-  auto stash = [&](auto P) {
-    constexpr int p = decltype(P)::value;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      As[p][lk + e][lr] = ra0[p][e];
-      As[p][lk + e][lr + 64] = ra1[p][e];
-    }
-    if (bload) {
-#pragma unroll
-      for (int e = 0; e < 4; ++e) Bs[p][lk + e][lr] = rb[p][e];
-    }
-  };
-
-  f32x16 acc;
-#pragma unroll
-  for (int i = 0; i < 16; ++i) acc[i] = 0.0f;
-  const int nk = (K + CK - 1) / CK;
-  load(0, Pi<0>());
-  stash(Pi<0>());
-  load(CK, Pi<1>());
-  __syncthreads();
-  auto step = [&](int t, auto P) {
-    constexpr int p = decltype(P)::value;
-    load((t + 2) * CK, P);
-#pragma unroll
-    for (int u = 0; u < CK / 2; ++u)
-      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(As[p][2 * u + h][wave * 32 + r],
-                                                 Bs[p][2 * u + h][r], acc, 0, 0, 0);
-    stash(Pi<p ^ 1>());
-    interleave<CK / 2>();
-    __syncthreads();
-  };
-  int t = 0;
-  for (; t + 1 < nk; t += 2) {
-    step(t, Pi<0>());
-    step(t + 1, Pi<1>());
-  }
-  if (t < nk) step(t, Pi<0>());
-
-  const int col = n0 + r;
-#pragma unroll
-  for (int i = 0; i < 16; ++i) {
-    const int row = m0 + wave * 32 + 8 * (i >> 2) + 4 * h + (i & 3);
-    if (row >= M || col >= N) continue;
-    const int64_t at = static_cast<int64_t>(row) * a.Co + col;
-    float zv = acc[i] + par[a.b_off + col];
-    if (a.skip) zv += a.skip[z * a.skip_slot + at];
-    a.out[z * a.out_slot + at] = zv > 0.0f ? zv : 0.0f;
-  }
-}
-
-// `lds` holds 2 CK (NM + NN + 8) floats.
-template <bool GATHER>
-__device__ __forceinline__ void conv_wgrad_narrow_tile(ConvArgs a, int tile, float* lds) {
-  typedef float StageA[2][CK][NN + 4];
-  typedef float StageB[2][CK][NM + 4];
-  StageA& As = *reinterpret_cast<StageA*>(lds);
-  StageB& Bs = *reinterpret_cast<StageB*>(lds + 2 * CK * (NN + 4));
-  const Dims d = pass_dims(a, CONV_WGRAD);
-  const int M = static_cast<int>(d.M), N = static_cast<int>(d.N), K = static_cast<int>(d.K);
-  const int z = blockIdx.y;
-  const int rep = a.order[z];
-  const int gm = (M + NN - 1) / NN, gn = (N + NM - 1) / NM;
-  const int split = tile / (gm * gn);
-  tile -= split * gm * gn;
-  const int m0 = tile / gn * NN, n0 = (tile - tile / gn * gn) * NM;
-  const int kbeg = split * static_cast<int>(a.k_per_split);
-  const int kend = K - kbeg < a.k_per_split ? K : kbeg + static_cast<int>(a.k_per_split);
-  const float* in = a.in + z * a.in_slot;
-  const int32_t* rows = a.gather ? a.gather + z * a.gather_slot : nullptr;
-  const float* dz = a.dout + z * a.dout_slot;
-
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, r = lane & 31, h = lane >> 5;
-  // K lk; A rows 4 q .. 4 q + 3 (q below 8); B columns 4 q .. + 3 and 64 + 4 q .. + 3
-  const int lk = tid >> 4, q = tid & 15;
-  const bool aload = q < NN / 4;
-  const WgradLoader<GATHER> w0(a, kend, aload ? m0 + 4 * q : M, M, n0 + 4 * q, N, in, rows, dz,
-                              nullptr);
-  const WgradLoader<GATHER> w1(a, kend, M, M, n0 + 64 + 4 * q, N, in, rows, dz, nullptr);
-  PixCursor pc(kbeg + lk, a.Ho, a.Wo);
-  float ra[2][4], rb0[2][4], rb1[2][4];
-  auto load = [&](int k0, auto P) {
-    constexpr int p = decltype(P)::value;
-    float unused[4];
-    w0.fetch(k0 + lk, pc, ra[p], rb0[p]);
-    w1.fetch(k0 + lk, pc, unused, rb1[p]);  // its A rows are past M: zeros, not stored
-    pc.next();
-  };
-  auto stash = [&](auto P) {
-    constexpr int p = decltype(P)::value;
-    if (aload)
-      *reinterpret_cast<f32x4*>(&As[p][lk][4 * q]) = f32x4{ra[p][0], ra[p][1], ra[p][2], ra[p][3]};
-    *reinterpret_cast<f32x4*>(&Bs[p][lk][4 * q]) =
-        f32x4{rb0[p][0], rb0[p][1], rb0[p][2], rb0[p][3]};
-    *reinterpret_cast<f32x4*>(&Bs[p][lk][64 + 4 * q]) =
-        f32x4{rb1[p][0], rb1[p][1], rb1[p][2], rb1[p][3]};
-  };
-
-  f32x16 acc;
-#pragma unroll
-  for (int i = 0; i < 16; ++i) acc[i] = 0.0f;
-  const int nk = (kend - kbeg + CK - 1) / CK;
-  load(kbeg, Pi<0>());
-  stash(Pi<0>());
-  load(kbeg + CK, Pi<1>());
-  __syncthreads();
-  // a wave whose 32 columns lie past N (the last tile) skips its products
-  const bool busy = n0 + wave * 32 < N;
-  auto step = [&](int t, auto P, auto MUL) {
-    constexpr int p = decltype(P)::value;
-    load(kbeg + (t + 2) * CK, P);
-    if constexpr (decltype(MUL)::value) {
-#pragma unroll
-      for (int u = 0; u < CK / 2; ++u)
-        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(As[p][2 * u + h][r],
-                                                   Bs[p][2 * u + h][wave * 32 + r], acc, 0, 0, 0);
-    }
-    stash(Pi<p ^ 1>());
-    if constexpr (decltype(MUL)::value) interleave<CK / 2>();
-    __syncthreads();
-  };
-  auto steps = [&](auto MUL) {
-    int t = 0;
-    for (; t + 1 < nk; t += 2) {
-      step(t, Pi<0>(), MUL);
-      step(t + 1, Pi<1>(), MUL);
-    }
-    if (t < nk) step(t, Pi<0>(), MUL);
-  };
-  if (busy)
-    steps(Pi<1>());
-  else
-    steps(Pi<0>());
-
-  const int col = n0 + wave * 32 + r;
-#pragma unroll
-  for (int i = 0; i < 16; ++i) {
-    const int row = m0 + 8 * (i >> 2) + 4 * h + (i & 3);
-    if (row >= M || col >= N) continue;
-    a.part[z * a.part_slot + (static_cast<int64_t>(split) * M + row) * N + col] = acc[i];
-  }
-}
-
-template <bool GATHER>
-__global__ __launch_bounds__(256) void conv_wgrad_narrow_kernel(ConvArgs a) {
-  __shared__ __attribute__((aligned(16))) float lds[2 * CK * (NM + NN + 8)];
-  conv_wgrad_narrow_tile<GATHER>(a, blockIdx.x, lds);
-}
-
-// Backward-data and backward-weight of one layer in one launch: the first nd
-// workgroups take backward-data tiles, the others backward-weight tiles.  The
-// two read the layer's output gradient and nothing that the other writes;
-// with one or two replicas either launch alone leaves most of every CU idle,
-// and with more the two kinds of tiles share the CUs better than in turn.
-// DN / WN: the 128 x 32 backward-data / 32 x 128 backward-weight tiles, else
-// the 64 x 64 ones (vector loaders, K steps of CK).
-template <bool DN, bool WN>
-__global__ __launch_bounds__(256) void conv_bwd_pair_kernel(ConvArgs d, ConvArgs w, int nd) {
-  constexpr int DF = DN ? 2 * CK * (NM + NN + 8) : 4 * CK * CLD;
-  constexpr int WF = WN ? 2 * CK * (NM + NN + 8) : 4 * CK * CLD;
-  __shared__ __attribute__((aligned(16))) float lds[DF > WF ? DF : WF];
-  const int b = blockIdx.x;
-  if (b < nd) {
-    if constexpr (DN)
-      conv_dgrad_narrow_tile(d, b, lds);
-    else
-      conv_gemm_tile<CONV_DGRAD, true, 1, false>(d, b, lds);
-  } else {
-    if constexpr (WN)
-      conv_wgrad_narrow_tile<false>(w, b - nd, lds);
-    else
-      conv_gemm_tile<CONV_WGRAD, true, 1, false>(w, b - nd, lds);
   }
 }
 
@@ -1483,7 +893,9 @@ __global__ __launch_bounds__(256) void conv_update_all_kernel(UpdateAll u, HeadA
   for (int g = 1; g < UG; ++g) tot += group_sum[g][w];
   const float* src = u.master_in + static_cast<int64_t>(rep) * u.master_in_slot;
   float* dst = master + static_cast<int64_t>(rep) * master_slot;
-  const int64_t at = n < ub.N - 1 ? ub.w_off + m * (ub.N - 1) + n : ub.b_off + m;
+  const int64_t MW = static_cast<int64_t>(ub.M) * (ub.N - 1);
+  const int64_t at = ub.packed ? (e < MW ? ub.w_off + e : ub.b_off + e - MW)
+                               : (n < ub.N - 1 ? ub.w_off + m * (ub.N - 1) + n : ub.b_off + m);
   dst[at] = fmaf(-lr, tot, src[at]);
 }
 
@@ -1635,41 +1047,9 @@ __global__ __launch_bounds__(256) void conv_head_kernel(HeadArgs h) {
   }
 }
 
-int conv_cu_count() {
-  static int cus = 0;
-  if (cus == 0) {
-    int dev = 0, v = 0;
-    if (hipGetDevice(&dev) == hipSuccess &&
-        hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && v > 0)
-      cus = v;
-    else
-      cus = 256;
-  }
-  return cus;
-}
-
-
-// Launches of at most two workgroups per CU (one or two replicas) take K
-// steps of 32 (one barrier per 16 MFMAs instead of 8): with one or two waves
-// per SIMD nothing else hides a step's fixed cost.  With the vector loaders
-// only (the general gathers spill with two halves).
-template <int PASS, bool TR>
+template <int PASS>
 void launch_conv_gemm(const dim3& grid, hipStream_t s, const ConvArgs& a) {
-  const int64_t wgs = static_cast<int64_t>(grid.x) * grid.y;
-  const bool wide = wgs <= 2LL * conv_cu_count();
-  if constexpr (PASS == CONV_WGRAD && TR) {
-    if (a.gather) {  // gathered dataset rows (a first layer with four or more channels)
-      hipLaunchKernelGGL((conv_gemm_kernel<PASS, TR, 1, true>), grid, dim3(256), 0, s, a);
-      return;
-    }
-  }
-  if constexpr (TR) {
-    if (wide) {
-      hipLaunchKernelGGL((conv_gemm_kernel<PASS, TR, 2>), grid, dim3(256), 0, s, a);
-      return;
-    }
-  }
-  hipLaunchKernelGGL((conv_gemm_kernel<PASS, TR, 1>), grid, dim3(256), 0, s, a);
+  hipLaunchKernelGGL(conv_gemm_kernel<PASS>, grid, dim3(256), 0, s, a);
 }
 
 }  // namespace
@@ -1679,25 +1059,11 @@ hipError_t launch_conv(const ConvArgs& a, ConvPass pass, int n_slots, hipStream_
   if (a.skip && (pass == FC_FWD || pass == FC_DGRAD || pass == CONV_WGRAD || pass == FC_WGRAD ||
                  (pass == CONV_FWD && thin_layer(a))))
     return hipErrorInvalidValue;
-  if (pass == CONV_DGRAD && dgrad_narrow(a)) {
-    if (n_slots < 1 || a.cls > 3 || a.B < 1 || a.Co < 1 || (a.stride == 2 && a.cls < -1))
-      return hipErrorInvalidValue;
-    int64_t gx = 0;
-    if (a.stride == 2 && a.cls < 0) {
-      for (int i = 0; i < 4; ++i) {
-        ConvArgs ac = a;
-        ac.cls = i;
-        gx += dgrad_narrow_tiles(ac);
-      }
-    } else {
-      gx = dgrad_narrow_tiles(a);
-    }
-    if (gx == 0) return hipSuccess;  // no pixels (extents of 1)
-    if (gx > 0x7FFFFFFF) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(conv_dgrad_narrow_kernel, dim3(static_cast<unsigned>(gx), n_slots),
-                       dim3(256), 0, s, a);
-    return hipGetLastError();
-  }
+  if (pass == CONV_FWD && conv_direct(a)) return launch_conv_direct_fwd(a, n_slots, s);
+  if (pass == CONV_WGRAD && conv_direct(a)) return launch_conv_direct_bwd(nullptr, a, n_slots, s);
+  // backward-data of such layers shares a launch with their backward-weight
+  // (launch_conv_pair)
+  if (pass == CONV_DGRAD && conv_direct(a)) return hipErrorInvalidValue;
   if (pass == CONV_DGRAD && a.stride == 2) {
     if (n_slots < 1 || a.cls > 3 || a.B < 1 || a.C < 1 || a.Co < 1) return hipErrorInvalidValue;
     int64_t gx = 0;
@@ -1707,10 +1073,7 @@ hipError_t launch_conv(const ConvArgs& a, ConvPass pass, int n_slots, hipStream_
       gx = dgrad_class_tiles(a, a.cls);
     if (gx == 0) return hipSuccess;  // no pixels (extents of 1)
     if (gx > 0x7FFFFFFF) return hipErrorInvalidValue;
-    if (vector_loaders(a))
-      launch_conv_gemm<CONV_DGRAD, true>(dim3(static_cast<unsigned>(gx), n_slots), s, a);
-    else
-      launch_conv_gemm<CONV_DGRAD, false>(dim3(static_cast<unsigned>(gx), n_slots), s, a);
+    launch_conv_gemm<CONV_DGRAD>(dim3(static_cast<unsigned>(gx), n_slots), s, a);
     return hipGetLastError();
   }
   const Dims d = pass_dims(a, pass);
@@ -1757,27 +1120,6 @@ hipError_t launch_conv(const ConvArgs& a, ConvPass pass, int n_slots, hipStream_
     }
     return hipGetLastError();
   }
-  if (pass == CONV_FWD && conv_narrow(a)) {
-    const int64_t gx = fwd_narrow_tiles(a);
-    if (gx > 0x7FFFFFFF) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(conv_fwd_narrow_kernel, dim3(static_cast<unsigned>(gx), n_slots), dim3(256),
-                       0, s, a);
-    return hipGetLastError();
-  }
-  if (pass == CONV_WGRAD && conv_narrow(a)) {
-    if (a.splits < 1 || a.k_per_split < 1 ||
-        static_cast<int64_t>(a.splits) * a.k_per_split < d.K)
-      return hipErrorInvalidValue;
-    const int64_t gx = wgrad_narrow_tiles(a) * a.splits;
-    if (gx > 0x7FFFFFFF) return hipErrorInvalidValue;
-    if (a.gather)
-      hipLaunchKernelGGL(conv_wgrad_narrow_kernel<true>, dim3(static_cast<unsigned>(gx), n_slots),
-                         dim3(256), 0, s, a);
-    else
-      hipLaunchKernelGGL(conv_wgrad_narrow_kernel<false>, dim3(static_cast<unsigned>(gx), n_slots),
-                         dim3(256), 0, s, a);
-    return hipGetLastError();
-  }
   int64_t gx = ((d.M + CT - 1) / CT) * ((d.N + CT - 1) / CT);
   if (pass == CONV_WGRAD || pass == FC_WGRAD) {
     if (a.splits < 1 || a.k_per_split < 1 ||
@@ -1786,91 +1128,26 @@ hipError_t launch_conv(const ConvArgs& a, ConvPass pass, int n_slots, hipStream_
     gx *= a.splits;
   }
   if (gx > 0x7FFFFFFF) return hipErrorInvalidValue;
-  const dim3 grid(static_cast<unsigned>(gx), n_slots), block(256);
+  const dim3 grid(static_cast<unsigned>(gx), n_slots);
   switch (pass) {
-    case CONV_FWD:
-      if (vector_loaders(a))
-        launch_conv_gemm<CONV_FWD, true>(grid, s, a);
-      else
-        launch_conv_gemm<CONV_FWD, false>(grid, s, a);
-      break;
-    case CONV_DGRAD:
-      if (vector_loaders(a))
-        launch_conv_gemm<CONV_DGRAD, true>(grid, s, a);
-      else
-        launch_conv_gemm<CONV_DGRAD, false>(grid, s, a);
-      break;
-    case CONV_WGRAD:
-      if (vector_loaders(a))
-        launch_conv_gemm<CONV_WGRAD, true>(grid, s, a);
-      else
-        launch_conv_gemm<CONV_WGRAD, false>(grid, s, a);
-      break;
-    case FC_FWD: launch_conv_gemm<FC_FWD, false>(grid, s, a); break;
-    case FC_DGRAD: launch_conv_gemm<FC_DGRAD, false>(grid, s, a); break;
-    case FC_WGRAD: launch_conv_gemm<FC_WGRAD, false>(grid, s, a); break;
+    case CONV_FWD: launch_conv_gemm<CONV_FWD>(grid, s, a); break;
+    case CONV_DGRAD: launch_conv_gemm<CONV_DGRAD>(grid, s, a); break;
+    case CONV_WGRAD: launch_conv_gemm<CONV_WGRAD>(grid, s, a); break;
+    case FC_FWD: launch_conv_gemm<FC_FWD>(grid, s, a); break;
+    case FC_DGRAD: launch_conv_gemm<FC_DGRAD>(grid, s, a); break;
+    case FC_WGRAD: launch_conv_gemm<FC_WGRAD>(grid, s, a); break;
   }
   return hipGetLastError();
 }
 
-namespace {
-// Tiles of the two launches conv_bwd_pair_kernel joins, or false where it
-// does not apply (channel counts for the vector loaders, no gathered rows).
-// Joined at every replica count: on the CIFAR-shaped networks of 3 and 9
-// conv layers (K = 8) a round took 2.65 / 14.4 ms, against 2.67 / 14.6 ms with
-// the pair only up to twelve workgroups per CU and 2.75 / 15.2 ms with two
-// launches everywhere.
-bool conv_pair_plan(const ConvArgs& d, const ConvArgs& w, int n_slots, bool* dn, bool* wn,
-                    int64_t* nd, int64_t* nw) {
-  if (n_slots < 1 || !vector_loaders(d) || !vector_loaders(w) || d.gather || w.gather ||
-      thin_layer(w) || d.B < 1 || d.cls > 3 || (d.stride == 2 && d.cls < -1) || w.splits < 1 ||
-      w.k_per_split < 1)
-    return false;
-  const Dims dw = pass_dims(w, CONV_WGRAD);
-  if (static_cast<int64_t>(w.splits) * w.k_per_split < dw.K) return false;
-  *dn = dgrad_narrow(d);
-  int64_t t = 0;
-  const bool all = d.stride == 2 && d.cls < 0;
-  for (int i = 0; i < (all ? 4 : 1); ++i) {
-    ConvArgs ac = d;
-    if (all) ac.cls = i;
-    if (*dn) {
-      t += dgrad_narrow_tiles(ac);
-    } else if (d.stride == 2) {
-      t += dgrad_class_tiles(ac, ac.cls);
-    } else {
-      const Dims dd = pass_dims(ac, CONV_DGRAD);
-      t += ((dd.M + CT - 1) / CT) * ((dd.N + CT - 1) / CT);
-    }
-  }
-  *nd = t;
-  *wn = conv_narrow(w);
-  *nw = (*wn ? wgrad_narrow_tiles(w) : ((dw.M + CT - 1) / CT) * ((dw.N + CT - 1) / CT)) * w.splits;
-  return *nd > 0 && *nw > 0 && *nd + *nw <= 0x7FFFFFFF;
-}
-}  // namespace
-
 bool conv_pair_fits(const ConvArgs& d, const ConvArgs& w, int n_slots) {
-  bool dn, wn;
-  int64_t nd, nw;
-  return conv_pair_plan(d, w, n_slots, &dn, &wn, &nd, &nw);
+  return n_slots >= 1 && conv_direct(d) && conv_direct(w) && !d.gather && !w.gather && d.B >= 1 &&
+         (d.stride != 2 || d.cls == -1);
 }
 
 hipError_t launch_conv_pair(const ConvArgs& d, const ConvArgs& w, int n_slots, hipStream_t s) {
-  bool dn, wn;
-  int64_t nd, nw;
-  if (!conv_pair_plan(d, w, n_slots, &dn, &wn, &nd, &nw)) return hipErrorInvalidValue;
-  const dim3 grid(static_cast<unsigned>(nd + nw), n_slots), block(256);
-  const int ndi = static_cast<int>(nd);
-  if (dn && wn)
-    hipLaunchKernelGGL((conv_bwd_pair_kernel<true, true>), grid, block, 0, s, d, w, ndi);
-  else if (dn)
-    hipLaunchKernelGGL((conv_bwd_pair_kernel<true, false>), grid, block, 0, s, d, w, ndi);
-  else if (wn)
-    hipLaunchKernelGGL((conv_bwd_pair_kernel<false, true>), grid, block, 0, s, d, w, ndi);
-  else
-    hipLaunchKernelGGL((conv_bwd_pair_kernel<false, false>), grid, block, 0, s, d, w, ndi);
-  return hipGetLastError();
+  if (!conv_pair_fits(d, w, n_slots)) return hipErrorInvalidValue;
+  return launch_conv_direct_bwd(&d, w, n_slots, s);
 }
 
 hipError_t launch_conv_updates(const UpdateBlock* blocks, int n_blocks, const HeadArgs* head,
@@ -1944,8 +1221,16 @@ void conv_wgrad_ranges(const ConvArgs& a, int* splits, int64_t* k_per_split) {
     return;
   }
   const int64_t pixels = static_cast<int64_t>(a.B) * a.Ho * a.Wo;
-  *k_per_split = CONV_WGRAD_PIXELS;
-  *splits = static_cast<int>((pixels + CONV_WGRAD_PIXELS - 1) / CONV_WGRAD_PIXELS);
+  *k_per_split = conv_direct(a) ? conv_direct_range(a) : CONV_WGRAD_PIXELS;
+  *splits = static_cast<int>((pixels + *k_per_split - 1) / *k_per_split);
+}
+
+int conv_wgrad_max_splits(const ConvArgs& a) {
+  int splits = 0;
+  int64_t per = 0;
+  conv_wgrad_ranges(a, &splits, &per);
+  // conv_direct_range shortens the ranges of a smaller batch: up to 32 of them
+  return conv_direct(a) && !thin_wgrad(a) && splits < 32 ? 32 : splits;
 }
 
 }  // namespace oscars

@@ -15,54 +15,19 @@
 // depends only on K, not on the tile
 // shape or on how many replicas share a launch, so every tiling gives the
 // same bits.  Backward-weight sums the batch in row order.
-//
-// An MFMA contracts k = 16 s + 4 q + t over the lane groups q = 0..3
-// (lane >> 4) for its t; a lane's four K-contiguous elements feed t = 0..3.
-// An operand stored M/N-contiguous is read as vectors of one K row: element i
-// of the vector at column MI * (lane & 15) feeds block i, so block i holds
-// the columns MI * c + i.
 #include <hip/hip_runtime.h>
 
 #include <type_traits>
 
 #include "kernels.h"
+#include "mfma_f32.h"
 
 namespace oscars {
 namespace {
 
-typedef float f32x2 __attribute__((ext_vector_type(2)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
-
 constexpr int SLICES = 4;  // K slices of forward / backward-data = waves per workgroup
 constexpr int HEAD_SLICES = 8;  // of the classifier head
 constexpr int KTILE = 32;  // K tile dealt to the slices in turn
-
-template <int W> struct Vec;
-template <> struct Vec<1> { typedef float T; };
-template <> struct Vec<2> { typedef f32x2 T; };
-template <> struct Vec<4> { typedef f32x4 T; };
-
-// Lanes with nothing to load read these zeros (no branch around a load).
-__device__ __attribute__((aligned(16))) float f32_zero[4];
-
-// a * b elements in one instruction (rows and strides are below 2^31).
-__device__ __forceinline__ int64_t offset_of(int a, int64_t b) {
-  return static_cast<int64_t>(static_cast<uint64_t>(static_cast<uint32_t>(a)) *
-                              static_cast<uint32_t>(b));
-}
-
-// Keeps the loads issued before it above the products that follow: the
-// scheduler otherwise moves them down to their first use, which then waits
-// out the whole latency.
-__device__ __forceinline__ void loads_first() { __builtin_amdgcn_sched_barrier(0); }
-
-// Flattened workgroup id -> work item: the workgroups that the hardware puts
-// on one XCD (id mod 8) take one contiguous range of the T work items.
-__device__ __forceinline__ int xcd_item(int id, int T) {
-  const int x = id & 7, i = id >> 3, q = T >> 3, r = T & 7;
-  return x < r ? x * (q + 1) + i : r * (q + 1) + (x - r) * q + i;
-}
 
 // K groups (16 deep) a wave loads at once: enough bytes in flight for small
 // tiles, few registers for large ones.  A slice is summed in whole pairs of
@@ -71,121 +36,162 @@ __device__ __forceinline__ int xcd_item(int id, int T) {
 template <int MI, int NJ> struct Depth {
   static constexpr int G = MI + NJ >= 8 ? 1 : (MI + NJ >= 4 ? 2 : 4);
 };
+// Floats of a wave's LDS for the K-contiguous operands of slice_products.
+template <bool TRANS, int MI, int NJ> constexpr int slice_lds() {
+  return Depth<MI, NJ>::G * ((TRANS ? 0 : MI) + NJ) * BLOCK_FLOATS;
+}
 
-// The operands of G consecutive K groups of one slice.
-template <bool TRANS, int MI, int NJ, int G, int S>
-struct Frags {
-  float a[G][MI][4], b[G][NJ][4];
-
-  // a_row[i]: row of block i (K-contiguous), or, TRANS, a_row[0]: column
-  // MI * (lane & 15) of K row 0; b_row[j]: row of block j (K-contiguous).
-  // Slice `slice`, its K groups q0 .. q0 + G - 1; zeros from K (A) and from
-  // b_ext (B) on.
-  __device__ __forceinline__ void load(const float* const (&a_row)[MI],
-                                       const float* const (&b_row)[NJ], int64_t a_ld, int K,
-                                       int b_ext, int slice, int q0, int lane) {
-    const int kq = 4 * (lane >> 4);
+// A K-contiguous operand of a tile: rows row0 .. of a matrix with row stride
+// ld, N blocks of 16 (rows past the last repeat it; their outputs are not
+// stored), or, gathered, rows anywhere.
+template <int N>
+struct Rows {
+  Buf buf;
+  uint32_t at[N];
+  const float* row[N];  // gathered
+  bool gathered;
+  __device__ __forceinline__ void init(const float* base, int64_t ld, int row0, int rows, int lane) {
+    const int last = min(rows - 1 - row0, 16 * N - 1);
+    buf = buffer(base + static_cast<int64_t>(row0) * ld, (last + 1) * ld * 4);
 #pragma unroll
-    for (int g = 0; g < G; ++g) {
-      const int q = q0 + g;
-      const int k = KTILE * (slice + S * (q >> 1)) + 16 * (q & 1) + kq;
-      if constexpr (!TRANS) {
-        const bool ok = k < K;  // K is a multiple of 4: whole chunks
-#pragma unroll
-        for (int i = 0; i < MI; ++i) {
-          const f32x4 v = *reinterpret_cast<const f32x4*>(ok ? a_row[i] + k : f32_zero);
-#pragma unroll
-          for (int t = 0; t < 4; ++t) a[g][i][t] = v[t];
-        }
-      } else {
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-          const float* row = a_row[0] + offset_of(k + t, a_ld);
-          const float* p = k + t < K ? row : f32_zero;
-          const typename Vec<MI>::T v = *reinterpret_cast<const typename Vec<MI>::T*>(p);
-          if constexpr (MI == 1) a[g][0][t] = v;
-          else {
-#pragma unroll
-            for (int i = 0; i < MI; ++i) a[g][i][t] = v[i];
-          }
-        }
-      }
-      const bool ok = k < b_ext;
-#pragma unroll
-      for (int j = 0; j < NJ; ++j) {
-        const f32x4 v = *reinterpret_cast<const f32x4*>(ok ? b_row[j] + k : f32_zero);
-#pragma unroll
-        for (int t = 0; t < 4; ++t) b[g][j][t] = v[t];
-      }
-    }
+    for (int i = 0; i < N; ++i)
+      at[i] = 4u * (static_cast<uint32_t>(min(16 * i + load_row(lane), last)) *
+                        static_cast<uint32_t>(ld) + load_k(lane));
+    gathered = false;
   }
-
-  __device__ __forceinline__ void mma(f32x4 (&acc)[MI][NJ]) const {
+  __device__ __forceinline__ void init_gathered(const float* base, int64_t ld,
+                                                const int32_t* gather, int row0, int rows,
+                                                int lane) {
 #pragma unroll
-    for (int g = 0; g < G; ++g) {
-#pragma unroll
-      for (int t = 0; t < 4; ++t)
-#pragma unroll
-        for (int i = 0; i < MI; ++i)
-#pragma unroll
-          for (int j = 0; j < NJ; ++j)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[g][i][t], b[g][j][t], acc[i][j], 0,
-                                                             0, 0);
-    }
+    for (int i = 0; i < N; ++i)
+      row[i] = base + static_cast<int64_t>(gather[min(row0 + 16 * i + load_row(lane), rows - 1)]) * ld +
+               load_k(lane);
+    gathered = true;
   }
 };
 
-// One K slice of a 16 MI x 16 NJ tile.
-template <bool TRANS, int S, int MI, int NJ>
-__device__ __forceinline__ void slice_products(f32x4 (&acc)[MI][NJ],
-                                               const float* const (&a_row)[MI],
-                                               const float* const (&b_row)[NJ], int64_t a_ld, int K,
-                                               int b_ext, int slice, int lane) {
+// K slice `slice` of S of a 16 MI x 16 NJ tile of A B^T.  A: rows (K-contiguous)
+// or, TRANS, a_cols: row 0, column m0 (the tile's first) of a K x M matrix with
+// row stride a_ld = M.  Zeros from K (A) and from b_ext (B) on.  The loads of groups
+// q + 2, the turn through LDS of q + 1 and the products of q are in flight
+// together.
+template <bool TRANS, bool GATHER, int S, int MI, int NJ>
+__device__ __forceinline__ void slice_products(f32x4 (&acc)[MI][NJ], const Rows<TRANS ? 1 : MI>& ra,
+                                               const Rows<NJ>& rb, const float* a_cols,
+                                               int m0, int64_t a_ld, int K, int b_ext, int slice,
+                                               int lane, float* lds) {
+  constexpr int G = Depth<MI, NJ>::G;
+  constexpr int AB = TRANS ? 0 : MI, NB = G * (AB + NJ);  // blocks through LDS
 #pragma unroll
   for (int i = 0; i < MI; ++i)
 #pragma unroll
     for (int j = 0; j < NJ; ++j) acc[i][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
   const int tiles = (K + KTILE - 1) / KTILE;
   const int nq = tiles > slice ? 2 * ((tiles - slice + S - 1) / S) : 0;
-  constexpr int G = Depth<MI, NJ>::G;
-  Frags<TRANS, MI, NJ, G, S> f0, f1;
-  f0.load(a_row, b_row, a_ld, K, b_ext, slice, 0, lane);
-  for (int q0 = 0; q0 < nq; q0 += 2 * G) {
-    f1.load(a_row, b_row, a_ld, K, b_ext, slice, q0 + G, lane);
-    loads_first();
-    f0.mma(acc);
-    f0.load(a_row, b_row, a_ld, K, b_ext, slice, q0 + 2 * G, lane);
-    loads_first();
-    f1.mma(acc);
-  }
-}
-
-// Four consecutive rows m of quad `qd` (0 .. MI - 1) of a lane, and their
-// first row within the tile: TRANS blocks interleave the columns.
-template <bool TRANS, int MI, int NJ>
-__device__ __forceinline__ f32x4 acc_quad(const f32x4 (&acc)[MI][NJ], int j, int qd) {
-  if constexpr (!TRANS) return acc[qd][j];
-  f32x4 v;
+  if (nq == 0) return;
+  const float* zero = GATHER ? zero_words() : nullptr;
+  auto k_of = [&](int q) { return KTILE * (slice + S * (q >> 1)) + 16 * (q & 1); };
+  f32x4 raw[NB];
+  auto load_rows = [&](int q0) {
 #pragma unroll
-  for (int e = 0; e < 4; ++e) v[e] = acc[(4 * qd + e) % MI][j][(4 * qd + e) / MI];
-  return v;
-}
-template <bool TRANS, int MI>
-__device__ __forceinline__ int quad_row(int qd, int lane) {
-  return TRANS ? 4 * MI * (lane >> 4) + 4 * qd : 16 * qd + 4 * (lane >> 4);
+    for (int g = 0; g < G; ++g) {
+      const int k = k_of(q0 + g);
+      const uint32_t k4 = 4u * min(k, K);  // within every row's buffer
+      const bool a_ok = load_k(lane) < K - k;  // K is a multiple of 4: whole chunks
+      const bool b_ok = load_k(lane) < b_ext - k;
+#pragma unroll
+      for (int i = 0; i < AB; ++i)
+        raw[g * (AB + NJ) + i] = load_buffer<4>(ra.buf, a_ok ? ra.at[i] : NOWHERE, k4);
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) {
+        f32x4& v = raw[g * (AB + NJ) + AB + j];
+        if constexpr (GATHER) v = load_global<4>(b_ok ? rb.row[j] + k : zero);
+        else v = load_buffer<4>(rb.buf, b_ok ? rb.at[j] : NOWHERE, k4);
+      }
+    }
+  };
+  uint32_t col_at[4];
+  if constexpr (TRANS) {
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+      col_at[t] = 4u * ((4 * (lane >> 4) + t) * static_cast<uint32_t>(a_ld) + MI * (lane & 15));
+  }
+  struct Set {
+    f32x4 rows[NB];
+    float cols[TRANS ? G : 1][TRANS ? MI : 1][4];
+  } f0, f1;
+  auto load_cols = [&](Set& f, int q0) {
+    if constexpr (TRANS) {
+#pragma unroll
+      for (int g = 0; g < G; ++g) {
+        // 16 rows of the matrix from K row k; zeros past K.  (Columns past M are
+        // other rows' values or zeros; their outputs are not stored.)
+        const int k = min(k_of(q0 + g), K);
+        const Buf b = buffer(a_cols + static_cast<int64_t>(k) * a_ld,
+                             k < K ? (min(K - k, 16) * a_ld - m0) * 4 : 0);
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+          float v[MI];
+          load_buffer_vec<MI>(v, b, col_at[t], 0);
+#pragma unroll
+          for (int i = 0; i < MI; ++i) f.cols[g][i][t] = v[i];
+        }
+      }
+    }
+  };
+  auto mma = [&](const Set& f) {
+#pragma unroll
+    for (int g = 0; g < G; ++g)
+#pragma unroll
+      for (int t = 0; t < 4; ++t)
+#pragma unroll
+        for (int i = 0; i < MI; ++i)
+#pragma unroll
+          for (int j = 0; j < NJ; ++j) {
+            float a;
+            if constexpr (TRANS) a = f.cols[g][i][t];
+            else a = f.rows[g * (AB + NJ) + i][t];
+            acc[i][j] = mfma16(a, f.rows[g * (AB + NJ) + AB + j][t], acc[i][j]);
+          }
+  };
+  constexpr int NM = 4 * G * MI * NJ, NV = NB + (TRANS ? 4 * G : 0);
+  load_rows(0);
+  load_cols(f0, 0);
+  blocks_write(lds, raw, lane);
+  load_rows(G);
+  blocks_read(lds, f0.rows, lane);
+  for (int q0 = 0; q0 < nq; q0 += 2 * G) {
+    blocks_write(lds, raw, lane);
+    load_rows(q0 + 2 * G);
+    load_cols(f1, q0 + G);
+    blocks_read(lds, f1.rows, lane);
+    mma(f0);
+    spread<NM, NB, NB, NV>();
+    blocks_write(lds, raw, lane);
+    load_rows(q0 + 3 * G);
+    load_cols(f0, q0 + 2 * G);
+    blocks_read(lds, f0.rows, lane);
+    mma(f1);
+    spread<NM, NB, NB, NV>();
+  }
 }
 
 // Forward and backward-data (GemmArgs as for the other GEMM kernels, without
 // rows_out and the split): one 16 MI x 16 NJ output tile per workgroup, one
 // K slice per wave.
-template <int MODE, int MI, int NJ>
-__global__ __launch_bounds__(64 * SLICES) void f32_gemm_kernel(GemmArgs g) {
+template <int MODE, int MI, int NJ, bool GATHER>
+__global__ __launch_bounds__(64 * SLICES, 2) void f32_gemm_kernel(GemmArgs g) {
   constexpr bool TRANS = MODE == GEMM_DGRAD;
   // The slices meet in LDS, at most 32 columns at a time (64 x 64 tiles: two
   // phases of 70 KB).
   constexpr int TM = 16 * MI, TN = 16 * NJ, LD = TM + 4;
   constexpr int NP = NJ > 2 ? 2 : 1, PN = TN / NP;  // phases, columns per phase
-  __shared__ __attribute__((aligned(16))) float red[SLICES][PN][LD];
+  constexpr int STAGE = slice_lds<TRANS, MI, NJ>();
+  __shared__ __attribute__((aligned(16))) union {
+    float stage[SLICES][STAGE];  // each wave's own
+    float red[SLICES][PN][LD];
+  } sm;
+  auto& red = sm.red;
   const int lane = threadIdx.x & 63;
   const int slice = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
   const int work = xcd_item(blockIdx.y * gridDim.x + blockIdx.x, gridDim.x * gridDim.y);
@@ -196,25 +202,14 @@ __global__ __launch_bounds__(64 * SLICES) void f32_gemm_kernel(GemmArgs g) {
   const float* A = static_cast<const float*>(g.a) + (g.a_by_order ? rep : z) * g.a_slot;
   const float* B = static_cast<const float*>(g.b) + z * g.b_slot;
 
-  // Rows past M or N repeat the last one: their outputs are never stored.
-  const float *a_row[MI], *b_row[NJ];
-  if constexpr (TRANS) {
-    const int m = m0 + MI * (lane & 15);  // M is a multiple of 8
-#pragma unroll
-    for (int i = 0; i < MI; ++i) a_row[i] = A + (m < g.M ? m : 0);
-  } else {
-#pragma unroll
-    for (int i = 0; i < MI; ++i)
-      a_row[i] = A + static_cast<int64_t>(min(m0 + 16 * i + (lane & 15), g.M - 1)) * g.a_ld;
-  }
-#pragma unroll
-  for (int j = 0; j < NJ; ++j) {
-    const int n = min(n0 + 16 * j + (lane & 15), g.N - 1);
-    const int64_t row = g.gather ? g.gather[z * g.gather_slot + n] : n;
-    b_row[j] = B + row * g.b_ld;
-  }
+  Rows<TRANS ? 1 : MI> ra;
+  Rows<NJ> rb;
+  if constexpr (!TRANS) ra.init(A, g.a_ld, m0, g.M, lane);
+  if constexpr (GATHER) rb.init_gathered(B, g.b_ld, g.gather + z * g.gather_slot, n0, g.N, lane);
+  else rb.init(B, g.b_ld, n0, g.N, lane);
   f32x4 acc[MI][NJ];
-  slice_products<TRANS, SLICES>(acc, a_row, b_row, g.a_ld, g.K, g.b_ext, slice, lane);
+  slice_products<TRANS, GATHER, SLICES>(acc, ra, rb, A + m0, m0, g.a_ld, g.K, g.b_ext, slice, lane,
+                                        sm.stage[slice]);
 
   // A thread takes four consecutive rows m of column n.
   constexpr int PER = (MI * 4 * PN + 64 * SLICES - 1) / (64 * SLICES);  // per thread and phase
@@ -235,7 +230,7 @@ __global__ __launch_bounds__(64 * SLICES) void f32_gemm_kernel(GemmArgs g) {
     }
 #pragma unroll
   for (int ph = 0; ph < NP; ++ph) {
-    if (ph > 0) __syncthreads();
+    __syncthreads();  // every wave is done with its stage, or the last phase is read
 #pragma unroll
     for (int j = 0; j < NJ / NP; ++j)
 #pragma unroll
@@ -277,24 +272,27 @@ __global__ __launch_bounds__(64 * SLICES) void f32_gemm_kernel(GemmArgs g) {
 // cross-entropy (as softmax_ce_kernel), and, with DGRAD, the delta of the
 // layer below (as f32_gemm_kernel's backward-data).  One launch instead of
 // three whose own latency was all they cost.
-template <int MI, bool DGRAD>
+template <int MI, bool DGRAD, bool GATHER>
 __global__ __launch_bounds__(64 * HEAD_SLICES) void f32_head_kernel(F32HeadArgs h) {
   constexpr int TM = 16 * MI, LD = TM + 4, ROWS = 16;
-  __shared__ __attribute__((aligned(16))) float red[HEAD_SLICES][ROWS][LD];
+  constexpr int STAGE = slice_lds<false, MI, 1>();
+  __shared__ __attribute__((aligned(16))) union {
+    float stage[HEAD_SLICES][STAGE];  // each wave's own
+    float red[HEAD_SLICES][ROWS][LD];
+  } sm;
+  auto& red = sm.red;
   __shared__ __attribute__((aligned(16))) float dl[ROWS][LD];
   const int lane = threadIdx.x & 63, c16 = lane & 15, gq = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
   const int z = blockIdx.y, rep = h.order[z], n0 = blockIdx.x * ROWS;
   const float* master = h.master_in + static_cast<int64_t>(rep) * h.master_in_slot;
   const float* W = master + h.w_off;
-  const float *a_row[MI], *b_row[1];
-#pragma unroll
-  for (int i = 0; i < MI; ++i)
-    a_row[i] = W + static_cast<int64_t>(min(16 * i + c16, h.C - 1)) * h.K;
-  const int nb = min(n0 + c16, h.B - 1);
-  b_row[0] = h.act + z * h.act_slot +
-             (h.act_gather ? static_cast<int64_t>(h.gather[z * h.gather_slot + nb])
-                           : static_cast<int64_t>(nb)) * h.act_ld;
+  const float* act = h.act + z * h.act_slot;
+  Rows<MI> ra;
+  Rows<1> rb;
+  ra.init(W, h.K, 0, h.C, lane);
+  if constexpr (GATHER) rb.init_gathered(act, h.act_ld, h.gather + z * h.gather_slot, n0, h.B, lane);
+  else rb.init(act, h.act_ld, n0, h.B, lane);
   // labels and bias before the products: their latency is hidden
   int label[ROWS / HEAD_SLICES];
 #pragma unroll
@@ -304,7 +302,9 @@ __global__ __launch_bounds__(64 * HEAD_SLICES) void f32_head_kernel(F32HeadArgs 
   }
   const float bias = master[h.b_off + min(lane, h.C - 1)];
   f32x4 acc[MI][1];
-  slice_products<false, HEAD_SLICES>(acc, a_row, b_row, h.K, h.K, h.K, wave, lane);
+  slice_products<false, GATHER, HEAD_SLICES>(acc, ra, rb, nullptr, 0, h.K, h.K, h.K, wave, lane,
+                                             sm.stage[wave]);
+  __syncthreads();  // every wave is done with its stage
 #pragma unroll
   for (int i = 0; i < MI; ++i)
     *reinterpret_cast<f32x4*>(&red[wave][c16][16 * i + 4 * gq]) = acc[i][0];
@@ -352,6 +352,7 @@ __global__ __launch_bounds__(64 * HEAD_SLICES) void f32_head_kernel(F32HeadArgs 
       for (int t = 0; t < 4; ++t) bd[s][t] = v[t];
     }
     const int b = n0 + c16;
+    const float* zero = zero_words();
     for (int m0 = 64 * wave; m0 < h.K; m0 += 64 * HEAD_SLICES) {
       const int m = m0 + 4 * c16;
       const float* col = W + (m < h.K ? m : 0);
@@ -361,16 +362,14 @@ __global__ __launch_bounds__(64 * HEAD_SLICES) void f32_head_kernel(F32HeadArgs 
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
           const int k = 16 * s + 4 * gq + t;
-          w[s][t] = *reinterpret_cast<const f32x4*>(
-              k < h.C ? col + static_cast<int64_t>(k) * h.K : f32_zero);
+          w[s][t] = load_global<4>(k < h.C ? col + static_cast<int64_t>(k) * h.K : zero);
         }
       const int mo = m0 + 16 * gq;  // this lane's 16 outputs
       const int64_t at = static_cast<int64_t>(min(b, h.B - 1)) * h.act_ld;
       f32x4 mask[4];
 #pragma unroll
       for (int r = 0; r < 4; ++r)
-        mask[r] = *reinterpret_cast<const f32x4*>(
-            mo + 4 * r < h.K ? h.act + z * h.act_slot + at + mo + 4 * r : f32_zero);
+        mask[r] = load_global<4>(mo + 4 * r < h.K ? h.act + z * h.act_slot + at + mo + 4 * r : zero);
       f32x4 d[2][4];
 #pragma unroll
       for (int u = 0; u < 2; ++u)
@@ -382,8 +381,7 @@ __global__ __launch_bounds__(64 * HEAD_SLICES) void f32_head_kernel(F32HeadArgs 
         for (int t = 0; t < 4; ++t)
 #pragma unroll
           for (int i = 0; i < 4; ++i)
-            d[s >> 1][i] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[s][t][i], bd[s][t], d[s >> 1][i],
-                                                                0, 0, 0);
+            d[s >> 1][i] = mfma16(w[s][t][i], bd[s][t], d[s >> 1][i]);
       if (b < h.B) {
         float* o = h.below + z * h.below_slot + static_cast<int64_t>(b) * h.below_ld + mo;
 #pragma unroll
@@ -401,78 +399,47 @@ __global__ __launch_bounds__(64 * HEAD_SLICES) void f32_head_kernel(F32HeadArgs 
   }
 }
 
-// Backward-weight and the SGD update of every layer in one launch (nothing
-// reads the weights after the last backward-data launch).  A workgroup of 2 x
-// 2 waves covers 32 T inputs x 32 T outputs of one layer, a wave 16 T x 16 T:
-// dW[o][i] over the batch, then W <- W - lr dW.  The biases have workgroups of
-// their own (64 outputs each): blocks of 64 batch rows row by row, the block
-// sums left to right.
-constexpr int UPDATE_ROWS = 1024 + 80;  // largest batch and the groups read ahead
-template <int T>
-__global__ __launch_bounds__(256) void f32_update_kernel(F32UpdateArgs u) {
-  __shared__ __attribute__((aligned(16))) int32_t rows[UPDATE_ROWS];  // of the activations
-  __shared__ float bias_sum[16][64];  // of the blocks of 64 batch rows
-  typedef typename Vec<T>::T V;
-  const int lane = threadIdx.x & 63, c16 = lane & 15, gq = lane >> 4;
-  const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
-  const int work = xcd_item(blockIdx.y * gridDim.x + blockIdx.x, gridDim.x * gridDim.y);
-  const int z = work / gridDim.x, wg = work % gridDim.x;
-  // one load of the whole table instead of one per layer, each waiting for
-  // the last (entries past the last layer are INT_MAX)
-  int l = 0;
+// One wave's 16 T inputs x 16 T outputs of a layer: dW over the batch, then
+// the update.  `rows`: the addresses of the batch's dataset rows (GATHER).
+template <int T, bool GATHER>
+__device__ __forceinline__ void update_tile(const F32UpdateArgs& u, const F32UpdateLayer& y, int z,
+                                            int rep, int m0, int n0, int lane,
+                                            const uint64_t* rows) {
+  const int c16 = lane & 15, gq = lane >> 4;
+  // Four batch rows of 16 T columns per load.  Columns past M are other rows'
+  // values (never stored); delta rows are padded to 64.
+  const float* A = y.a + z * y.a_slot + m0;
+  const float* D = y.d + z * y.d_slot + n0;
+  // (Gathered rows: column 0 of the tile instead, inside the row.)
+  const uint32_t ma = m0 + T * c16 < y.M ? 4u * ((m0 & 16 * T) + T * c16) : 0;
+  uint32_t a_at[4], d_at[4];
 #pragma unroll
-  for (int i = 1; i < F32_UPDATE_LAYERS; ++i) l += wg >= u.first_wg[i] ? 1 : 0;
-  const F32UpdateLayer& y = u.layer[l];
-  const int rep = u.order[z];
-  const int gm = (y.M + 32 * T - 1) / (32 * T), tile = wg - u.first_wg[l];
-  const int m0 = (tile % gm * 2 + (wave & 1)) * 16 * T;
-  const int n0 = (tile / gm * 2 + (wave >> 1)) * 16 * T;
-  const bool gathered = l == 0 && u.gather != nullptr;
-  for (int b = threadIdx.x; b < UPDATE_ROWS; b += 256)
-    rows[b] = b >= u.B ? 0 : (gathered ? u.gather[z * u.gather_slot + b] : b);
-  __syncthreads();
-  if (tile >= y.tiles) {  // the biases of 64 outputs
-    const int n = (tile - y.tiles) * 64 + lane, blocks = (u.B + 63) / 64;
-    const float* D = y.d + z * y.d_slot + n;  // rows padded to 64
-    for (int b = wave; b < blocks; b += 4) {
-      float sum = 0.0f;
-      for (int k = 64 * b; k < 64 * b + 64; k += 16) {
-        float v[16];
-#pragma unroll
-        for (int e = 0; e < 16; ++e) v[e] = *(k + e < u.B ? D + offset_of(k + e, y.d_ld) : f32_zero);
-#pragma unroll
-        for (int e = 0; e < 16; ++e) sum += v[e];
-      }
-      bias_sum[b][lane] = sum;
-    }
-    __syncthreads();
-    if (wave == 0 && n < y.N) {
-      float db = bias_sum[0][lane];
-      for (int b = 1; b < blocks; ++b) db += bias_sum[b][lane];
-      const int64_t at = static_cast<int64_t>(rep) * u.master_slot + y.b_off + n;
-      u.master[at] = fmaf(-u.lr, db, u.master_in[static_cast<int64_t>(rep) * u.master_in_slot +
-                                                 y.b_off + n]);
-    }
-    return;
+  for (int t = 0; t < 4; ++t) {
+    a_at[t] = 4u * ((4 * gq + t) * static_cast<uint32_t>(y.a_ld) + T * c16);
+    d_at[t] = 4u * ((4 * gq + t) * static_cast<uint32_t>(y.d_ld) + T * c16);
   }
-  if (m0 >= y.M || n0 >= y.N) return;
-  // Columns past M repeat column 0 (never stored); delta rows are padded to 64.
-  const int ma = m0 + T * c16;
-  const float* A = y.a + z * y.a_slot + (ma < y.M ? ma : 0);
-  const float* D = y.d + z * y.d_slot + n0 + T * c16;
   float a[2][T][4], b[2][T][4];
-  i32x4 row[2];  // of the group loaded next into each set
-  auto load_rows = [&](int set, int s) {
-    row[set] = *reinterpret_cast<const i32x4*>(&rows[16 * s + 4 * gq]);
+  uint64_t row[2][4];  // of the group loaded next into each set
+  auto load_index = [&](int set, int s) {
+    if constexpr (GATHER) {
+#pragma unroll
+      for (int t = 0; t < 4; ++t) row[set][t] = rows[16 * s + 4 * gq + t];
+    }
   };
   auto load = [&](int set, int s) {
+    // 16 batch rows from row 16 s; zeros past the batch
+    const int k = min(16 * s, u.B), n = min(u.B - k, 16);
+    const Buf db = buffer(D + static_cast<int64_t>(k) * y.d_ld, n > 0 ? (n * y.d_ld - n0) * 4 : 0);
+    const Buf ab = buffer(A + static_cast<int64_t>(k) * y.a_ld, n > 0 ? (n * y.a_ld - m0) * 4 : 0);
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
-      const int k = 16 * s + 4 * gq + t;
-      const float* pa = A + offset_of(row[set][t], y.a_ld);
-      const float* pd = D + offset_of(k, y.d_ld);
-      const V va = *reinterpret_cast<const V*>(k < u.B ? pa : f32_zero);
-      const V vb = *reinterpret_cast<const V*>(k < u.B ? pd : f32_zero);
+      float va[T], vb[T];
+      if constexpr (GATHER) {
+        load_vec<T>(va, reinterpret_cast<const float*>(row[set][t] + ma));
+      } else {
+        load_buffer_vec<T>(va, ab, a_at[t], 0);
+      }
+      load_buffer_vec<T>(vb, db, d_at[t], 0);
 #pragma unroll
       for (int i = 0; i < T; ++i) {
         a[set][i][t] = va[i];
@@ -491,13 +458,11 @@ __global__ __launch_bounds__(256) void f32_update_kernel(F32UpdateArgs u) {
 #pragma unroll
       for (int i = 0; i < T; ++i)
 #pragma unroll
-        for (int j = 0; j < T; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[set][i][t], b[set][j][t], acc[i][j], 0,
-                                                           0, 0);
+        for (int j = 0; j < T; ++j) acc[i][j] = mfma16(a[set][i][t], b[set][j][t], acc[i][j]);
   };
   const int ns = (u.B + 15) / 16;
-  load_rows(0, 0);
-  load_rows(1, 1);
+  load_index(0, 0);
+  load_index(1, 1);
   load(0, 0);
   // The weights, needed after the products only.  Lane (gq, c16) holds inputs
   // m0 + 4 T gq .. + 4 T - 1 of outputs n0 + T c16 + j.
@@ -508,20 +473,24 @@ __global__ __launch_bounds__(256) void f32_update_kernel(F32UpdateArgs u) {
 #pragma unroll
   for (int j = 0; j < T; ++j) {
     const int n = n0 + T * c16 + j < y.N ? n0 + T * c16 + j : 0;
-    const float* row = win + y.w_off + static_cast<int64_t>(n) * y.M;
+    const float* wrow = win + y.w_off + static_cast<int64_t>(n) * y.M;
 #pragma unroll
-    for (int qd = 0; qd < T; ++qd)
-      w[j][qd] = *reinterpret_cast<const f32x4*>(mo + 4 * qd < y.M ? row + mo + 4 * qd : f32_zero);
+    for (int qd = 0; qd < T; ++qd) {
+      const int m = mo + 4 * qd < y.M ? mo + 4 * qd : 0;
+      w[j][qd] = *reinterpret_cast<const f32x4*>(wrow + m);
+    }
   }
   for (int s = 0; s < ns; s += 2) {
-    load_rows(0, s + 2);
     load(1, s + 1);
+    load_index(0, s + 2);
     loads_first();
     mma(0);
-    load_rows(1, s + 3);
+    loads_first();
     load(0, s + 2);
+    load_index(1, s + 3);
     loads_first();
     mma(1);  // zeros past the batch
+    loads_first();
   }
 #pragma unroll
   for (int j = 0; j < T; ++j) {
@@ -538,13 +507,88 @@ __global__ __launch_bounds__(256) void f32_update_kernel(F32UpdateArgs u) {
   }
 }
 
+// Backward-weight and the SGD update of every layer in one launch (nothing
+// reads the weights after the last backward-data launch).  A workgroup of 2 x
+// 2 waves covers 32 T inputs x 32 T outputs of one layer, a wave 16 T x 16 T:
+// dW[o][i] over the batch, then W <- W - lr dW.  The biases have workgroups of
+// their own (64 outputs each): blocks of 64 batch rows row by row, the block
+// sums left to right.
+constexpr int UPDATE_ROWS = 1024 + 80;  // largest batch and the groups read ahead
+template <int T>
+__global__ __launch_bounds__(256, T == 4 ? 1 : 2) void f32_update_kernel(F32UpdateArgs u) {
+  // Addresses of the gathered activations' rows at the workgroup's first column
+  // (zeros past the batch): one addition per load.
+  __shared__ __attribute__((aligned(16))) uint64_t rows[UPDATE_ROWS];
+  __shared__ float bias_sum[16][64];  // of the blocks of 64 batch rows
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
+  const int work = xcd_item(blockIdx.y * gridDim.x + blockIdx.x, gridDim.x * gridDim.y);
+  const int z = work / gridDim.x, wg = work % gridDim.x;
+  // one load of the whole table instead of one per layer, each waiting for
+  // the last (entries past the last layer are INT_MAX)
+  int l = 0;
+#pragma unroll
+  for (int i = 1; i < F32_UPDATE_LAYERS; ++i) l += wg >= u.first_wg[i] ? 1 : 0;
+  const F32UpdateLayer& y = u.layer[l];
+  const int rep = u.order[z];
+  const int gm = (y.M + 32 * T - 1) / (32 * T), tile = wg - u.first_wg[l];
+  const int m0 = (tile % gm * 2 + (wave & 1)) * 16 * T;
+  const int n0 = (tile / gm * 2 + (wave >> 1)) * 16 * T;
+  const bool gathered = l == 0 && u.gather != nullptr;
+  if (tile >= y.tiles) {  // the biases of 64 outputs
+    const int n = (tile - y.tiles) * 64 + lane, blocks = (u.B + 63) / 64;
+    const Buf D = buffer(y.d + z * y.d_slot, static_cast<int64_t>(u.B) * y.d_ld * 4);
+    for (int b = wave; b < blocks; b += 4) {
+      float sum = 0.0f;
+      for (int k = 64 * b; k < 64 * b + 64; k += 16) {
+        float v[16];
+#pragma unroll
+        for (int e = 0; e < 16; ++e)  // rows padded to 64; zeros past the batch
+          v[e] = load_buffer<1>(D, 4u * n, 4u * min(k + e, u.B) * static_cast<uint32_t>(y.d_ld));
+#pragma unroll
+        for (int e = 0; e < 16; ++e) sum += v[e];
+      }
+      bias_sum[b][lane] = sum;
+    }
+    __syncthreads();
+    if (wave == 0 && n < y.N) {
+      float db = bias_sum[0][lane];
+      for (int b = 1; b < blocks; ++b) db += bias_sum[b][lane];
+      const int64_t at = static_cast<int64_t>(rep) * u.master_slot + y.b_off + n;
+      u.master[at] = fmaf(-u.lr, db, u.master_in[static_cast<int64_t>(rep) * u.master_in_slot +
+                                                 y.b_off + n]);
+    }
+    return;
+  }
+  if (gathered) {
+    const uint64_t base = reinterpret_cast<uint64_t>(y.a + z * y.a_slot + (m0 & ~(32 * T - 1)));
+    const uint64_t zero = reinterpret_cast<uint64_t>(f32_zero_words);
+    for (int b = threadIdx.x; b < UPDATE_ROWS; b += 256)
+      rows[b] = b < u.B ? base + 4 * offset_of(u.gather[z * u.gather_slot + b], y.a_ld) : zero;
+    __syncthreads();
+  }
+  if (m0 >= y.M || n0 >= y.N) return;
+  // The larger tile keeps a SIMD's products busy alone, and two such waves on
+  // one SIMD slowed each other (dense activations: 100 us for a pair of tiles, 39
+  // for one): these registers leave room for one.
+  if constexpr (T == 4) asm volatile("" ::: "a255");
+  if (gathered) update_tile<T, true>(u, y, z, rep, m0, n0, lane, rows);
+  else update_tile<T, false>(u, y, z, rep, m0, n0, lane, rows);
+}
+
 template <int MODE, int MI, int NJ>
 hipError_t f32_gemm_launch(const GemmArgs& g, int n_slots, hipStream_t s) {
   const int64_t gx = static_cast<int64_t>((g.M + 16 * MI - 1) / (16 * MI)) *
                      ((g.N + 16 * NJ - 1) / (16 * NJ));
   if (gx * n_slots > 0x7FFFFFFF) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((f32_gemm_kernel<MODE, MI, NJ>), dim3(static_cast<unsigned>(gx), n_slots),
-                     dim3(64 * SLICES), 0, s, g);
+  const dim3 grid(static_cast<unsigned>(gx), n_slots), block(64 * SLICES);
+  if constexpr (MODE == GEMM_FWD) {
+    if (g.gather) {
+      hipLaunchKernelGGL((f32_gemm_kernel<MODE, MI, NJ, true>), grid, block, 0, s, g);
+      return hipGetLastError();
+    }
+  }
+  hipLaunchKernelGGL((f32_gemm_kernel<MODE, MI, NJ, false>), grid, block, 0, s, g);
   return hipGetLastError();
 }
 
@@ -568,11 +612,12 @@ hipError_t launch_f32_gemm(const GemmArgs& g, GemmMode mode, int n_slots, hipStr
 
 hipError_t launch_f32_head(const F32HeadArgs& h, int n_slots, hipStream_t s) {
   if (h.B < 1 || n_slots < 1) return hipSuccess;
-  if (h.C < 1 || h.C > F32_HEAD_CLASSES) return hipErrorInvalidValue;
+  if (h.C < 1 || h.C > F32_HEAD_CLASSES || (h.below && h.act_gather)) return hipErrorInvalidValue;
   const dim3 grid((h.B + 15) / 16, n_slots), block(64 * HEAD_SLICES);
-#define HEAD(mi)                                                                          \
-  if (h.below) hipLaunchKernelGGL((f32_head_kernel<mi, true>), grid, block, 0, s, h);     \
-  else hipLaunchKernelGGL((f32_head_kernel<mi, false>), grid, block, 0, s, h)
+#define HEAD(mi)                                                                                \
+  if (h.below) hipLaunchKernelGGL((f32_head_kernel<mi, true, false>), grid, block, 0, s, h);    \
+  else if (h.act_gather) hipLaunchKernelGGL((f32_head_kernel<mi, false, true>), grid, block, 0, s, h); \
+  else hipLaunchKernelGGL((f32_head_kernel<mi, false, false>), grid, block, 0, s, h)
   if (h.C <= 16) { HEAD(1); }
   else if (h.C <= 32) { HEAD(2); }
   else { HEAD(4); }
@@ -601,7 +646,7 @@ hipError_t launch_f32_update(const F32UpdateArgs& u_in, int n_slots, hipStream_t
   // per byte but whose waves are four times as many and start up sooner.
   // Measured: 784-512-256-10, batch 64, 8 replicas (304 workgroups of the
   // larger tile) 22.8 against 17.9 us; 1024-2048-2048-10, batch 512, 1 replica
-  // (465 workgroups) 83 against 102 us.
+  // (465 workgroups) 82 against 102 us.
   for (int l = u.n_layers; l < F32_UPDATE_LAYERS; ++l) u.first_wg[l] = 0x7FFFFFFF;
   int t = 4;
   int64_t gx = groups(4);

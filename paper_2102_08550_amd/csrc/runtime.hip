@@ -512,10 +512,8 @@ oscars_status oscars_create_cnn(oscars_ctx** out, const oscars_cnn_model* m, int
     a.Wo = c->img_w[l];
     a.Co = c->img_c[l];
     a.stride = c->conv_stride[l];
-    int splits = 0;
-    int64_t per = 0;
-    conv_wgrad_ranges(a, &splits, &per);
-    c->cpart_slot_l[l] = round_up(static_cast<int64_t>(splits) * a.Co * (9LL * a.C + 1), 64);
+    c->cpart_slot_l[l] =
+        round_up(static_cast<int64_t>(conv_wgrad_max_splits(a)) * a.Co * (9LL * a.C + 1), 64);
   }
   int64_t part_total = 0;
   for (int l = 1; l <= Lc + 1; ++l) part_total += c->cpart_slot_l[l];
@@ -785,7 +783,7 @@ hipError_t cnn_backward(oscars_ctx* c, float* replicas, const float* master_in,
     a.part = c->cpart_l[l];
     a.part_slot = c->cpart_slot_l[l];
     if (l > 1 && conv_pair_fits(ad, a, ns)) {
-      // one or two replicas: backward-data and backward-weight in one launch
+      // backward-data and backward-weight in one launch
       e = timed(c, OSCARS_KERNEL_BWD_FUSED,
                 [&] { return launch_conv_pair(ad, a, ns, c->stream); });
     } else {
@@ -802,6 +800,7 @@ hipError_t cnn_backward(oscars_ctx* c, float* replicas, const float* master_in,
     u.splits = a.splits;
     u.M = a.Co;
     u.N = 9 * a.C + 1;
+    u.packed = conv_direct(a);
     u.w_off = a.w_off;
     u.b_off = a.b_off;
     upd.push_back(u);
