@@ -16,7 +16,7 @@
 // Cout.  Backward-data of a stride-2 layer treats each parity class of the
 // input pixels as a GEMM of its own with its one, two or four taps.  Every
 // output of the forward and of backward-data is one K-order sum; backward-weight
-// sums ranges of output pixels (eight consecutive parts of a range by one
+// sums ranges of output pixels (four consecutive parts of a range by one
 // wave each, added in order), one partial per range, which the update kernel
 // adds in a fixed order.  So results depend on nothing but the inputs.
 #include <hip/hip_runtime.h>
@@ -55,6 +55,29 @@ __host__ __device__ inline int pass_pixels(const ConvArgs& a, int pass, int cls)
   return cls < 0 ? a.B * a.H * a.W : a.B * class_rows(a, cls) * class_cols(a, cls);
 }
 
+// Quotient and remainder by one divisor.  Exact for n < 2^21: (n + 1/2) / d is
+// at least 1 / 2d from an integer, the product's error below n / d 2^-22.  (An
+// integer division is some 35 vector instructions, and those of a tile's
+// pixels took as long as a third of its products.)
+struct Divisor {
+  int d;
+  float inv;
+  __device__ explicit Divisor(int d_) : d(d_), inv(__builtin_amdgcn_rcpf(static_cast<float>(d_))) {}
+  __device__ int operator()(int n, int& rem) const {
+    const int q = static_cast<int>(fmaf(static_cast<float>(n), inv, 0.5f * inv));
+    rem = n - __mul24(q, d);
+    return q;
+  }
+};
+constexpr int IMAGE_PIXELS = 1 << 20;  // per image: a tile's or range's pixels stay below 2^21
+
+// The 3 x 3 taps (bit 3 r + s) around (h, w) that lie inside an H x W image;
+// (h, w) itself does.
+__device__ __forceinline__ uint32_t taps_inside(int h, int w, int H, int W) {
+  const uint32_t s = (w > 0 ? 1u : 0u) | 2u | (w + 1 < W ? 4u : 0u);
+  return (h > 0 ? s : 0u) | s << 3 | (h + 1 < H ? s << 6 : 0u);
+}
+
 // Forward (PASS = CONV_FWD) or backward-data of one wave's 16 MI x 16 NJ tile:
 // rows m0 .. (output / input channels), pixels n0 .. of slot z.
 //   UNI: the channels per tap are a multiple of 16, so a K group lies in one
@@ -86,7 +109,10 @@ __device__ __forceinline__ void conv_pixels_tile(const ConvArgs& a, int cls, int
 
   // Offsets are from the row of the tile's first pixel, moved back by a row and
   // a pixel (taps reach that far; a class's taps do not), so none is negative.
-  const int img0 = n0 / (rows * cols), i0 = (n0 - img0 * rows * cols) / cols;
+  const int img0 = n0 / (rows * cols), n_img = n0 - img0 * rows * cols;
+  const Divisor by_image(rows * cols), by_row(cols);
+  int j0;
+  const int i0 = __builtin_amdgcn_readfirstlane(by_row(n_img, j0));
   const int64_t base = (static_cast<int64_t>(img0) * PH + st * i0) * PW * D;
   const int back = cls < 0 ? (PW + 1) * D : 0;
   const Buf px = buffer(src + base - back, 0x7FFFFFFF);
@@ -95,16 +121,13 @@ __device__ __forceinline__ void conv_pixels_tile(const ConvArgs& a, int cls, int
   const float* ptr[NJ];  // GATHER: the centre
 #pragma unroll
   for (int j = 0; j < NJ; ++j) {
-    const int n = n0 + 16 * j + load_row(lane), nc = n < N ? n : N - 1;
-    const int img = nc / (rows * cols), p = nc - img * rows * cols, pi = p / cols, pj = p - pi * cols;
+    const int n = n0 + 16 * j + load_row(lane), nc = min(n, N - 1);
+    int p, pj;
+    const int img = img0 + by_image(nc - n0 + n_img, p), pi = by_row(p, pj);
     uint32_t ok = 0;
     if (cls < 0) {
-#pragma unroll
-      for (int t = 0; t < 9; ++t) {
-        const int h = FWD ? st * pi + t / 3 - 1 : pi + 1 - t / 3;
-        const int w = FWD ? st * pj + t % 3 - 1 : pj + 1 - t % 3;
-        ok |= static_cast<uint32_t>((h >= 0) & (h < PH) & (w >= 0) & (w < PW)) << t;
-      }
+      ok = taps_inside(st * pi, st * pj, PH, PW);
+      if (!FWD) ok = __builtin_bitreverse32(ok) >> 23;  // tap t reads around at 8 - t
     } else {
 #pragma unroll
       for (int t = 0; t < 4; ++t) {  // tap (tr, ts) reads dZ (i + (odd and tr = 0), j + ...)
@@ -284,8 +307,9 @@ __device__ __forceinline__ void conv_pixels_tile(const ConvArgs& a, int cls, int
     const int n = n0 + 16 * j + c16, nc = n < N ? n : N - 1;
     int out = nc * M;
     if (!FWD && cls >= 0) {
-      const int img = nc / (rows * cols), p = nc - img * rows * cols, pi = p / cols;
-      out = ((img * a.H + 2 * pi + oddr) * a.W + 2 * (p - pi * cols) + oddc) * a.C;
+      int p, pj;
+      const int img = img0 + by_image(nc - n0 + n_img, p), pi = by_row(p, pj);
+      out = ((img * a.H + 2 * pi + oddr) * a.W + 2 * pj + oddc) * a.C;
     }
     f32x4 v[MI], x[MI], y[MI];
 #pragma unroll
@@ -333,11 +357,13 @@ __global__ __launch_bounds__(64 * FWD_WAVES, 2) void conv_fwd_direct_kernel(Conv
 }
 
 // Backward-weight of 64 weight columns (tap, channel) x 16 NJ output channels
-// over one range of output pixels: eight waves take consecutive eighths of
-// the range, their sums are added in order through LDS.  The positions of the
+// over one range of output pixels: four waves take consecutive quarters of
+// the range, their sums are added in order through LDS.  (Eight waves filled a
+// CU with one workgroup, whose table and final sum nothing overlapped: 32x32
+// CNN of 128 channels at eight replicas 11.8 against 11.2 ms per round.)  The positions of the
 // range's pixels (offset of the centre tap, one bit per tap inside) are
 // tabled in LDS once.
-constexpr int BWD_WAVES = 8;
+constexpr int BWD_WAVES = 4;
 constexpr int WG_RANGE = 1024;  // longest range
 struct PixelPos {
   uint32_t at, out_of;  // byte offset of the moved centre; bit t: tap t lies outside
@@ -364,19 +390,17 @@ __device__ __forceinline__ void conv_weights_tile(const ConvArgs& a, int tile, i
   const int kbeg = split * R, kend = min(K, kbeg + R);
   // Offsets from the input row of the range's first pixel, moved back as in
   // conv_pixels_tile.
-  const int img0 = kbeg / hw, i0 = (kbeg - img0 * hw) / a.Wo;
+  const int img0 = kbeg / hw, k_img = kbeg - img0 * hw;
+  const Divisor by_image(hw), by_row(a.Wo);
+  int j0;
+  const int i0 = __builtin_amdgcn_readfirstlane(by_row(k_img, j0));
   const int64_t base = (static_cast<int64_t>(img0) * a.H + a.stride * i0) * a.W * a.C;
   const int back = (a.W + 1) * a.C;
   for (int p = threadIdx.x; p < R + 64; p += 64 * BWD_WAVES) {
-    const int k = min(kbeg + p, K - 1);
-    const int img = k / hw, q = k - img * hw, i = q / a.Wo, j = q - i * a.Wo;
+    int q, j;
+    const int img = img0 + by_image(min(p, K - 1 - kbeg) + k_img, q), i = by_row(q, j);
     const int hi = a.stride * i, wi = a.stride * j;
-    uint32_t ok = 0;
-#pragma unroll
-    for (int t = 0; t < 9; ++t) {
-      const int h = hi + t / 3 - 1, w = wi + t % 3 - 1;
-      ok |= static_cast<uint32_t>((h >= 0) & (h < a.H) & (w >= 0) & (w < a.W)) << t;
-    }
+    uint32_t ok = taps_inside(hi, wi, a.H, a.W);
     if (kbeg + p >= kend) ok = 0;
     if constexpr (GATHER) {
       const int64_t img_at = static_cast<int64_t>(a.gather[z * a.gather_slot + img]) * a.in_ld;
@@ -485,7 +509,7 @@ __device__ __forceinline__ void conv_weights_tile(const ConvArgs& a, int tile, i
     add_bias(f0);
   }
 
-  // The eight waves' sums, added in order; a thread takes four consecutive
+  // The waves' sums, added in order; a thread takes four consecutive
   // columns of one output channel.
   const int64_t MW = static_cast<int64_t>(a.Co) * C9;
   float* part = a.part + z * a.part_slot + split * (MW + a.Co);
@@ -505,9 +529,11 @@ __device__ __forceinline__ void conv_weights_tile(const ConvArgs& a, int tile, i
         *reinterpret_cast<f32x4*>(&sm.red[wave][16 * jj + c16][quad_row<true, MI>(qd, lane)]) =
             acc_quad<true>(acc, ph * (NJ / NP) + jj, qd);
     __syncthreads();
-    const int row = threadIdx.x >> 4, col = 4 * (threadIdx.x & 15);  // 32 rows x 16 quads
-    const int oo = o0 + NJ * (row & 15) + ph * (NJ / NP) + (row >> 4);
-    if (row < 16 * (NJ / NP) && oo < a.Co && m0 + col < C9) {
+    const int col = 4 * (threadIdx.x & 15);
+#pragma unroll
+    for (int row = threadIdx.x >> 4; row < 16 * (NJ / NP); row += 4 * BWD_WAVES) {
+      const int oo = o0 + NJ * (row & 15) + ph * (NJ / NP) + (row >> 4);
+      if (oo >= a.Co || m0 + col >= C9) continue;
       f32x4 v = *reinterpret_cast<const f32x4*>(&sm.red[0][row][col]);
 #pragma unroll
       for (int w = 1; w < BWD_WAVES; ++w)
@@ -525,7 +551,7 @@ __device__ __forceinline__ void conv_weights_tile(const ConvArgs& a, int tile, i
 
 // Backward-weight alone, of a first layer (GATHER: its images are dataset rows).
 template <int WJ, bool GATHER>
-__global__ __launch_bounds__(64 * BWD_WAVES) void conv_wgrad_direct_kernel(ConvArgs w) {
+__global__ __launch_bounds__(64 * BWD_WAVES, 2) void conv_wgrad_direct_kernel(ConvArgs w) {
   __shared__ __attribute__((aligned(16))) WgradLds sm;
   conv_weights_tile<WJ, GATHER>(w, xcd_item(blockIdx.x, gridDim.x), blockIdx.y, sm);
 }
@@ -535,7 +561,7 @@ __global__ __launch_bounds__(64 * BWD_WAVES) void conv_wgrad_direct_kernel(ConvA
 // what the other writes, and together they fill CUs that either leaves idle
 // with one or two replicas.
 template <int MI, int NJ, int WJ, bool UNI>
-__global__ __launch_bounds__(64 * BWD_WAVES) void conv_bwd_direct_kernel(ConvArgs d, ConvArgs w,
+__global__ __launch_bounds__(64 * BWD_WAVES, 2) void conv_bwd_direct_kernel(ConvArgs d, ConvArgs w,
                                                                          int nd) {
   __shared__ __attribute__((aligned(16))) WgradLds sm;
   // Within each kind of work (and each class below) the workgroups of one XCD
@@ -618,12 +644,13 @@ void wgrad_launch(const dim3& grid, hipStream_t s, const ConvArgs& w) {
 // gathers.
 bool conv_direct(const ConvArgs& a) {
   return (a.C & 3) == 0 && (a.Co & 3) == 0 && a.C >= 4 &&
+         static_cast<int64_t>(a.H) * a.W <= IMAGE_PIXELS &&
          static_cast<int64_t>(a.W) * a.C <= (1 << 24) && static_cast<int64_t>(a.Wo) * a.Co <= (1 << 24) &&
          9LL * a.C * a.Co < (1 << 28);
 }
 
 int conv_direct_range(const ConvArgs& a) {
-  // 1024 pixels (128 per wave): long enough that the partials are a small part
+  // 1024 pixels (256 per wave): long enough that the partials are a small part
   // of the traffic; shorter where the layer has few pixels, so that it still
   // gives 16 ranges.
   const int64_t pixels = static_cast<int64_t>(a.B) * a.Ho * a.Wo;

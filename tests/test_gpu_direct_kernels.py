@@ -1,0 +1,100 @@
+"""The register-fed fp32 kernels at the edges of their tiles and dispatch rules,
+against the oracle on the same seeded inputs.
+
+* MLP: the fused head at 16, 17, 33, 64 classes and the separate path at 65;
+  batches of one row, around 16 and past 128; widths and K that leave ragged
+  32-wide K tiles and ragged output tiles; the 64 x 64 update tiles with a
+  gathered first layer whose batch is no multiple of 16.
+* Convolutions: a gathered first layer on the direct kernels (4 and 16
+  channels), K groups within one tap (channels a multiple of 16) and across taps
+  (4, 12, 20), 1 to 3 output-channel blocks, stride 2 on odd sizes, several
+  pixel ranges with a ragged last one, pixels beyond one tile of every kind.
+* Evaluation over several passes with a ragged last one, MLP and CNN.
+
+The tolerance is FP32_TOL of the trajectory tests: these are sums of the same
+lengths (K up to 2304, pixels up to 4800) in fp32, whose order alone differs."""
+import numpy as np
+import pytest
+
+import oracle
+import workload
+from _parity import FP32_TOL, assert_tensors_close, gpu_rounds, oracle_rounds, say, tensor_errors
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def P():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    import paper_2102_08550_amd
+    return paper_2102_08550_amd
+
+
+def _mlp(dims, batch, tau, seed, K=None):
+    K = K or len(tau)
+    return workload.Config("direct-mlp", dims, workload.FP32, K=K, n_rows=4 * batch + 3,
+                           batch=batch, tau_rule="given", tau_given=tau, lr=0.05, rounds=1,
+                           seed=seed)
+
+
+def _cnn(image, conv, batch, tau, seed, classes=10):
+    return workload.Config("direct-cnn", (image[0] * image[1] * image[2], classes), workload.FP32,
+                           K=len(tau), n_rows=4 * batch + 3, batch=batch, tau_rule="given",
+                           tau_given=tau, lr=0.1, rounds=1, seed=seed, image=image, conv=conv,
+                           mean_scale=0.5)
+
+
+CASES = {
+    "head-16": _mlp((24, 40, 16), 15, (2, 1), 101),
+    "head-17": _mlp((40, 72, 17), 16, (2, 1), 102),
+    "head-33": _mlp((136, 264, 33), 17, (1, 2), 103),
+    "head-64": _mlp((264, 1032, 64), 1, (2, 3), 104),
+    "classes-65": _mlp((72, 104, 65), 33, (2, 1), 105),
+    "softmax": _mlp((792, 10), 65, (3, 0, 2), 106),
+    "update-64": _mlp((1032, 2056, 10), 130, (1, 2, 1), 107),
+    "update-last": _mlp((2056, 1544, 136), 128, (2,), 108),
+    "gather-4": _cnn((9, 11, 4), ((4, 1), (12, 2)), 5, (2, 1), 111),
+    "gather-16": _cnn((8, 6, 16), ((16, 1), (32, 1)), 6, (2, 1), 112),
+    "taps-cross": _cnn((7, 9, 3), ((20, 1), (12, 1), (36, 2)), 7, (1, 2), 113),
+    "blocks-3": _cnn((11, 13, 3), ((48, 1), (68, 2), (68, 1), (68, 1, 1)), 4, (2, 1), 114),
+    "ranges": _cnn((20, 20, 3), ((16, 1), (32, 1), (64, 2)), 12, (1, 2), 115),
+    "many-slots": _cnn((16, 16, 3), ((32, 1), (64, 2), (64, 1, 0)), 16, (1, 1, 1, 1, 1), 116),
+}
+
+
+@pytest.mark.parametrize("name", CASES)
+def test_direct_kernels_match_oracle(P, name):
+    cfg = CASES[name]
+    say(f"direct {name}: dims={cfg.dims} image={cfg.image} conv={cfg.conv} B={cfg.batch}")
+    ds = workload.gen_dataset(cfg)
+    init = workload.gen_init(cfg)
+    tau = np.array([cfg.tau_given])
+    g_gpu, l_gpu = gpu_rounds(cfg, ds, init, tau, fused=False)
+    g_ref, l_ref = oracle_rounds(cfg, ds, init, tau)
+    assert_tensors_close(tensor_errors(g_gpu[0], g_ref[0]), FP32_TOL, name)
+    for k in range(cfg.K):
+        if tau[0][k]:
+            assert abs(l_gpu[0][k] - l_ref[0][k]) <= FP32_TOL * max(abs(l_ref[0][k]), 1e-2), k
+
+
+# One row, one pass less one row, exactly one, and one with a ragged second.
+@pytest.mark.parametrize("rows", [1, 8191, 8192, 8192 + 70])
+def test_evaluation_passes_match_oracle(P, rows):
+    import torch
+    cfg = _mlp((40, 72, 17), 16, (1, 1), 121)
+    say(f"evaluate {rows} rows")
+    init = workload.gen_init(cfg)
+    ctx = P.Context(cfg.dims, P.FP32, cfg.K, cfg.batch)
+    try:
+        ev = workload.gen_eval_set(cfg, rows)
+        loss, hits = ctx.evaluate(torch.from_numpy(ctx.pack(init)).cuda(),
+                                  torch.from_numpy(ev.x).cuda(),
+                                  torch.from_numpy(ev.y.astype(np.int32)).cuda())
+        ref_loss, ref_hits, gaps = oracle.mlp.evaluate(
+            [(W.astype(np.float64), b.astype(np.float64)) for W, b in init],
+            ev.x.astype(np.float64), ev.y)
+        assert abs(loss - ref_loss) <= FP32_TOL * abs(ref_loss)
+        assert abs(hits - ref_hits) <= int((np.asarray(gaps) < 1e-4).sum())  # rounding decides these
+    finally:
+        ctx.close()
