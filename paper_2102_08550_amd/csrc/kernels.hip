@@ -66,6 +66,12 @@ struct Shape {
 //   taken; below that, the K chunks are split over workgroups (split-K).
 enum { SHAPE_L = 0, SHAPE_M = 1, SHAPE_S = 2, SHAPE_W = 3, SHAPE_V = 4 };
 template <int MODE, int SID> struct ShapeOf;
+// Forward tiles of every shape stream through LDS (gemm_dma_kernel), 3 or 4
+// stages: 5 (L), 6 (M) and 9 (S) stages gave nothing, so a step is not bound by
+// the latency of its loads.
+template <> struct ShapeOf<GEMM_FWD, SHAPE_L> { typedef Shape<128, 128, 2, 4, 3, 1> type; };
+template <> struct ShapeOf<GEMM_FWD, SHAPE_M> { typedef Shape<64, 128, 1, 4, 4, 1> type; };
+template <> struct ShapeOf<GEMM_FWD, SHAPE_S> { typedef Shape<64, 64, 2, 2, 4, 1> type; };
 template <int MODE> struct ShapeOf<MODE, SHAPE_L> { typedef Shape<128, 128, 2, 4, 2, 1> type; };
 template <int MODE> struct ShapeOf<MODE, SHAPE_M> { typedef Shape<64, 128, 1, 4, 2, 1> type; };
 template <int MODE> struct ShapeOf<MODE, SHAPE_S> { typedef Shape<64, 64, 2, 2, 2, 1> type; };
@@ -124,7 +130,7 @@ __device__ __forceinline__ u32x4 load16(bool ok, const T* p) {
 }
 
 // Tile of an operand stored K-contiguous: 128 rows (M or N) x BK.
-//   rows valid: row0 + r < R (row r of memory is gather[row0 + r] if gathered);
+//   rows valid: row0 + r < R;
 //   chunk valid: k < ext.
 template <int NTHR, int ROWS>
 struct RowSrc {
@@ -133,15 +139,12 @@ struct RowSrc {
   static constexpr int P = ROWS * 8 / NTHR;
   const T* rowp[P];
   bool rowok[P];
-  __device__ __forceinline__ void init(const T* base, int64_t ld, const int32_t* gather, int row0,
-                                       int R, int tid) {
+  __device__ __forceinline__ void init(const T* base, int64_t ld, int row0, int R, int tid) {
 #pragma unroll
     for (int p = 0; p < P; ++p) {
       const int gr = row0 + ((tid + NTHR * p) >> 3);
       rowok[p] = gr < R;
-      const int grc = gr < R ? gr : R - 1;
-      const int64_t row = gather ? gather[grc] : grc;
-      rowp[p] = base + row * ld;
+      rowp[p] = base + static_cast<int64_t>(gr < R ? gr : R - 1) * ld;
     }
   }
 };
@@ -158,16 +161,6 @@ struct RowTile {
       const int k = k0 + ((tid + NTHR * p) & 7) * CH;
       const bool ok = src.rowok[p] && k < ext;
       v[p] = load16(ok, src.rowp[p] + k);
-    }
-  }
-  // Copy of the loaded chunks to dst (same row index, row stride ld_dst).
-  __device__ __forceinline__ void copy_out(T* dst, int64_t ld_dst, int row0, int R, int k0,
-                                           int ext, int tid) const {
-#pragma unroll
-    for (int p = 0; p < P; ++p) {
-      const int idx = tid + NTHR * p, gr = row0 + (idx >> 3), k = k0 + (idx & 7) * CH;
-      if (gr < R && k < ext)
-        *reinterpret_cast<u32x4*>(dst + static_cast<int64_t>(gr) * ld_dst + k) = v[p];
     }
   }
   __device__ __forceinline__ void store(uint32_t* lds, int tid) const {
@@ -329,10 +322,12 @@ __device__ __forceinline__ void store_out_with(const GemmArgs& g, int z, int n, 
 // chunk c only and stores it as fp32 partial c of its outputs (g.part);
 // splitk_reduce_kernel then sums the partials in chunk order and applies the
 // epilogue.
-template <int MODE, bool GATHER, int SID, bool SPLIT>
-__global__ __launch_bounds__((ShapeOf<MODE, SID>::type::NT), (ShapeOf<MODE, SID>::type::MIN_WAVES)) void
+template <int SID, bool SPLIT>
+__global__ __launch_bounds__((ShapeOf<GEMM_DGRAD, SID>::type::NT),
+                             (ShapeOf<GEMM_DGRAD, SID>::type::MIN_WAVES)) void
 gemm_kernel(GemmArgs g) {
   typedef uint16_t T;
+  constexpr int MODE = GEMM_DGRAD;
   typedef typename ShapeOf<MODE, SID>::type S;
   constexpr int NTHR = S::NT, WAVES_N = S::WAVES_N, MI = S::MI, NJ = S::NJ;
   constexpr int BM = S::BM, BN = S::BN;
@@ -364,22 +359,12 @@ gemm_kernel(GemmArgs g) {
   const T* B = static_cast<const T*>(g.b) + z * g.b_slot;
   const float* master_in = g.master_in + static_cast<int64_t>(rep) * g.master_in_slot;
 
-  // A: weights K-contiguous in FWD, weights M-contiguous in DGRAD.  B:
-  // activations / delta K-contiguous.
-  typedef typename std::conditional<MODE == GEMM_FWD, RowTile<NTHR, BM>, TransTile<NTHR, BM>>::type
-      TileA;
+  // A: weights, M-contiguous.  B: delta, K-contiguous, its row pointers fixed
+  // for the whole K loop.
+  typedef TransTile<NTHR, BM> TileA;
   typedef RowTile<NTHR, BN> TileB;
-  // Row pointers of the K-contiguous operands, fixed for the whole K loop.
-  RowSrc<NTHR, BM> sa;
   RowSrc<NTHR, BN> sb;
-  if constexpr (MODE == GEMM_FWD) sa.init(A, g.a_ld, nullptr, m0, M, tid);
-  sb.init(B, g.b_ld, GATHER ? g.gather + z * g.gather_slot : nullptr, n0, N, tid);
-  // Forward layer 1 also keeps the gathered batch rows, contiguous, for the
-  // backward-weight pass of that layer: K tile kt of the rows is written by
-  // the workgroup of M tile kt mod (number of M tiles), so the copy is spread
-  // over all workgroups of the launch.
-  T* rows_out = GATHER ? static_cast<T*>(g.rows_out) + z * g.rows_out_slot : nullptr;
-  const int gm = (M + BM - 1) / BM, mt = m0 / BM;
+  sb.init(B, g.b_ld, n0, N, tid);
 
   // Accumulator element (i, j, r) sits at row m = mrow(i, r>>2) + (r & 3),
   // column n = ncol(j): four consecutive rows per lane and group r>>2.
@@ -397,19 +382,9 @@ gemm_kernel(GemmArgs g) {
   constexpr bool TOTAL = !SPLIT;
   f32x16 tot[TOTAL ? MI : 1][TOTAL ? NJ : 1];
 
-  // A: rows m (RowTile, FWD) or k rows with m chunks (TransTile).
-  // B: rows n (RowTile).
-#define LOAD_A(t, k0)                                                     \
-  do {                                                                    \
-    if constexpr (MODE == GEMM_FWD) t.load(sa, A, k0, g.a_ext, tid);      \
-    else t.load(A, g.a_ld, m0, g.a_ext, k0, K, tid);                      \
-  } while (0)
-#define LOAD_B(t, k0)                                                     \
-  do {                                                                    \
-    t.load(sb, B, k0, g.b_ext, tid);                                      \
-    if (GATHER && (k0) < kend && ((k0) / BK) % gm == mt)                  \
-      t.copy_out(rows_out, g.rows_out_ld, n0, N, k0, g.b_ext, tid);       \
-  } while (0)
+  // A: k rows with m chunks.  B: rows n.
+  auto load_a = [&](TileA& t, int k0) { t.load(A, g.a_ld, m0, g.a_ext, k0, K, tid); };
+  auto load_b = [&](TileB& t, int k0) { t.load(sb, B, k0, g.b_ext, tid); };
 
   auto compute = [&](int buf) { mma_tile<MI, NJ>(lds_a(buf), lds_b(buf), wm, wn, lane, acc); };
 
@@ -442,8 +417,8 @@ gemm_kernel(GemmArgs g) {
     TileB tB[ST];
 #pragma unroll
     for (int u = 0; u < ST; ++u) {
-      LOAD_A(tA[u], kbeg + u * BK);
-      LOAD_B(tB[u], kbeg + u * BK);
+      load_a(tA[u], kbeg + u * BK);
+      load_b(tB[u], kbeg + u * BK);
     }
     tA[0].store(lds_a(0), tid);
     tB[0].store(lds_b(0), tid);
@@ -451,8 +426,8 @@ gemm_kernel(GemmArgs g) {
     static_assert(!TOTAL || TPC % ST == 0, "chunks start on register set 0");
     auto tile_step = [&](int j, auto uc) {
       constexpr int u = decltype(uc)::value;
-      LOAD_A(tA[u], kbeg + (j + ST) * BK);
-      LOAD_B(tB[u], kbeg + (j + ST) * BK);
+      load_a(tA[u], kbeg + (j + ST) * BK);
+      load_b(tB[u], kbeg + (j + ST) * BK);
       compute(j & 1);
       tA[(u + 1) % ST].store(lds_a((j + 1) & 1), tid);
       tB[(u + 1) % ST].store(lds_b((j + 1) & 1), tid);
@@ -479,8 +454,6 @@ gemm_kernel(GemmArgs g) {
       fold_chunk(nk <= TPC);
     }
   }
-#undef LOAD_A
-#undef LOAD_B
 
   if constexpr (SPLIT) {
     // Partial `chunk` of outputs (m, n): fp32 at part[slot][chunk][n][m]
@@ -542,7 +515,7 @@ gemm_kernel(GemmArgs g) {
 }
 
 // ---------------------------------------------------------------------------
-// Forward / backward-data of bf16 models with whole-batch tiles (W, V): K
+// Forward of bf16 models, and backward-data with whole-batch tiles (W, V): K
 // tiles go from global memory straight into LDS (global_load_lds, 16 bytes
 // per lane), ST stages deep, so no VGPRs hold tiles in flight and ST - 1
 // stages load while one is multiplied.  One wave instruction fills 8 LDS rows
@@ -704,7 +677,8 @@ gemm_dma_kernel(GemmArgs g) {
     if constexpr (MODE == GEMM_DGRAD) ta[decltype(par)::value].pin();
     const int k0 = k_of(j);
     if (GATHER && k0 < kend && (k0 / BK) % gm == mt) {
-      // Layer 1: this workgroup keeps K tile j of the gathered batch rows.
+      // Layer 1 keeps the gathered batch rows, contiguous, for its
+      // backward-weight pass: this workgroup K tile j, the next M tile the next.
       constexpr int PC = BN * 8 / NTHR;
 #pragma unroll
       for (int p = 0; p < PC; ++p) {
@@ -1877,13 +1851,10 @@ hipError_t gemm_launch_shape(const GemmArgs& g, int n_slots, hipStream_t s) {
       static_cast<int64_t>((g.N + S::BN - 1) / S::BN) * ((g.M + S::BM - 1) / S::BM) * nchunks;
   if (gx * n_slots > 0x7FFFFFFF) return hipErrorInvalidValue;
   const dim3 grid(static_cast<unsigned>(gx), n_slots);
-  constexpr bool DMA = SID == SHAPE_W || SID == SHAPE_V;
+  constexpr bool DMA = MODE == GEMM_FWD || SID == SHAPE_W || SID == SHAPE_V;
   if (g.gather) {
     if constexpr (MODE == GEMM_FWD) {
-      if constexpr (DMA)
-        hipLaunchKernelGGL((gemm_dma_kernel<MODE, true, SID, SPLIT>), grid, dim3(S::NT), 0, s, g);
-      else
-        hipLaunchKernelGGL((gemm_kernel<MODE, true, SID, SPLIT>), grid, dim3(S::NT), 0, s, g);
+      hipLaunchKernelGGL((gemm_dma_kernel<MODE, true, SID, SPLIT>), grid, dim3(S::NT), 0, s, g);
     } else {
       return hipErrorInvalidValue;  // only the forward pass gathers dataset rows
     }
@@ -1891,7 +1862,7 @@ hipError_t gemm_launch_shape(const GemmArgs& g, int n_slots, hipStream_t s) {
     if constexpr (DMA)
       hipLaunchKernelGGL((gemm_dma_kernel<MODE, false, SID, SPLIT>), grid, dim3(S::NT), 0, s, g);
     else
-      hipLaunchKernelGGL((gemm_kernel<MODE, false, SID, SPLIT>), grid, dim3(S::NT), 0, s, g);
+      hipLaunchKernelGGL((gemm_kernel<SID, SPLIT>), grid, dim3(S::NT), 0, s, g);
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || !SPLIT) return e;
