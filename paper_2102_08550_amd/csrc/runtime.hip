@@ -181,7 +181,7 @@ void free_ctx(oscars_ctx* c) {
 // kEvalRows rows per pass in up to kEvalBytes of buffers of its own where the
 // local steps' activations (K * max_batch rows) hold fewer.
 constexpr int64_t kEvalRows = 8192;
-constexpr int64_t kEvalBytes = int64_t{32} << 20;
+constexpr int64_t kEvalBytes = int64_t{96} << 20;
 
 hipError_t alloc_eval(oscars_ctx* c) {
   const int64_t have = static_cast<int64_t>(c->K) * c->max_batch;
@@ -1499,8 +1499,12 @@ hipError_t run_evaluate(oscars_ctx* c, const float* params, const void* x, const
     auto act = [&](int l) { return own ? c->eval_act[l & 1] : c->act[l]; };
     float* logits = own ? c->eval_logits : c->logits;
     const bool head = !c->bf16 && c->dims[L] <= F32_HEAD_CLASSES;
-    for (int64_t i0 = 0; i0 < n_rows && e == hipSuccess; i0 += c->eval_rows) {
-      const int N = static_cast<int>(std::min<int64_t>(c->eval_rows, n_rows - i0));
+    // passes of equal size (whole 256-row tiles): a short last one would leave
+    // most of the CUs idle for as long as a full one
+    const int64_t passes = (n_rows + c->eval_rows - 1) / c->eval_rows;
+    const int64_t pass = std::min(c->eval_rows, ((n_rows + passes - 1) / passes + 255) / 256 * 256);
+    for (int64_t i0 = 0; i0 < n_rows && e == hipSuccess; i0 += pass) {
+      const int N = static_cast<int>(std::min<int64_t>(pass, n_rows - i0));
       const void* rows0 = static_cast<const char*>(x) +
                           i0 * c->dims[0] * static_cast<int64_t>(c->esize);
       for (int l = 1; l <= (head ? L - 1 : L) && e == hipSuccess; ++l) {
