@@ -156,6 +156,21 @@ hipError_t launch_softmax_ce(const float* logits, int64_t ld, int64_t slot_strid
                              void* delta, bool delta_bf16, float* loss, int64_t loss_slot,
                              int n_slots, hipStream_t s, int32_t* correct = nullptr);
 
+// The forward of a bf16 model's last layer (GemmArgs as for launch_gemm, not
+// gathered, K a multiple of 8; out is not written) and the softmax in one
+// launch, for at most BF16_HEAD_CLASSES classes: delta bf16 [slot][B][out_ld]
+// (slot stride out_slot) and loss as launch_softmax_ce, bit for bit.
+constexpr int BF16_HEAD_CLASSES = 64;
+struct Bf16HeadArgs {
+  const int32_t* y;
+  const int32_t* gather;  // dataset row of batch row b (labels); nullptr: b itself
+  int64_t gather_slot;
+  uint16_t* delta;
+  float* loss;
+  int64_t loss_slot;
+};
+hipError_t launch_bf16_head(const GemmArgs& g, const Bf16HeadArgs& h, int n_slots, hipStream_t s);
+
 // wcopy[z][i] = bf16(master[order[z]][i]) for i < n, z < n_slots.
 hipError_t launch_cast_bf16(const float* master, int64_t master_slot, const int32_t* order,
                             uint16_t* wcopy, int64_t wcopy_slot, int64_t n, int n_slots,

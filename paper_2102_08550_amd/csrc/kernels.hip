@@ -22,6 +22,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
 #include <atomic>
 #include <map>
 #include <mutex>
@@ -1623,6 +1624,151 @@ __global__ __launch_bounds__(256) void softmax_ce_kernel(const float* logits, in
   }
 }
 
+// Last layer of a bf16 MLP with at most 64 classes and the softmax, one launch:
+// a workgroup takes 32 batch rows, a wave one K chunk of 32 classes, four K tiles
+// of both operands in registers ahead, turned through LDS of the wave's own.  The
+// layer is a chain (its tile is 32 x 32 MB, K long), so what counts is its
+// latency: the streaming tiles waited some 1000 cycles per 64 K for barriers.
+// 2048 inputs, 10 classes, 128 rows of 2 to 12 replicas: 10.8 us against
+// 18.6 (13.9 and 4.7) for the two launches.  (Operands
+// loaded as the products take them, 32 rows per load, were bound by the vector
+// L1: 12 us.)  The sums (chunks from zero in K
+// order, then left to right, then the bias; the softmax of a row over one wave)
+// are those of the separate launches.
+constexpr int BH_WAVES = 8, BH_ROWS = 32, BH_AHEAD = 4;
+typedef __amdgpu_buffer_rsrc_t Buf;
+constexpr uint32_t BH_NOWHERE = 0x80000000u;  // past every buffer: reads zeros
+template <int MB>
+__global__ __launch_bounds__(64 * BH_WAVES, 2) void bf16_head_kernel(GemmArgs g, Bf16HeadArgs h) {
+  constexpr int CHUNKS = BH_WAVES / MB, LD = 32 * MB + 1;  // chunks at a time
+  __shared__ __attribute__((aligned(16))) union {
+    uint32_t tile[BH_WAVES][2][32 * ROW_U32];  // each wave's own
+    float red[BH_WAVES][BH_ROWS][33];
+  } sm;
+  auto& red = sm.red;
+  __shared__ float logit[BH_ROWS][LD];
+  const int tid = threadIdx.x, lane = tid & 63, r = lane & 31, hi = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  uint32_t *const As = sm.tile[wave][0], *const Bs = sm.tile[wave][1];
+  const int z = blockIdx.y, rep = g.order[z], n0 = blockIdx.x * BH_ROWS;
+  const uint16_t* A = static_cast<const uint16_t*>(g.a) + (g.a_by_order ? rep : z) * g.a_slot;
+  const uint16_t* B = static_cast<const uint16_t*>(g.b) + z * g.b_slot + n0 * g.b_ld;
+  const float* master_in = g.master_in + static_cast<int64_t>(rep) * g.master_in_slot;
+  const Buf ab = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(A), 0, 0x7FFFFFFF, 0x00020000);
+  const Buf bb = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(B), 0, 0x7FFFFFFF, 0x00020000);
+  const int block = wave % MB, nchunks = (g.K + KCHUNK - 1) / KCHUNK;
+  // Eight lanes load 64 K of one class or batch row (past the last: the last
+  // again, not used): chunk lane & 7 of rows 8 p + lane / 8.
+  const int lr = lane >> 3, lc = lane & 7;
+  uint32_t a_at[4], b_at[4];
+#pragma unroll
+  for (int p = 0; p < 4; ++p) {
+    a_at[p] = 2u * (min(32 * block + 8 * p + lr, g.M - 1) * static_cast<uint32_t>(g.a_ld) + 8 * lc);
+    b_at[p] = 2u * (min(8 * p + lr, g.N - 1 - n0) * static_cast<uint32_t>(g.b_ld) + 8 * lc);
+  }
+  // the softmax: one lane per class, RP rows of a wave side by side, Q in turn
+  constexpr int LPR = 32 * MB, RP = 64 / LPR, Q = BH_ROWS / BH_WAVES / RP;
+  const int cls = lane % LPR, row0 = wave * Q * RP + lane / LPR;
+  int label[Q];
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    const int b = min(n0 + row0 + q * RP, g.N - 1);
+    label[q] = h.y[h.gather ? h.gather[z * h.gather_slot + b] : b];
+  }
+  constexpr int EL = BH_ROWS * 32 * MB / (64 * BH_WAVES);  // logits per thread
+  float tot[EL];
+  for (int c0 = 0; c0 < nchunks; c0 += CHUNKS) {
+    const int chunk = c0 + wave / MB;
+    const int kbeg = min(chunk * KCHUNK, g.K), kend = min(kbeg + KCHUNK, g.K);
+    u32x4 a[BH_AHEAD][4], b[BH_AHEAD][4];
+    auto load = [&](int u, int k0) {
+      const int k = min(k0, kend);  // zeros past the chunk
+      const bool in = 8 * lc < kend - k;
+#pragma unroll
+      for (int p = 0; p < 4; ++p) {
+        a[u][p] = __builtin_bit_cast(
+            u32x4, __builtin_amdgcn_raw_buffer_load_b128(ab, in ? a_at[p] : BH_NOWHERE, 2 * k, 0));
+        b[u][p] = __builtin_bit_cast(
+            u32x4, __builtin_amdgcn_raw_buffer_load_b128(bb, in ? b_at[p] : BH_NOWHERE, 2 * k, 0));
+      }
+    };
+    f32x16 acc[1][1];
+#pragma unroll
+    for (int e = 0; e < 16; ++e) acc[0][0][e] = 0.0f;
+#pragma unroll
+    for (int u = 0; u < BH_AHEAD; ++u) load(u, kbeg + u * BK);
+    // LDS operations of one wave execute in order: no barrier, one buffer
+    for (int k = kbeg; k < kend; k += BH_AHEAD * BK) {
+#pragma unroll
+      for (int u = 0; u < BH_AHEAD; ++u) {
+#pragma unroll
+        for (int p = 0; p < 4; ++p) {
+          *reinterpret_cast<u32x4*>(As + lds_word(8 * p + lr, lc)) = a[u][p];
+          *reinterpret_cast<u32x4*>(Bs + lds_word(8 * p + lr, lc)) = b[u][p];
+        }
+        __builtin_amdgcn_wave_barrier();
+        load(u, k + (u + BH_AHEAD) * BK);
+        __builtin_amdgcn_sched_barrier(0);
+        mma_tile<1, 1>(As, Bs, 0, 0, lane, acc);
+        __builtin_amdgcn_wave_barrier();
+      }
+    }
+    __syncthreads();  // every wave is done with its tiles
+    // rows m = 8 q + 4 hi .. + 3 of column n = r
+#pragma unroll
+    for (int e = 0; e < 16; ++e) red[wave][r][8 * (e >> 2) + 4 * hi + (e & 3)] = acc[0][0][e];
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < EL; ++e) {
+      const int i = tid + 64 * BH_WAVES * e, row = i / (32 * MB), c = i % (32 * MB);
+      for (int w = 0; w < CHUNKS && c0 + w < nchunks; ++w) {
+        const float v = red[w * MB + (c >> 5)][row][c & 31];
+        tot[e] = c0 + w == 0 ? v : tot[e] + v;
+      }
+    }
+    __syncthreads();
+  }
+#pragma unroll
+  for (int e = 0; e < EL; ++e) {
+    const int i = tid + 64 * BH_WAVES * e, row = i / (32 * MB), c = i % (32 * MB);
+    logit[row][c] = tot[e] + master_in[g.b_off + min(c, g.M - 1)];
+  }
+  __syncthreads();
+  // As softmax_ce_kernel over one wave per row (the lanes past LPR hold nothing
+  // there); the rows' chains of shuffles side by side.
+  const float invB = 1.0f / static_cast<float>(g.N);
+  const bool in = cls < g.M;
+  float v[Q], zl[Q], mx[Q], ex[Q], sum[Q];
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    mx[q] = v[q] = in ? logit[row0 + q * RP][cls] : -INFINITY;
+    zl[q] = __shfl(v[q], label[q] & (LPR - 1), LPR);
+  }
+#pragma unroll
+  for (int d = LPR / 2; d >= 1; d >>= 1)
+#pragma unroll
+    for (int q = 0; q < Q; ++q) mx[q] = fmaxf(mx[q], __shfl_xor(mx[q], d));
+#pragma unroll
+  for (int q = 0; q < Q; ++q) sum[q] = ex[q] = in ? expf(v[q] - mx[q]) : 0.0f;
+#pragma unroll
+  for (int d = LPR / 2; d >= 1; d >>= 1)
+#pragma unroll
+    for (int q = 0; q < Q; ++q) sum[q] += __shfl_xor(sum[q], d);
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    const int b = n0 + row0 + q * RP;
+    const bool label_ok = label[q] >= 0 && label[q] < g.M;
+    const float dv = in ? (ex[q] / sum[q] - (cls == label[q] ? 1.0f : 0.0f)) * invB : 0.0f;
+    if (b >= g.N) continue;
+    uint16_t* delta = h.delta + z * g.out_slot + static_cast<int64_t>(b) * g.out_ld;
+    for (int c = cls; c < g.out_ld; c += LPR)
+      delta[c] = c < LPR ? static_cast<uint16_t>(f2bf(dv)) : 0;
+    if (cls == 0)
+      h.loss[z * h.loss_slot + b] =
+          label_ok ? logf(sum[q]) - (zl[q] - mx[q]) : __builtin_nanf("");
+  }
+}
+
 __global__ __launch_bounds__(256) void cast_bf16_kernel(const float* master, int64_t master_slot,
                                                         const int32_t* order, uint16_t* wcopy,
                                                         int64_t wcopy_slot, int64_t n) {
@@ -2293,6 +2439,17 @@ void softmax_dispatch(const float* logits, int64_t ld, int64_t slot_stride, int 
   else
     softmax_launch<BF16_OUT, 0>(logits, ld, slot_stride, C, B, y, gather, gather_slot, delta, loss,
                                 loss_slot, n_slots, s, correct);
+}
+
+hipError_t launch_bf16_head(const GemmArgs& g, const Bf16HeadArgs& h, int n_slots, hipStream_t s) {
+  if (g.N < 1 || n_slots < 1) return hipSuccess;
+  if (g.M < 1 || g.M > BF16_HEAD_CLASSES || g.gather || g.K % 8 != 0 ||
+      static_cast<int64_t>(BF16_HEAD_CLASSES) * std::max(g.a_ld, g.b_ld) >= (1 << 29))
+    return hipErrorInvalidValue;
+  const dim3 grid((g.N + BH_ROWS - 1) / BH_ROWS, n_slots), block(64 * BH_WAVES);
+  if (g.M > 32) hipLaunchKernelGGL(bf16_head_kernel<2>, grid, block, 0, s, g, h);
+  else hipLaunchKernelGGL(bf16_head_kernel<1>, grid, block, 0, s, g, h);
+  return hipGetLastError();
 }
 
 hipError_t launch_softmax_ce(const float* logits, int64_t ld, int64_t slot_stride, int C, int B,

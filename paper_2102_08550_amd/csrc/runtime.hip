@@ -1202,6 +1202,9 @@ oscars_status run_local_steps(oscars_ctx* c, float* replicas, const float* start
 
   const int L = c->L;
   const int64_t rows_slot = static_cast<int64_t>(tau_max) * B;
+  // the last layer and the softmax in one launch (the first layer, whose launch
+  // keeps the gathered rows, is not the last one)
+  const bool fused_head = L > 1 && c->dims[L] <= BF16_HEAD_CLASSES && c->dims[L - 1] % 8 == 0;
   for (int j = 0; j < tau_max; ++j) {
     int ns = 0, ns_next = 0;
     while (ns < n_slots && tau[order[ns]] > j) ++ns;
@@ -1277,11 +1280,22 @@ oscars_status run_local_steps(oscars_ctx* c, float* replicas, const float* start
       }
       g.out_ld = c->ld[l];
       g.out_slot = c->act_slot(l);
-      e = timed(c, OSCARS_KERNEL_FWD, [&] { return launch_gemm(g, GEMM_FWD, c->bf16, ns, c->stream, c->tuner); });
+      if (fused_head && l == L) {
+        Bf16HeadArgs h{};
+        h.y = s->y;
+        h.gather = rows_j;
+        h.gather_slot = rows_slot;
+        h.delta = static_cast<uint16_t*>(c->delta[L]);
+        h.loss = c->loss_dev + static_cast<int64_t>(j) * B;
+        h.loss_slot = rows_slot;
+        e = timed(c, OSCARS_KERNEL_SOFTMAX, [&] { return launch_bf16_head(g, h, ns, c->stream); });
+      } else {
+        e = timed(c, OSCARS_KERNEL_FWD, [&] { return launch_gemm(g, GEMM_FWD, c->bf16, ns, c->stream, c->tuner); });
+      }
       if (e != hipSuccess) return hip_fail(e);
     }
     // loss gradient
-    e = timed(c, OSCARS_KERNEL_SOFTMAX, [&] {
+    if (!fused_head) e = timed(c, OSCARS_KERNEL_SOFTMAX, [&] {
       return launch_softmax_ce(c->logits, c->ld[L], c->act_slot(L), c->dims[L], B, s->y, rows_j,
                                rows_slot, c->delta[L], c->bf16, c->loss_dev + static_cast<int64_t>(j) * B,
                                rows_slot, ns, c->stream);

@@ -1,24 +1,26 @@
-"""The register-fed fp32 kernels at the edges of their tiles and dispatch rules,
+"""The register-fed kernels at the edges of their tiles and dispatch rules,
 against the oracle on the same seeded inputs.
 
 * MLP: the fused head at 16, 17, 33, 64 classes and the separate path at 65;
   batches of one row, around 16 and past 128; widths and K that leave ragged
   32-wide K tiles and ragged output tiles; the 64 x 64 update tiles with a
   gathered first layer whose batch is no multiple of 16.
+* The fused bf16 head: 32, 33 and 64 classes (65: the separate launches), one
+  K chunk, a ragged second one, and more chunks than the waves take at once.
 * Convolutions: a gathered first layer on the direct kernels (4 and 16
   channels), K groups within one tap (channels a multiple of 16) and across taps
   (4, 12, 20), 1 to 3 output-channel blocks, stride 2 on odd sizes, several
   pixel ranges with a ragged last one, pixels beyond one tile of every kind.
 * Evaluation over several passes with a ragged last one, MLP and CNN.
 
-The tolerance is FP32_TOL of the trajectory tests: these are sums of the same
+The tolerance is FP32_TOL (BF16_TOL) of the trajectory tests: these are sums of the same
 lengths (K up to 2304, pixels up to 4800) in fp32, whose order alone differs."""
 import numpy as np
 import pytest
 
 import oracle
 import workload
-from _parity import FP32_TOL, assert_tensors_close, gpu_rounds, oracle_rounds, say, tensor_errors
+from _parity import BF16_TOL, FP32_TOL, assert_tensors_close, gpu_rounds, oracle_rounds, say, tensor_errors
 
 pytestmark = pytest.mark.gpu
 
@@ -31,9 +33,8 @@ def P():
     return paper_2102_08550_amd
 
 
-def _mlp(dims, batch, tau, seed, K=None):
-    K = K or len(tau)
-    return workload.Config("direct-mlp", dims, workload.FP32, K=K, n_rows=4 * batch + 3,
+def _mlp(dims, batch, tau, seed, dtype=workload.FP32):
+    return workload.Config("direct-mlp", dims, dtype, K=len(tau), n_rows=4 * batch + 3,
                            batch=batch, tau_rule="given", tau_given=tau, lr=0.05, rounds=1,
                            seed=seed)
 
@@ -54,6 +55,10 @@ CASES = {
     "softmax": _mlp((792, 10), 65, (3, 0, 2), 106),
     "update-64": _mlp((1032, 2056, 10), 130, (1, 2, 1), 107),
     "update-last": _mlp((2056, 1544, 136), 128, (2,), 108),
+    "bf16-head-32": _mlp((16, 24, 32), 1, (2, 1), 131, workload.BF16),
+    "bf16-head-33": _mlp((40, 1032, 33), 33, (2, 1), 132, workload.BF16),
+    "bf16-head-64": _mlp((24, 9224, 64), 31, (1, 2), 133, workload.BF16),
+    "bf16-classes-65": _mlp((72, 2056, 65), 40, (2, 1), 134, workload.BF16),
     "gather-4": _cnn((9, 11, 4), ((4, 1), (12, 2)), 5, (2, 1), 111),
     "gather-16": _cnn((8, 6, 16), ((16, 1), (32, 1)), 6, (2, 1), 112),
     "taps-cross": _cnn((7, 9, 3), ((20, 1), (12, 1), (36, 2)), 7, (1, 2), 113),
@@ -72,10 +77,11 @@ def test_direct_kernels_match_oracle(P, name):
     tau = np.array([cfg.tau_given])
     g_gpu, l_gpu = gpu_rounds(cfg, ds, init, tau, fused=False)
     g_ref, l_ref = oracle_rounds(cfg, ds, init, tau)
-    assert_tensors_close(tensor_errors(g_gpu[0], g_ref[0]), FP32_TOL, name)
+    tol = BF16_TOL if cfg.dtype == workload.BF16 else FP32_TOL
+    assert_tensors_close(tensor_errors(g_gpu[0], g_ref[0]), tol, name)
     for k in range(cfg.K):
         if tau[0][k]:
-            assert abs(l_gpu[0][k] - l_ref[0][k]) <= FP32_TOL * max(abs(l_ref[0][k]), 1e-2), k
+            assert abs(l_gpu[0][k] - l_ref[0][k]) <= tol * max(abs(l_ref[0][k]), 1e-2), k
 
 
 # One row, one pass less one row, exactly one, and one with a ragged second.
