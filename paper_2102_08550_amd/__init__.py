@@ -119,9 +119,19 @@ def _check(status: int, what: str):
         raise OscarsError(status, what)
 
 
+_CTYPES = {np.int32: _i32, np.int64: _i64, np.float32: _f32}
+
+
 def _arr(a, dtype):
+    """``a`` as a contiguous array of ``dtype`` and a C pointer to it.  (Through
+    the buffer protocol: 1.3 us for five values, 5.8 us by way of
+    ndarray.ctypes and a pointer type looked up per call; a round passes
+    three such arrays, an average one.)"""
     a = np.ascontiguousarray(a, dtype=dtype)
-    return a, a.ctypes.data_as(_P(np.ctypeslib.as_ctypes_type(dtype)))
+    c = _CTYPES[dtype]
+    if a.size and a.flags.writeable:
+        return a, ctypes.pointer(c.from_buffer(a))
+    return a, a.ctypes.data_as(_P(c))
 
 
 def _stream_handle(stream=None) -> Optional[int]:
