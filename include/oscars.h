@@ -106,7 +106,9 @@ typedef struct {
  * (with pinned host staging), and, for bf16 models, the scratch replicas
  * on which OSCARS_BACKWARD_AUTO times the backward paths (K x the widest
  * layer, fp32 + bf16; left out where they would take
- * more than a quarter of the free device memory, and then nothing is timed).
+ * more than a quarter of the free device memory, and then nothing is timed);
+ * and, where those activations hold fewer rows, up to 96 MiB of activations
+ * for the passes of oscars_evaluate.
  * `hip_stream` (a hipStream_t, NULL = null stream) is the stream
  * oscars_local_steps enqueues on.  The context owns its tuning state (GEMM
  * tilings, backward path): contexts do not share it. */
@@ -270,6 +272,8 @@ oscars_status oscars_round_losses(oscars_ctx* ctx, float* losses);
  *             GPU in double in a fixed order: 256 contiguous runs of rows,
  *             each in row order, the run sums left to right);
  *   correct   out: rows whose label's logit is the largest (ties count).
+ * The rows go through in passes of equal size, as many rows as the
+ * workspace holds (a row's result does not depend on them).
  * Uses the context's activation workspace (not the losses of the last
  * local steps), allocates and frees temporary device buffers (the row
  * table, per-row losses and flags: 12 bytes per row), times GEMM tilings
@@ -349,8 +353,9 @@ oscars_status oscars_profile_begin(oscars_ctx* ctx, uint32_t kind_mask);
 oscars_status oscars_profile_end(oscars_ctx* ctx, double* ms, int64_t* launches);
 
 /* Tiling of the forward and backward-data GEMMs of one context (a tuning and
- * testing aid).  Every tiling sums each output in the same order (K in
- * chunks of 1024 summed left to right), so results are bit-identical
+ * testing aid).  Every tiling sums each output in the same order (bf16
+ * models: K in chunks of 1024 summed left to right; fp32 models: four
+ * interleaved slices of K added in order), so results are bit-identical
  * whatever the tiling; only the speed differs.
  *   OSCARS_TILING_AUTO (default): the launches of each GEMM configuration
  *     (layer shape, batch, number of active replicas) in the process are
@@ -361,8 +366,9 @@ oscars_status oscars_profile_end(oscars_ctx* ctx, double* ms, int64_t* launches)
  *     configurations still being tuned); while the stream is being captured
  *     into a graph
  *     a fixed rule chooses instead.
- *   L, M, S: 128 x 128, 64 x 128, 64 x 64 output tiles; LS: 128 x 128 with
- *     the K chunks split over workgroups (more than one K chunk);
+ *   L, M, S: 128 x 128, 64 x 128, 64 x 64 output tiles (fp32 models: 64 x
+ *     64, 32 x 32, 16 x 16); LS: 128 x 128 with the K chunks split over
+ *     workgroups (bf16, more than one K chunk);
  *   W: 128 x 256 (bf16 models, batches above 128); WS, VS: 128 x 256 and
  *     64 x 256 with the K chunks split over workgroups (bf16, batches above
  *     128, more than one K chunk) -- where a forced tiling does not apply, W

@@ -1629,12 +1629,11 @@ __global__ __launch_bounds__(256) void softmax_ce_kernel(const float* logits, in
 // of both operands in registers ahead, turned through LDS of the wave's own.  The
 // layer is a chain (its tile is 32 x 32 MB, K long), so what counts is its
 // latency: the streaming tiles waited some 1000 cycles per 64 K for barriers.
-// 2048 inputs, 10 classes, 128 rows of 2 to 12 replicas: 10.8 us against
-// 18.6 (13.9 and 4.7) for the two launches.  (Operands
-// loaded as the products take them, 32 rows per load, were bound by the vector
-// L1: 12 us.)  The sums (chunks from zero in K
-// order, then left to right, then the bias; the softmax of a row over one wave)
-// are those of the separate launches.
+// 2048 inputs, 10 classes, 128 rows of 2 to 12 replicas: 10.8 us against 18.6
+// (13.9 and 4.7) for the two launches.  (Operands loaded as the products take
+// them, 32 rows per load, were bound by the vector L1: 12 us.)  The sums (chunks
+// from zero in K order, then left to right, then the bias; the softmax of a row
+// over one wave) are those of the separate launches.
 constexpr int BH_WAVES = 8, BH_ROWS = 32, BH_AHEAD = 4;
 typedef __amdgpu_buffer_rsrc_t Buf;
 constexpr uint32_t BH_NOWHERE = 0x80000000u;  // past every buffer: reads zeros
