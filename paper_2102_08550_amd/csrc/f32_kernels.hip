@@ -537,14 +537,16 @@ __global__ __launch_bounds__(256, T == 4 ? 1 : 2) void f32_update_kernel(F32Upda
   const bool gathered = l == 0 && u.gather != nullptr;
   if (tile >= y.tiles) {  // the biases of 64 outputs
     const int n = (tile - y.tiles) * 64 + lane, blocks = (u.B + 63) / 64;
-    const Buf D = buffer(y.d + z * y.d_slot, static_cast<int64_t>(u.B) * y.d_ld * 4);
+    const float* D = y.d + z * y.d_slot;
     for (int b = wave; b < blocks; b += 4) {
       float sum = 0.0f;
       for (int k = 64 * b; k < 64 * b + 64; k += 16) {
         float v[16];
+        const int in = max(min(u.B - k, 16), 0);  // rows padded to 64; zeros past the batch
+        const Buf rows16 = buffer(D + static_cast<int64_t>(min(k, u.B)) * y.d_ld, in * y.d_ld * 4);
 #pragma unroll
-        for (int e = 0; e < 16; ++e)  // rows padded to 64; zeros past the batch
-          v[e] = load_buffer<1>(D, 4u * n, 4u * min(k + e, u.B) * static_cast<uint32_t>(y.d_ld));
+        for (int e = 0; e < 16; ++e)
+          v[e] = load_buffer<1>(rows16, 4u * n, 4u * min(e, in) * static_cast<uint32_t>(y.d_ld));
 #pragma unroll
         for (int e = 0; e < 16; ++e) sum += v[e];
       }
