@@ -9,12 +9,14 @@
 // no barrier in any K loop, and waves drift freely.  LDS is used once, to add
 // the K slices of an output tile.
 //
-// K order of forward and backward-data: slice j = 0..3 sums the 32-wide K
-// tiles j, j + 4, j + 8, ... from zero in K order (one wave per slice), the
-// output is ((s0 + s1) + s2) + s3 (the classifier head: eight slices).  It
-// depends only on K, not on the tile
-// shape or on how many replicas share a launch, so every tiling gives the
-// same bits.  Backward-weight sums the batch in row order.
+// K order of forward and backward-data: slice j = 0..3 takes the 32-wide K
+// tiles j, j + 4, j + 8, ... in order (one wave per slice), the output is
+// ((s0 + s1) + s2) + s3 (the classifier head: eight slices).  A slice sums each
+// 1024 of its K from zero and adds those sums in order, so no accumulator
+// runs over more than 1024 products however wide the layer is.  The order
+// depends only on K, not on the tile shape or on how many replicas share a
+// launch, so every tiling gives the same bits.  Backward-weight sums the batch
+// in row order.
 #include <hip/hip_runtime.h>
 
 #include <type_traits>
@@ -28,6 +30,7 @@ namespace {
 constexpr int SLICES = 4;  // K slices of forward / backward-data = waves per workgroup
 constexpr int HEAD_SLICES = 8;  // of the classifier head
 constexpr int KTILE = 32;  // K tile dealt to the slices in turn
+constexpr int KFOLD = 1024;  // of a slice's K in one running sum
 
 // K groups (16 deep) a wave loads at once: enough bytes in flight for small
 // tiles, few registers for large ones.  A slice is summed in whole pairs of
@@ -74,8 +77,9 @@ struct Rows {
 // or, TRANS, a_cols: row 0, column m0 (the tile's first) of a K x M matrix with
 // row stride a_ld = M.  Zeros from K (A) and from b_ext (B) on.  The loads of groups
 // q + 2, the turn through LDS of q + 1 and the products of q are in flight
-// together.
-template <bool TRANS, bool GATHER, int S, int MI, int NJ>
+// together.  FOLD: slices longer than KFOLD; kernels of their own, since the
+// second accumulator set cost the others registers they never used.
+template <bool TRANS, bool GATHER, bool FOLD, int S, int MI, int NJ>
 __device__ __forceinline__ void slice_products(f32x4 (&acc)[MI][NJ], const Rows<TRANS ? 1 : MI>& ra,
                                                const Rows<NJ>& rb, const float* a_cols,
                                                int m0, int64_t a_ld, int K, int b_ext, int slice,
@@ -160,7 +164,7 @@ __device__ __forceinline__ void slice_products(f32x4 (&acc)[MI][NJ], const Rows<
   blocks_write(lds, raw, lane);
   load_rows(G);
   blocks_read(lds, f0.rows, lane);
-  for (int q0 = 0; q0 < nq; q0 += 2 * G) {
+  auto two_sets = [&](int q0) {
     blocks_write(lds, raw, lane);
     load_rows(q0 + 2 * G);
     load_cols(f1, q0 + G);
@@ -173,13 +177,35 @@ __device__ __forceinline__ void slice_products(f32x4 (&acc)[MI][NJ], const Rows<
     blocks_read(lds, f0.rows, lane);
     mma(f1);
     spread<NM, NB, NB, NV>();
+  };
+  if constexpr (!FOLD) {
+    for (int q0 = 0; q0 < nq; q0 += 2 * G) two_sets(q0);
+  } else {
+    constexpr int PER = KFOLD / 16;  // groups per sum
+    static_assert(PER % (2 * G) == 0, "whole loop steps per sum");
+    f32x4 tot[MI][NJ];
+    for (int q0 = 0; q0 < nq;) {
+      const bool first = q0 == 0;
+      for (const int end = min(nq, q0 + PER); q0 < end; q0 += 2 * G) two_sets(q0);
+#pragma unroll
+      for (int i = 0; i < MI; ++i)
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) {
+          tot[i][j] = first ? acc[i][j] : tot[i][j] + acc[i][j];
+          acc[i][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) acc[i][j] = tot[i][j];
   }
 }
 
 // Forward and backward-data (GemmArgs as for the other GEMM kernels, without
 // rows_out and the split): one 16 MI x 16 NJ output tile per workgroup, one
 // K slice per wave.
-template <int MODE, int MI, int NJ, bool GATHER>
+template <int MODE, int MI, int NJ, bool GATHER, bool FOLD>
 __global__ __launch_bounds__(64 * SLICES, 2) void f32_gemm_kernel(GemmArgs g) {
   constexpr bool TRANS = MODE == GEMM_DGRAD;
   // The slices meet in LDS, at most 32 columns at a time (64 x 64 tiles: two
@@ -208,8 +234,8 @@ __global__ __launch_bounds__(64 * SLICES, 2) void f32_gemm_kernel(GemmArgs g) {
   if constexpr (GATHER) rb.init_gathered(B, g.b_ld, g.gather + z * g.gather_slot, n0, g.N, lane);
   else rb.init(B, g.b_ld, n0, g.N, lane);
   f32x4 acc[MI][NJ];
-  slice_products<TRANS, GATHER, SLICES>(acc, ra, rb, A + m0, m0, g.a_ld, g.K, g.b_ext, slice, lane,
-                                        sm.stage[slice]);
+  slice_products<TRANS, GATHER, FOLD, SLICES>(acc, ra, rb, A + m0, m0, g.a_ld, g.K, g.b_ext, slice,
+                                              lane, sm.stage[slice]);
 
   // A thread takes four consecutive rows m of column n.
   constexpr int PER = (MI * 4 * PN + 64 * SLICES - 1) / (64 * SLICES);  // per thread and phase
@@ -272,7 +298,7 @@ __global__ __launch_bounds__(64 * SLICES, 2) void f32_gemm_kernel(GemmArgs g) {
 // cross-entropy (as softmax_ce_kernel), and, with DGRAD, the delta of the
 // layer below (as f32_gemm_kernel's backward-data).  One launch instead of
 // three whose own latency was all they cost.
-template <int MI, bool DGRAD, bool GATHER>
+template <int MI, bool DGRAD, bool GATHER, bool FOLD>
 __global__ __launch_bounds__(64 * HEAD_SLICES) void f32_head_kernel(F32HeadArgs h) {
   constexpr int TM = 16 * MI, LD = TM + 4, ROWS = 16;
   constexpr int STAGE = slice_lds<false, MI, 1>();
@@ -302,8 +328,8 @@ __global__ __launch_bounds__(64 * HEAD_SLICES) void f32_head_kernel(F32HeadArgs 
   }
   const float bias = master[h.b_off + min(lane, h.C - 1)];
   f32x4 acc[MI][1];
-  slice_products<false, GATHER, HEAD_SLICES>(acc, ra, rb, nullptr, 0, h.K, h.K, h.K, wave, lane,
-                                             sm.stage[wave]);
+  slice_products<false, GATHER, FOLD, HEAD_SLICES>(acc, ra, rb, nullptr, 0, h.K, h.K, h.K, wave, lane,
+                                                   sm.stage[wave]);
   __syncthreads();  // every wave is done with its stage
 #pragma unroll
   for (int i = 0; i < MI; ++i)
@@ -578,20 +604,25 @@ __global__ __launch_bounds__(256, T == 4 ? 1 : 2) void f32_update_kernel(F32Upda
   else update_tile<T, false>(u, y, z, rep, m0, n0, lane, rows);
 }
 
-template <int MODE, int MI, int NJ>
-hipError_t f32_gemm_launch(const GemmArgs& g, int n_slots, hipStream_t s) {
+template <int MODE, int MI, int NJ, bool FOLD>
+hipError_t f32_gemm_grid(const GemmArgs& g, int n_slots, hipStream_t s) {
   const int64_t gx = static_cast<int64_t>((g.M + 16 * MI - 1) / (16 * MI)) *
                      ((g.N + 16 * NJ - 1) / (16 * NJ));
   if (gx * n_slots > 0x7FFFFFFF) return hipErrorInvalidValue;
   const dim3 grid(static_cast<unsigned>(gx), n_slots), block(64 * SLICES);
   if constexpr (MODE == GEMM_FWD) {
     if (g.gather) {
-      hipLaunchKernelGGL((f32_gemm_kernel<MODE, MI, NJ, true>), grid, block, 0, s, g);
+      hipLaunchKernelGGL((f32_gemm_kernel<MODE, MI, NJ, true, FOLD>), grid, block, 0, s, g);
       return hipGetLastError();
     }
   }
-  hipLaunchKernelGGL((f32_gemm_kernel<MODE, MI, NJ, false>), grid, block, 0, s, g);
+  hipLaunchKernelGGL((f32_gemm_kernel<MODE, MI, NJ, false, FOLD>), grid, block, 0, s, g);
   return hipGetLastError();
+}
+template <int MODE, int MI, int NJ>
+hipError_t f32_gemm_launch(const GemmArgs& g, int n_slots, hipStream_t s) {
+  return g.K > SLICES * KFOLD ? f32_gemm_grid<MODE, MI, NJ, true>(g, n_slots, s)
+                              : f32_gemm_grid<MODE, MI, NJ, false>(g, n_slots, s);
 }
 
 template <int MODE>
@@ -616,13 +647,18 @@ hipError_t launch_f32_head(const F32HeadArgs& h, int n_slots, hipStream_t s) {
   if (h.B < 1 || n_slots < 1) return hipSuccess;
   if (h.C < 1 || h.C > F32_HEAD_CLASSES || (h.below && h.act_gather)) return hipErrorInvalidValue;
   const dim3 grid((h.B + 15) / 16, n_slots), block(64 * HEAD_SLICES);
-#define HEAD(mi)                                                                                \
-  if (h.below) hipLaunchKernelGGL((f32_head_kernel<mi, true, false>), grid, block, 0, s, h);    \
-  else if (h.act_gather) hipLaunchKernelGGL((f32_head_kernel<mi, false, true>), grid, block, 0, s, h); \
-  else hipLaunchKernelGGL((f32_head_kernel<mi, false, false>), grid, block, 0, s, h)
-  if (h.C <= 16) { HEAD(1); }
-  else if (h.C <= 32) { HEAD(2); }
-  else { HEAD(4); }
+#define HEAD(mi, fold)                                                                               \
+  if (h.below) hipLaunchKernelGGL((f32_head_kernel<mi, true, false, fold>), grid, block, 0, s, h);   \
+  else if (h.act_gather)                                                                             \
+    hipLaunchKernelGGL((f32_head_kernel<mi, false, true, fold>), grid, block, 0, s, h);              \
+  else hipLaunchKernelGGL((f32_head_kernel<mi, false, false, fold>), grid, block, 0, s, h)
+  if (h.K > HEAD_SLICES * KFOLD) {
+    if (h.C <= 16) { HEAD(1, true); }
+    else if (h.C <= 32) { HEAD(2, true); }
+    else { HEAD(4, true); }
+  } else if (h.C <= 16) { HEAD(1, false); }
+  else if (h.C <= 32) { HEAD(2, false); }
+  else { HEAD(4, false); }
 #undef HEAD
   return hipGetLastError();
 }

@@ -104,3 +104,111 @@ def test_evaluation_passes_match_oracle(P, rows):
         assert abs(hits - ref_hits) <= int((np.asarray(gaps) < 1e-4).sum())  # rounding decides these
     finally:
         ctx.close()
+
+
+WIDE = 65536  # the widest accepted layer
+BIG = 2.0 ** 27
+# A product of 2^27 followed by ones: a running sum that has reached 2^27 (ulp 16)
+# loses every one that it adds.  Runs of at most 1024 products lose 1023 of
+# them; every other run is a whole number below 2^24, and adding it to the
+# total rounds by at most 8.  At most 64 + 8 such additions.  (A slice of 16384
+# or 8192 in one run loses all of its ones.)
+WIDE_BOUND = 1023 + (64 + 8) * 8
+
+
+def _context(P, torch, dims):
+    ctx = P.Context(dims, P.FP32, 1, 1)
+    y = torch.tensor([dims[-1] - 1], dtype=torch.int32).cuda()  # the last class
+    return ctx, y
+
+
+def _weights(dims):
+    return [(np.zeros((o, i), np.float32), np.zeros(o, np.float32))
+            for i, o in zip(dims, dims[1:])]
+
+
+def _step(ctx, torch, layers, x, y, lr):
+    flat = torch.from_numpy(ctx.pack(layers)).cuda()
+    ctx.local_steps(flat, x, y, [0, 1], 1, [1], lr, 1)
+    return ctx.unpack(flat.cpu().numpy())
+
+
+@pytest.mark.parametrize("tiling", ["L", "M", "S"])
+def test_wide_layers_sum_in_runs_of_1024(P, tiling):
+    """Forward (gathered and not) and backward-data of a layer of 65536 inputs
+    (outputs), whose values are read off one update or the loss exactly: all
+    factors around them are powers of two."""
+    import torch
+    say(f"wide sums, tiling {tiling}")
+    lr = 2.0 ** -20
+    dims = (WIDE, 8, 2)
+    ctx, y = _context(P, torch, dims)
+    try:
+        ctx.set_gemm_tiling(P.TILINGS[tiling])
+        layers = _weights(dims)
+        layers[0][0][3] = 1.0
+        layers[0][0][3, 0] = BIG
+        x = torch.ones((1, WIDE)).cuda()
+        true = BIG + WIDE - 1
+        # zero W_2: delta_2 = (1/2, -1/2), W_2 <- 0 - lr delta_2 a_1
+        a1 = float(_step(ctx, torch, layers, x, y, lr)[1][0][1, 3]) / (lr * 0.5)
+        assert abs(a1 - true) <= WIDE_BOUND, a1 - true
+        # logits (a_1, 0), label 1: the loss is a_1
+        layers[1][0][0, 3] = 1.0
+        loss, _ = ctx.evaluate(torch.from_numpy(ctx.pack(layers)).cuda(), x, y)
+        assert abs(loss - true) <= WIDE_BOUND, loss - true
+    finally:
+        ctx.close()
+    dims = (8, 8, WIDE)
+    ctx, y = _context(P, torch, dims)
+    try:
+        ctx.set_gemm_tiling(P.TILINGS[tiling])
+        # logits of at most 2^-33: the softmax is uniform, delta_2 = 2^-16 but
+        # for the label, whose weight is zero
+        layers = _weights(dims)
+        layers[0][1][5] = 2.0 ** -60
+        layers[1][0][:, 5] = 1.0
+        layers[1][0][0, 5] = BIG
+        layers[1][0][WIDE - 1, 5] = 0.0
+        x = torch.zeros((1, 8)).cuda()
+        x[0, 2] = 1.0
+        d1 = float(_step(ctx, torch, layers, x, y, lr)[0][0][5, 2]) / (-lr * 2.0 ** -16)
+        assert abs(d1 - (BIG + WIDE - 2)) <= WIDE_BOUND, d1 - (BIG + WIDE - 2)
+    finally:
+        ctx.close()
+
+
+@pytest.mark.parametrize("classes", [2, 17, 33])
+def test_wide_head_sums_in_runs_of_1024(P, classes):
+    """The fused head on 65536 inputs, its rows gathered (local steps), and
+    not (evaluation, and below a hidden layer)."""
+    import torch
+    say(f"wide head, {classes} classes")
+    true = BIG + WIDE - 1
+    dims = (WIDE, classes)
+    ctx, y = _context(P, torch, dims)
+    try:
+        layers = _weights(dims)
+        layers[0][0][0] = 1.0
+        layers[0][0][0, 0] = BIG
+        x = torch.ones((1, WIDE)).cuda()
+        flat = torch.from_numpy(ctx.pack(layers)).cuda()
+        loss, _ = ctx.evaluate(flat, x, y)  # the largest logit is all of the loss
+        assert abs(loss - true) <= WIDE_BOUND, loss - true
+        ctx.local_steps(flat, x, y, [0, 1], 1, [1], 2.0 ** -20, 1)
+        loss = float(ctx.round_losses()[0])
+        assert abs(loss - true) <= WIDE_BOUND, loss - true
+    finally:
+        ctx.close()
+    dims = (8, WIDE, classes)
+    ctx, y = _context(P, torch, dims)
+    try:
+        layers = _weights(dims)
+        layers[0][1][:] = 1.0  # activations of one
+        layers[1][0][0] = 1.0
+        layers[1][0][0, 0] = BIG
+        _step(ctx, torch, layers, torch.zeros((1, 8)).cuda(), y, 2.0 ** -20)
+        loss = float(ctx.round_losses()[0])
+        assert abs(loss - true) <= WIDE_BOUND, loss - true
+    finally:
+        ctx.close()
