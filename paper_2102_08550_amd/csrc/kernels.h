@@ -170,6 +170,8 @@ struct Bf16HeadArgs {
   int64_t loss_slot;
 };
 hipError_t launch_bf16_head(const GemmArgs& g, const Bf16HeadArgs& h, int n_slots, hipStream_t s);
+// Whether that launch is the faster one (else launch_gemm and launch_softmax_ce).
+bool bf16_head_pays(const GemmArgs& g, int n_slots);
 
 // wcopy[z][i] = bf16(master[order[z]][i]) for i < n, z < n_slots.
 hipError_t launch_cast_bf16(const float* master, int64_t master_slot, const int32_t* order,

@@ -2451,6 +2451,20 @@ hipError_t launch_bf16_head(const GemmArgs& g, const Bf16HeadArgs& h, int n_slot
   return hipGetLastError();
 }
 
+// The head's waves take one K chunk each at a time (eight, or four with more than
+// 32 classes): a longer K is a chain of such turns in one workgroup per 32 rows,
+// which split-K spreads over the CUs where the context holds its partials
+// (batches above 128).  Measured there, us per round of four steps, separate
+// launches and head, 64-K-classes: batch 160, one worker, 8192-10 (one turn) 252
+// and 223, 8192-64 (two) 258 and 287, 65536-64 (sixteen) 462 and 1261; batch 1024,
+// four workers, 4096-64 (one) 724 and 699, 16384-64 (four) 1353 and 1434.
+// Without partials the head wins at any K: batch 128, 65536-64 1920 and 1217.
+bool bf16_head_pays(const GemmArgs& g, int n_slots) {
+  if (g.M > BF16_HEAD_CLASSES) return false;
+  const int turn = g.M > 32 ? BH_WAVES / 2 : BH_WAVES;
+  return g.K <= turn * KCHUNK || !split_fits(g, n_slots);
+}
+
 hipError_t launch_softmax_ce(const float* logits, int64_t ld, int64_t slot_stride, int C, int B,
                              const int32_t* y, const int32_t* gather, int64_t gather_slot,
                              void* delta, bool delta_bf16, float* loss, int64_t loss_slot,

@@ -1202,9 +1202,6 @@ oscars_status run_local_steps(oscars_ctx* c, float* replicas, const float* start
 
   const int L = c->L;
   const int64_t rows_slot = static_cast<int64_t>(tau_max) * B;
-  // the last layer and the softmax in one launch (the first layer, whose launch
-  // keeps the gathered rows, is not the last one)
-  const bool fused_head = L > 1 && c->dims[L] <= BF16_HEAD_CLASSES && c->dims[L - 1] % 8 == 0;
   for (int j = 0; j < tau_max; ++j) {
     int ns = 0, ns_next = 0;
     while (ns < n_slots && tau[order[ns]] > j) ++ns;
@@ -1245,7 +1242,9 @@ oscars_status run_local_steps(oscars_ctx* c, float* replicas, const float* start
       g.part_cap = c->part_cap;
     };
 
-    // forward: C[o][b] = W_l . act_{l-1}
+    // forward: C[o][b] = W_l . act_{l-1}; the last layer (but not the first, whose
+    // launch keeps the gathered rows) with the softmax in one launch where that pays
+    bool head = false;
     for (int l = 1; l <= L; ++l) {
       GemmArgs g{};
       g.M = c->dims[l];
@@ -1280,7 +1279,8 @@ oscars_status run_local_steps(oscars_ctx* c, float* replicas, const float* start
       }
       g.out_ld = c->ld[l];
       g.out_slot = c->act_slot(l);
-      if (fused_head && l == L) {
+      head = l == L && L > 1 && bf16_head_pays(g, ns);
+      if (head) {
         Bf16HeadArgs h{};
         h.y = s->y;
         h.gather = rows_j;
@@ -1295,7 +1295,7 @@ oscars_status run_local_steps(oscars_ctx* c, float* replicas, const float* start
       if (e != hipSuccess) return hip_fail(e);
     }
     // loss gradient
-    if (!fused_head) e = timed(c, OSCARS_KERNEL_SOFTMAX, [&] {
+    if (!head) e = timed(c, OSCARS_KERNEL_SOFTMAX, [&] {
       return launch_softmax_ce(c->logits, c->ld[L], c->act_slot(L), c->dims[L], B, s->y, rows_j,
                                rows_slot, c->delta[L], c->bf16, c->loss_dev + static_cast<int64_t>(j) * B,
                                rows_slot, ns, c->stream);

@@ -212,3 +212,35 @@ def test_wide_head_sums_in_runs_of_1024(P, classes):
         assert abs(loss - true) <= WIDE_BOUND, loss - true
     finally:
         ctx.close()
+
+
+@pytest.mark.parametrize("dims,one_launch", [((24, 4096, 64), True), ((24, 4104, 64), False),
+                                             ((24, 8192, 10), True), ((24, 8200, 10), False)])
+def test_bf16_head_or_split_k_by_depth(P, dims, one_launch):
+    """With split-K partials in the context (batches above 128) a last layer
+    deeper than the head's one turn of K chunks takes the separate launches;
+    without, the head.  The same bits either way."""
+    import torch
+    say(f"bf16 head {dims}")
+    cfg = _mlp(dims, 40, (2, 1), 141, workload.BF16)
+    ds, init = workload.gen_dataset(cfg), workload.gen_init(cfg)
+    x = torch.from_numpy(np.ascontiguousarray(ds.x).view(np.int16)).cuda()
+    y = torch.from_numpy(ds.y.astype(np.int32)).cuda()
+    out = []
+    for max_batch in (cfg.batch, 256):
+        ctx = P.Context(cfg.dims, P.BF16, cfg.K, max_batch)
+        try:
+            flat = torch.from_numpy(np.tile(ctx.pack(init), cfg.K)).cuda()
+            ctx.profile_begin(range(len(P.KERNEL_NAMES)))
+            ctx.local_steps(flat, x, y, P.shard_offsets(cfg.n_rows, cfg.K), 5, cfg.tau_given, 0.05,
+                            cfg.batch)
+            launches = {k: n for k, (_, n) in ctx.profile_end().items()}
+            # two local steps: layer 1, and the last layer where it is not in the head
+            head = max_batch == cfg.batch or one_launch
+            assert launches["gemm_fwd"] == (2 if head else 4), launches
+            assert launches["softmax_ce"] == 2
+            out.append((flat.cpu().numpy(), ctx.round_losses()))
+        finally:
+            ctx.close()
+    assert np.array_equal(out[0][0].view(np.uint32), out[1][0].view(np.uint32))
+    assert np.array_equal(out[0][1], out[1][1])
