@@ -19,6 +19,7 @@
 // in row order.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <type_traits>
 
 #include "kernels.h"
@@ -426,11 +427,14 @@ __global__ __launch_bounds__(64 * HEAD_SLICES) void f32_head_kernel(F32HeadArgs 
 }
 
 // One wave's 16 T inputs x 16 T outputs of a layer: dW over the batch, then
-// the update.  `rows`: the addresses of the batch's dataset rows (GATHER).
-template <int T, bool GATHER>
+// the update.  `rows`: the addresses of the batch's dataset rows (GATHER).  BIAS:
+// the bias gradient too, from the deltas that the products have in registers:
+// each lane adds the rows of its own (4 q .. 4 q + 3 of 16, q its group of
+// 16 lanes), the four groups are added at the end, (0 + 1) + (2 + 3).
+template <int T, bool GATHER, bool BIAS>
 __device__ __forceinline__ void update_tile(const F32UpdateArgs& u, const F32UpdateLayer& y, int z,
                                             int rep, int m0, int n0, int lane,
-                                            const uint64_t* rows) {
+                                            const uint64_t* rows, float* lds) {
   const int c16 = lane & 15, gq = lane >> 4;
   // Four batch rows of 16 T columns per load.  Columns past M are other rows'
   // values (never stored); delta rows are padded to 64.
@@ -486,66 +490,98 @@ __device__ __forceinline__ void update_tile(const F32UpdateArgs& u, const F32Upd
 #pragma unroll
         for (int j = 0; j < T; ++j) acc[i][j] = mfma16(a[set][i][t], b[set][j][t], acc[i][j]);
   };
+  float db[T];
+#pragma unroll
+  for (int j = 0; j < T; ++j) db[j] = 0.0f;
+  auto add_bias = [&](int set) {
+    if constexpr (BIAS) {
+#pragma unroll
+      for (int t = 0; t < 4; ++t)
+#pragma unroll
+        for (int j = 0; j < T; ++j) db[j] += b[set][j][t];
+    }
+  };
   const int ns = (u.B + 15) / 16;
   load_index(0, 0);
   load_index(1, 1);
   load(0, 0);
-  // The weights, needed after the products only.  Lane (gq, c16) holds inputs
-  // m0 + 4 T gq .. + 4 T - 1 of outputs n0 + T c16 + j.
+  // The weights, needed after the products only: whole rows of the tile (4 T
+  // lanes of 16 bytes), the sums come to this layout through LDS.
   const float* win = u.master_in + static_cast<int64_t>(rep) * u.master_in_slot;
   float* wout = u.master + static_cast<int64_t>(rep) * u.master_slot;
-  const int mo = m0 + 4 * T * gq;
-  f32x4 w[T][T];
+  constexpr int CH = 4 * T, RPI = 64 / CH;  // 16-byte chunks per row, rows per load
+  const int wr = lane / CH, wc = lane % CH;
+  const bool col_in = m0 + 4 * wc < y.M;
+  f32x4 w[T * T];
 #pragma unroll
-  for (int j = 0; j < T; ++j) {
-    const int n = n0 + T * c16 + j < y.N ? n0 + T * c16 + j : 0;
-    const float* wrow = win + y.w_off + static_cast<int64_t>(n) * y.M;
-#pragma unroll
-    for (int qd = 0; qd < T; ++qd) {
-      const int m = mo + 4 * qd < y.M ? mo + 4 * qd : 0;
-      w[j][qd] = *reinterpret_cast<const f32x4*>(wrow + m);
-    }
+  for (int i = 0; i < T * T; ++i) {
+    const int n = n0 + RPI * i + wr;
+    w[i] = *reinterpret_cast<const f32x4*>(win + y.w_off + static_cast<int64_t>(n < y.N ? n : 0) * y.M +
+                                           (col_in ? m0 + 4 * wc : 0));
   }
   for (int s = 0; s < ns; s += 2) {
     load(1, s + 1);
     load_index(0, s + 2);
     loads_first();
     mma(0);
+    add_bias(0);
     loads_first();
     load(0, s + 2);
     load_index(1, s + 3);
     loads_first();
     mma(1);  // zeros past the batch
+    add_bias(1);
     loads_first();
   }
+  if constexpr (BIAS) {
 #pragma unroll
-  for (int j = 0; j < T; ++j) {
-    const int n = n0 + T * c16 + j;
-    const int64_t at = y.w_off + static_cast<int64_t>(n < y.N ? n : 0) * y.M;
-#pragma unroll
-    for (int qd = 0; qd < T; ++qd) {
-      const f32x4 d = acc_quad<true>(acc, j, qd);
-#pragma unroll
-      for (int e = 0; e < 4; ++e) w[j][qd][e] = fmaf(-u.lr, d[e], w[j][qd][e]);
-      if (n < y.N && mo + 4 * qd < y.M)
-        *reinterpret_cast<f32x4*>(wout + at + mo + 4 * qd) = w[j][qd];
+    for (int j = 0; j < T; ++j) {
+      db[j] += __shfl_xor(db[j], 16);
+      db[j] += __shfl_xor(db[j], 32);
+      const int n = n0 + T * c16 + j;
+      if (gq == 0 && n < y.N) wout[y.b_off + n] = fmaf(-u.lr, db[j], win[y.b_off + n]);
     }
+  }
+  // Chunk c of row r at c ^ (r / T) (no bank conflicts either way); LDS
+  // operations of one wave execute in order, no barrier.
+#pragma unroll
+  for (int j = 0; j < T; ++j)
+#pragma unroll
+    for (int qd = 0; qd < T; ++qd)
+      *reinterpret_cast<f32x4*>(lds + (T * c16 + j) * 4 * CH + 4 * ((T * gq + qd) ^ (c16 & (CH - 1)))) =
+          acc_quad<true>(acc, j, qd);
+  __builtin_amdgcn_wave_barrier();
+#pragma unroll
+  for (int i = 0; i < T * T; ++i) {
+    const int r = RPI * i + wr, n = n0 + r;
+    const f32x4 d = *reinterpret_cast<const f32x4*>(lds + r * 4 * CH + 4 * (wc ^ (r / T & (CH - 1))));
+#pragma unroll
+    for (int e = 0; e < 4; ++e) w[i][e] = fmaf(-u.lr, d[e], w[i][e]);
+    if (n < y.N && col_in)
+      *reinterpret_cast<f32x4*>(wout + y.w_off + static_cast<int64_t>(n) * y.M + m0 + 4 * wc) = w[i];
   }
 }
 
 // Backward-weight and the SGD update of every layer in one launch (nothing
 // reads the weights after the last backward-data launch).  A workgroup of 2 x
 // 2 waves covers 32 T inputs x 32 T outputs of one layer, a wave 16 T x 16 T:
-// dW[o][i] over the batch, then W <- W - lr dW.  The biases have workgroups of
-// their own (64 outputs each): blocks of 64 batch rows row by row, the block
-// sums left to right.
-constexpr int UPDATE_ROWS = 1024 + 80;  // largest batch and the groups read ahead
-template <int T>
-__global__ __launch_bounds__(256, T == 4 ? 1 : 2) void f32_update_kernel(F32UpdateArgs u) {
+// dW[o][i] over the batch, then W <- W - lr dW; the waves of input 0 update the
+// biases too.  ALONE: registers for one wave per SIMD only.  What bounds it is
+// the fp32 products where a wave's tile is 64 x 64 (1024-2048-2048-10, batch 512: 79
+// us, 82 TFLOP/s in two uneven passes over the CUs), and the weights, read and
+// written once, at short batches (4096-4096-4096-4096-1000, two replicas, batch 256:
+// 543 us).  Biases in workgroups of their own read every delta once more
+// and held a CU each: 784-4000 at one replica, batch 1012 134 against 75 us,
+// 256-4000 at 35, batch 128 179 against 137; 16-byte pieces of the weights, as the
+// products leave them, instead of whole rows: 2048-2048-10 at 8, batch 128 119
+// against 115, 4096-wide 576 against 543.
+constexpr int UPDATE_ROWS = 1024 + 48;  // largest batch and the groups read ahead
+template <int T, bool ALONE>
+__global__ __launch_bounds__(256, ALONE ? 1 : 2) void f32_update_kernel(F32UpdateArgs u) {
   // Addresses of the gathered activations' rows at the workgroup's first column
   // (zeros past the batch): one addition per load.
   __shared__ __attribute__((aligned(16))) uint64_t rows[UPDATE_ROWS];
-  __shared__ float bias_sum[16][64];  // of the blocks of 64 batch rows
+  __shared__ __attribute__((aligned(16))) float sums[4][256 * T * T];  // each wave's own
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
   const int work = xcd_item(blockIdx.y * gridDim.x + blockIdx.x, gridDim.x * gridDim.y);
@@ -561,47 +597,23 @@ __global__ __launch_bounds__(256, T == 4 ? 1 : 2) void f32_update_kernel(F32Upda
   const int m0 = (tile % gm * 2 + (wave & 1)) * 16 * T;
   const int n0 = (tile / gm * 2 + (wave >> 1)) * 16 * T;
   const bool gathered = l == 0 && u.gather != nullptr;
-  if (tile >= y.tiles) {  // the biases of 64 outputs
-    const int n = (tile - y.tiles) * 64 + lane, blocks = (u.B + 63) / 64;
-    const float* D = y.d + z * y.d_slot;
-    for (int b = wave; b < blocks; b += 4) {
-      float sum = 0.0f;
-      for (int k = 64 * b; k < 64 * b + 64; k += 16) {
-        float v[16];
-        const int in = max(min(u.B - k, 16), 0);  // rows padded to 64; zeros past the batch
-        const Buf rows16 = buffer(D + static_cast<int64_t>(min(k, u.B)) * y.d_ld, in * y.d_ld * 4);
-#pragma unroll
-        for (int e = 0; e < 16; ++e)
-          v[e] = load_buffer<1>(rows16, 4u * n, 4u * min(e, in) * static_cast<uint32_t>(y.d_ld));
-#pragma unroll
-        for (int e = 0; e < 16; ++e) sum += v[e];
-      }
-      bias_sum[b][lane] = sum;
-    }
-    __syncthreads();
-    if (wave == 0 && n < y.N) {
-      float db = bias_sum[0][lane];
-      for (int b = 1; b < blocks; ++b) db += bias_sum[b][lane];
-      const int64_t at = static_cast<int64_t>(rep) * u.master_slot + y.b_off + n;
-      u.master[at] = fmaf(-u.lr, db, u.master_in[static_cast<int64_t>(rep) * u.master_in_slot +
-                                                 y.b_off + n]);
-    }
-    return;
-  }
   if (gathered) {
     const uint64_t base = reinterpret_cast<uint64_t>(y.a + z * y.a_slot + (m0 & ~(32 * T - 1)));
     const uint64_t zero = reinterpret_cast<uint64_t>(f32_zero_words);
-    for (int b = threadIdx.x; b < UPDATE_ROWS; b += 256)
+    const int end = (u.B + 15) / 16 * 16 + 48;  // and the groups read ahead
+    for (int b = threadIdx.x; b < end; b += 256)
       rows[b] = b < u.B ? base + 4 * offset_of(u.gather[z * u.gather_slot + b], y.a_ld) : zero;
     __syncthreads();
   }
   if (m0 >= y.M || n0 >= y.N) return;
-  // The larger tile keeps a SIMD's products busy alone, and two such waves on
-  // one SIMD slowed each other (dense activations: 100 us for a pair of tiles, 39
-  // for one): these registers leave room for one.
-  if constexpr (T == 4) asm volatile("" ::: "a255");
-  if (gathered) update_tile<T, true>(u, y, z, rep, m0, n0, lane, rows);
-  else update_tile<T, false>(u, y, z, rep, m0, n0, lane, rows);
+  if constexpr (ALONE) asm volatile("" ::: "a255");
+  if (gathered) {
+    if (m0 == 0) update_tile<T, true, true>(u, y, z, rep, m0, n0, lane, rows, sums[wave]);
+    else update_tile<T, true, false>(u, y, z, rep, m0, n0, lane, rows, sums[wave]);
+  } else {
+    if (m0 == 0) update_tile<T, false, true>(u, y, z, rep, m0, n0, lane, rows, sums[wave]);
+    else update_tile<T, false, false>(u, y, z, rep, m0, n0, lane, rows, sums[wave]);
+  }
 }
 
 template <int MODE, int MI, int NJ, bool FOLD>
@@ -671,31 +683,38 @@ hipError_t launch_f32_update(const F32UpdateArgs& u_in, int n_slots, hipStream_t
   auto groups = [&](int t) {
     int64_t n = 0;
     for (int l = 0; l < u.n_layers; ++l) {
-      F32UpdateLayer& y = u.layer[l];
-      const int64_t tiles =
-          static_cast<int64_t>((y.M + 32 * t - 1) / (32 * t)) * ((y.N + 32 * t - 1) / (32 * t));
+      const F32UpdateLayer& y = u.layer[l];
       u.first_wg[l] = static_cast<int>(n);
-      y.tiles = static_cast<int>(tiles);
-      n += tiles + (y.N + 63) / 64;
+      n += static_cast<int64_t>((y.M + 32 * t - 1) / (32 * t)) * ((y.N + 32 * t - 1) / (32 * t));
     }
     return n;
   };
-  // 64 x 64 per wave, or 32 x 32, whose 8-byte loads take twice the L1 accesses
-  // per byte but whose waves are four times as many and start up sooner.
-  // Measured: 784-512-256-10, batch 64, 8 replicas (304 workgroups of the
-  // larger tile) 22.8 against 17.9 us; 1024-2048-2048-10, batch 512, 1 replica
-  // (465 workgroups) 82 against 102 us.
   for (int l = u.n_layers; l < F32_UPDATE_LAYERS; ++l) u.first_wg[l] = 0x7FFFFFFF;
-  int t = 4;
-  int64_t gx = groups(4);
-  if (u.B < 128 || gx * n_slots < 256) {
-    t = 2;
-    gx = groups(2);
-  }
-  if (gx * n_slots > 0x7FFFFFFF) return hipErrorInvalidValue;
+  // Waves of 64 x 64 outputs, or of 32 x 32, whose 8-byte loads take twice the
+  // L1 accesses per byte but whose waves are four times as many, start up sooner
+  // and waste less of narrow layers.  Their times (us) fitted over 76 models of
+  // 10 to 4096 wide layers, 1 to 44 replicas and batches 8 to 1024 (rms 13 and 9%;
+  // the faster one is missed by 1% on average): a start, the weights per
+  // workgroup, and per batch row one wave's products or all workgroups'.  Both
+  // sides, 32 x 32 and 64 x 64: 784-512-256-10 at 8 replicas, batch 64 19 and 22,
+  // batch 512 77 and 76; 456-100 at 10, batch 855 25 and 62; 1024-2048-2048-10 at
+  // one, batch 512 121 and 79; 784-4000 at one, batch 1012 132 and 75.
+  const int64_t g4 = groups(4) * n_slots, g2 = groups(2) * n_slots;
+  const float t2 = 8.0f + 4e-3f * g2 + u.B * std::max(0.02f, 1.15e-4f * g2);
+  const float t4 = 9.0f + 0.024f * g4 + u.B * std::max(0.06f, 2.65e-4f * g4);
+  const int64_t gx = groups(t2 < t4 ? 2 : 4);
+  // Two waves of the larger tile on one SIMD slow each other's products (dense
+  // activations: 100 us for a pair of tiles, 39 for one) but hide each other's
+  // start and weights, which is more with short batches and several tiles per
+  // CU.  Alone and in pairs: 2048-2048-10 at 8 replicas (2176 workgroups), batch
+  // 128 127 and 115, 200 176 and 172, 320 230 and 235, 512 331 and 359;
+  // 256-4000, batch 128, at 35 (2240) 146 and 137, at 8 (512) 38 and 41.
+  const bool alone = u.B >= 176 || g4 < 1024;
+  if (g2 > 0x7FFFFFFF) return hipErrorInvalidValue;
   const dim3 grid(static_cast<unsigned>(gx), n_slots), block(256);
-  if (t == 4) hipLaunchKernelGGL(f32_update_kernel<4>, grid, block, 0, s, u);
-  else hipLaunchKernelGGL(f32_update_kernel<2>, grid, block, 0, s, u);
+  if (t2 < t4) hipLaunchKernelGGL((f32_update_kernel<2, false>), grid, block, 0, s, u);
+  else if (alone) hipLaunchKernelGGL((f32_update_kernel<4, true>), grid, block, 0, s, u);
+  else hipLaunchKernelGGL((f32_update_kernel<4, false>), grid, block, 0, s, u);
   return hipGetLastError();
 }
 

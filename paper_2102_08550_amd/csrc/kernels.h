@@ -219,7 +219,6 @@ struct F32UpdateLayer {
   const float* d;  // delta [B][d_ld], rows padded to 64
   int64_t d_ld, d_slot;
   int64_t w_off, b_off;
-  int tiles;  // weight tiles (set by the launcher)
 };
 struct F32UpdateArgs {
   int first_wg[F32_UPDATE_LAYERS];  // of each layer (set by the launcher)

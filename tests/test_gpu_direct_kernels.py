@@ -54,6 +54,8 @@ CASES = {
     "classes-65": _mlp((72, 104, 65), 33, (2, 1), 105),
     "softmax": _mlp((792, 10), 65, (3, 0, 2), 106),
     "update-64": _mlp((1032, 2056, 10), 130, (1, 2, 1), 107),
+    "update-pairs": _mlp((1032, 2056, 10), 130, (1,) * 7, 109),
+    "update-alone": _mlp((1032, 2056, 10), 200, (1, 1, 1), 110),
     "update-last": _mlp((2056, 1544, 136), 128, (2,), 108),
     "bf16-head-32": _mlp((16, 24, 32), 1, (2, 1), 131, workload.BF16),
     "bf16-head-33": _mlp((40, 1032, 33), 33, (2, 1), 132, workload.BF16),
@@ -244,3 +246,29 @@ def test_bf16_head_or_split_k_by_depth(P, dims, one_launch):
             ctx.close()
     assert np.array_equal(out[0][0].view(np.uint32), out[1][0].view(np.uint32))
     assert np.array_equal(out[0][1], out[1][1])
+
+
+@pytest.mark.parametrize("batch", [130, 200])
+def test_update_tiles_give_the_same_bits(P, batch):
+    """Seven replicas take 64 x 64 update tiles, two waves per SIMD (batch 130) or
+    one (200), a single one 32 x 32 tiles: a replica's bits are the same."""
+    import torch
+    say(f"update tiles, batch {batch}")
+    cfg = _mlp((1032, 2056, 10), batch, (1,) * 7, 142)
+    ds, init = workload.gen_dataset(cfg), workload.gen_init(cfg)
+    x, y = torch.from_numpy(ds.x).cuda(), torch.from_numpy(ds.y.astype(np.int32)).cuda()
+    off = P.shard_offsets(cfg.n_rows, cfg.K)
+    ctx = P.Context(cfg.dims, P.FP32, cfg.K, batch)
+    try:
+        start = torch.from_numpy(np.tile(ctx.pack(init), cfg.K)).cuda()
+        flat = start.clone()
+        ctx.local_steps(flat, x, y, off, 5, [1] * 7, 0.05, batch)
+        for k in (0, 6):
+            solo = start.clone()
+            ctx.set_cursors([0] * 7)
+            ctx.local_steps(solo, x, y, off, 5, [int(j == k) for j in range(7)], 0.05, batch)
+            n = ctx.n_pad
+            assert torch.equal(solo[k * n:(k + 1) * n].view(torch.int32),
+                               flat[k * n:(k + 1) * n].view(torch.int32)), k
+    finally:
+        ctx.close()
