@@ -108,7 +108,8 @@ typedef struct {
  * layer, fp32 + bf16; left out where they would take
  * more than a quarter of the free device memory, and then nothing is timed);
  * and, where those activations hold fewer rows, up to 96 MiB of activations
- * for the passes of oscars_evaluate.
+ * for the passes of oscars_evaluate (left out where they do not fit: the
+ * passes are then shorter).
  * `hip_stream` (a hipStream_t, NULL = null stream) is the stream
  * oscars_local_steps enqueues on.  The context owns its tuning state (GEMM
  * tilings, backward path): contexts do not share it. */

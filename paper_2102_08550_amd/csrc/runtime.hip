@@ -179,28 +179,36 @@ void free_ctx(oscars_ctx* c) {
 // Evaluation forward passes take as many rows as they can: the launches of a
 // pass cost their latency whatever its rows.  An evaluation of an MLP runs
 // kEvalRows rows per pass in up to kEvalBytes of buffers of its own where the
-// local steps' activations (K * max_batch rows) hold fewer.
+// local steps' activations (K * max_batch rows) hold fewer, or, where there is
+// no room for them, those rows.
 constexpr int64_t kEvalRows = 8192;
 constexpr int64_t kEvalBytes = int64_t{96} << 20;
+
+// Whether an MLP's last layer and its softmax are one fp32 launch.
+bool f32_head(const oscars_ctx* c) { return !c->bf16 && c->dims[c->L] <= F32_HEAD_CLASSES; }
 
 hipError_t alloc_eval(oscars_ctx* c) {
   const int64_t have = static_cast<int64_t>(c->K) * c->max_batch;
   int64_t ld = 64;
   for (int l = 1; l < c->L; ++l) ld = std::max(ld, c->ld[l]);
-  const int64_t act = ld * static_cast<int64_t>(c->esize), logits = c->ld[c->L] * 4;
-  c->eval_rows = std::min(kEvalRows, kEvalBytes / (2 * act + logits));
-  if (c->eval_rows <= have) {
-    c->eval_rows = have;
+  const int64_t act = ld * static_cast<int64_t>(c->esize);
+  const int64_t logits = f32_head(c) ? 0 : c->ld[c->L] * 4;
+  const int64_t rows = std::min(kEvalRows, kEvalBytes / (2 * act + logits));
+  c->eval_rows = have;
+  if (rows <= have) return hipSuccess;
+  void* p = nullptr;
+  const hipError_t e = hipMalloc(&p, static_cast<size_t>(rows * (2 * act + logits)));
+  if (e == hipErrorOutOfMemory) {
+    (void)hipGetLastError();
     return hipSuccess;
   }
-  void* p = nullptr;
-  const hipError_t e = hipMalloc(&p, static_cast<size_t>(c->eval_rows * (2 * act + logits)));
   if (e != hipSuccess) return e;
   c->allocs.push_back(p);
+  c->eval_rows = rows;
   char* base = static_cast<char*>(p);
   c->eval_act[0] = base;
-  c->eval_act[1] = base + c->eval_rows * act;
-  c->eval_logits = reinterpret_cast<float*>(base + 2 * c->eval_rows * act);
+  c->eval_act[1] = base + rows * act;
+  c->eval_logits = reinterpret_cast<float*>(base + 2 * rows * act);
   return hipSuccess;
 }
 
@@ -970,7 +978,7 @@ hipError_t f32_step(oscars_ctx* c, float* replicas, const float* master_in, int6
                     int64_t rows_slot, int B, int ns, float lr, float* loss) {
   const int L = c->L;
   hipError_t e = hipSuccess;
-  const bool head = c->dims[L] <= F32_HEAD_CLASSES;
+  const bool head = f32_head(c);
   auto fact = [&](int l) { return static_cast<float*>(c->act[l]); };
   auto fdelta = [&](int l) { return static_cast<float*>(c->delta[l]); };
   for (int l = 1; l <= (head ? L - 1 : L) && e == hipSuccess; ++l) {
@@ -1512,7 +1520,7 @@ hipError_t run_evaluate(oscars_ctx* c, const float* params, const void* x, const
     const bool own = c->eval_act[0] != nullptr;
     auto act = [&](int l) { return own ? c->eval_act[l & 1] : c->act[l]; };
     float* logits = own ? c->eval_logits : c->logits;
-    const bool head = !c->bf16 && c->dims[L] <= F32_HEAD_CLASSES;
+    const bool head = f32_head(c);
     // passes of equal size (whole 256-row tiles): a short last one would leave
     // most of the CUs idle for as long as a full one
     const int64_t passes = (n_rows + c->eval_rows - 1) / c->eval_rows;

@@ -108,6 +108,39 @@ def test_evaluation_passes_match_oracle(P, rows):
         ctx.close()
 
 
+def test_context_without_room_for_evaluation_buffers(P):
+    """A context is created where the 64 MiB for wide evaluation passes no
+    longer fit, and evaluates in passes of its local steps' rows."""
+    import torch
+    say("evaluation without buffers of its own")
+    cfg = _mlp((16, 1024, 17), 16, (1, 1), 151)
+    init = workload.gen_init(cfg)
+    ev = workload.gen_eval_set(cfg, 100)
+    args = (torch.from_numpy(ev.x).cuda(), torch.from_numpy(ev.y.astype(np.int32)).cuda())
+    ctx = P.Context(cfg.dims, P.FP32, cfg.K, cfg.batch)
+    flat = torch.from_numpy(ctx.pack(init)).cuda()
+    ref = ctx.evaluate(flat, *args)
+    ctx.close()
+    ballast = []
+    for size in (1 << 32, 1 << 28, 1 << 24):  # until not even 16 MiB are free
+        try:
+            while True:
+                ballast.append(torch.empty(size, dtype=torch.uint8, device="cuda"))
+        except torch.OutOfMemoryError:
+            pass
+    del ballast[-2:]  # 32 MiB for the rest of the context
+    torch.cuda.empty_cache()
+    try:
+        ctx = P.Context(cfg.dims, P.FP32, cfg.K, cfg.batch)
+    finally:
+        del ballast
+        torch.cuda.empty_cache()
+    try:
+        assert ctx.evaluate(flat, *args) == ref
+    finally:
+        ctx.close()
+
+
 WIDE = 65536  # the widest accepted layer
 BIG = 2.0 ** 27
 # A product of 2^27 followed by ones: a running sum that has reached 2^27 (ulp 16)
