@@ -1225,12 +1225,16 @@ void conv_wgrad_ranges(const ConvArgs& a, int* splits, int64_t* k_per_split) {
   *splits = static_cast<int>((pixels + *k_per_split - 1) / *k_per_split);
 }
 
-int conv_wgrad_max_splits(const ConvArgs& a) {
-  int splits = 0;
-  int64_t per = 0;
-  conv_wgrad_ranges(a, &splits, &per);
-  // conv_direct_range shortens the ranges of a smaller batch: up to 32 of them
-  return conv_direct(a) && !thin_wgrad(a) && splits < 32 ? 32 : splits;
+int conv_wgrad_max_splits(const ConvArgs& a_in) {
+  ConvArgs a = a_in;
+  int most = 0;
+  for (a.B = 1; a.B <= a_in.B; ++a.B) {  // smaller batches have shorter ranges
+    int splits = 0;
+    int64_t per = 0;
+    conv_wgrad_ranges(a, &splits, &per);
+    if (splits > most) most = splits;
+  }
+  return most;
 }
 
 }  // namespace oscars

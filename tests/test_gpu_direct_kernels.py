@@ -66,6 +66,7 @@ CASES = {
     "taps-cross": _cnn((7, 9, 3), ((20, 1), (12, 1), (36, 2)), 7, (1, 2), 113),
     "blocks-3": _cnn((11, 13, 3), ((48, 1), (68, 2), (68, 1), (68, 1, 1)), 4, (2, 1), 114),
     "ranges": _cnn((20, 20, 3), ((16, 1), (32, 1), (64, 2)), 12, (1, 2), 115),
+    "ranges-wide": _cnn((8, 8, 3), ((384, 1), (392, 1), (384, 2)), 9, (1, 2), 118),
     "many-slots": _cnn((16, 16, 3), ((32, 1), (64, 2), (64, 1, 0)), 16, (1, 1, 1, 1, 1), 116),
 }
 
@@ -139,6 +140,39 @@ def test_context_without_room_for_evaluation_buffers(P):
         assert ctx.evaluate(flat, *args) == ref
     finally:
         ctx.close()
+
+
+def test_weight_gradient_partials_fit_the_pixels(P):
+    """A context holds the partials of the ranges that its batches have, not of
+    a fixed number: one copy of the weights for 128 pixels, and a batch of fewer
+    pixels than max_batch's may have more ranges (63 against 64 images here)."""
+    import torch
+    say("weight-gradient partials")
+    image, conv = (4, 4, 8), ((1024, 1), (1024, 1))
+    K, batch = 2, 8
+    torch.cuda.synchronize()
+    free = torch.cuda.mem_get_info()[0]
+    ctx = P.Context((128, 10), P.FP32, K, batch, cnn=(image, conv))
+    try:
+        used = free - torch.cuda.mem_get_info()[0]
+        partials = K * 4 * ctx.n_pad
+        activations = K * batch * 16 * 2 * 2 * 1024 * 4
+        assert used <= partials + activations + (64 << 20), (used, partials, activations)
+    finally:
+        ctx.close()
+    cfg = _cnn((8, 8, 4), ((16, 1), (32, 1)), 63, (2, 1), 152)
+    ds, init = workload.gen_dataset(cfg), workload.gen_init(cfg)
+    x, y = torch.from_numpy(ds.x).cuda(), torch.from_numpy(ds.y.astype(np.int32)).cuda()
+    out = []
+    for max_batch in (63, 64):
+        ctx = P.Context((256, 10), P.FP32, cfg.K, max_batch, cnn=(cfg.image, cfg.conv))
+        try:
+            flat = torch.from_numpy(np.tile(ctx.pack(init), cfg.K)).cuda()
+            ctx.local_steps(flat, x, y, P.shard_offsets(cfg.n_rows, cfg.K), 5, cfg.tau_given, 0.1, 63)
+            out.append(flat.cpu())
+        finally:
+            ctx.close()
+    assert torch.equal(out[0].view(torch.int32), out[1].view(torch.int32))
 
 
 WIDE = 65536  # the widest accepted layer
