@@ -69,7 +69,27 @@ struct Divisor {
     return q;
   }
 };
-constexpr int IMAGE_PIXELS = 1 << 20;  // per image: a tile's or range's pixels stay below 2^21
+
+// Positions of the pixels of a tile or range, counted from its first pixel n0
+// (uniform): along the row, then down the image, so that each quotient is of a
+// number below 2^21 (images have at most 4096 rows and columns) however many
+// pixels an image has.
+struct PixelWalk {
+  int img0, i0, j0;  // of the first pixel
+  Divisor by_col, by_row;
+  __device__ PixelWalk(int n0, int rows, int cols) : by_col(cols), by_row(rows) {
+    const int hw = rows * cols;
+    img0 = n0 / hw;
+    const int n = n0 - img0 * hw;
+    i0 = __builtin_amdgcn_readfirstlane(n / cols);
+    j0 = n - i0 * cols;
+  }
+  // image of pixel n0 + p, row i and column j in it
+  __device__ int operator()(int p, int& i, int& j) const {
+    const int down = by_col(j0 + p, j);
+    return img0 + by_row(i0 + down, i);
+  }
+};
 
 // The 3 x 3 taps (bit 3 r + s) around (h, w) that lie inside an H x W image;
 // (h, w) itself does.
@@ -109,11 +129,8 @@ __device__ __forceinline__ void conv_pixels_tile(const ConvArgs& a, int cls, int
 
   // Offsets are from the row of the tile's first pixel, moved back by a row and
   // a pixel (taps reach that far; a class's taps do not), so none is negative.
-  const int img0 = n0 / (rows * cols), n_img = n0 - img0 * rows * cols;
-  const Divisor by_image(rows * cols), by_row(cols);
-  int j0;
-  const int i0 = __builtin_amdgcn_readfirstlane(by_row(n_img, j0));
-  const int64_t base = (static_cast<int64_t>(img0) * PH + st * i0) * PW * D;
+  const PixelWalk walk(n0, rows, cols);
+  const int64_t base = (static_cast<int64_t>(walk.img0) * PH + st * walk.i0) * PW * D;
   const int back = cls < 0 ? (PW + 1) * D : 0;
   const Buf px = buffer(src + base - back, 0x7FFFFFFF);
   uint32_t at[NJ];    // byte offset of the tap at the centre (UNI: and this lane's channels)
@@ -122,8 +139,8 @@ __device__ __forceinline__ void conv_pixels_tile(const ConvArgs& a, int cls, int
 #pragma unroll
   for (int j = 0; j < NJ; ++j) {
     const int n = n0 + 16 * j + load_row(lane), nc = min(n, N - 1);
-    int p, pj;
-    const int img = img0 + by_image(nc - n0 + n_img, p), pi = by_row(p, pj);
+    int pi, pj;
+    const int img = walk(nc - n0, pi, pj);
     uint32_t ok = 0;
     if (cls < 0) {
       ok = taps_inside(st * pi, st * pj, PH, PW);
@@ -307,8 +324,8 @@ __device__ __forceinline__ void conv_pixels_tile(const ConvArgs& a, int cls, int
     const int n = n0 + 16 * j + c16, nc = n < N ? n : N - 1;
     int out = nc * M;
     if (!FWD && cls >= 0) {
-      int p, pj;
-      const int img = img0 + by_image(nc - n0 + n_img, p), pi = by_row(p, pj);
+      int pi, pj;
+      const int img = walk(nc - n0, pi, pj);
       out = ((img * a.H + 2 * pi + oddr) * a.W + 2 * pj + oddc) * a.C;
     }
     f32x4 v[MI], x[MI], y[MI];
@@ -386,19 +403,16 @@ __device__ __forceinline__ void conv_weights_tile(const ConvArgs& a, int tile, i
   const int C9 = 9 * a.C, gm = (C9 + 63) / 64, go = (a.Co + 16 * NJ - 1) / (16 * NJ);
   const int split = tile / (gm * go), rest = tile - split * gm * go;
   const int m0 = rest % gm * 64, o0 = rest / gm * 16 * NJ;
-  const int K = a.B * a.Ho * a.Wo, R = static_cast<int>(a.k_per_split), hw = a.Ho * a.Wo;
+  const int K = a.B * a.Ho * a.Wo, R = static_cast<int>(a.k_per_split);
   const int kbeg = split * R, kend = min(K, kbeg + R);
   // Offsets from the input row of the range's first pixel, moved back as in
   // conv_pixels_tile.
-  const int img0 = kbeg / hw, k_img = kbeg - img0 * hw;
-  const Divisor by_image(hw), by_row(a.Wo);
-  int j0;
-  const int i0 = __builtin_amdgcn_readfirstlane(by_row(k_img, j0));
-  const int64_t base = (static_cast<int64_t>(img0) * a.H + a.stride * i0) * a.W * a.C;
+  const PixelWalk walk(kbeg, a.Ho, a.Wo);
+  const int64_t base = (static_cast<int64_t>(walk.img0) * a.H + a.stride * walk.i0) * a.W * a.C;
   const int back = (a.W + 1) * a.C;
   for (int p = threadIdx.x; p < R + 64; p += 64 * BWD_WAVES) {
-    int q, j;
-    const int img = img0 + by_image(min(p, K - 1 - kbeg) + k_img, q), i = by_row(q, j);
+    int i, j;
+    const int img = walk(min(p, K - 1 - kbeg), i, j);
     const int hi = a.stride * i, wi = a.stride * j;
     uint32_t ok = taps_inside(hi, wi, a.H, a.W);
     if (kbeg + p >= kend) ok = 0;
@@ -639,14 +653,14 @@ void wgrad_launch(const dim3& grid, hipStream_t s, const ConvArgs& w) {
 
 }  // namespace
 
-// Sizes within the 31-bit offsets of a tile (up to 1024 pixels from the row of
-// its first) and of one layer's weights; larger layers take the general
-// gathers.
+// Byte offsets below 2^31: those of a tile from its first pixel's row (the taps of
+// 1024 output pixels of W-wide images, stride 2, span at most 4096 + 5 W pixels,
+// of at most 65536 channels), and those in a layer's weights where a K group is
+// not one tap's (backward-data, output channels no multiple of 16).
 bool conv_direct(const ConvArgs& a) {
   return (a.C & 3) == 0 && (a.Co & 3) == 0 && a.C >= 4 &&
-         static_cast<int64_t>(a.H) * a.W <= IMAGE_PIXELS &&
-         static_cast<int64_t>(a.W) * a.C <= (1 << 24) && static_cast<int64_t>(a.Wo) * a.Co <= (1 << 24) &&
-         9LL * a.C * a.Co < (1 << 28);
+         static_cast<int64_t>(a.W) * a.C <= (1 << 25) && static_cast<int64_t>(a.Wo) * a.Co <= (1 << 25) &&
+         (a.Co % 16 == 0 || 9LL * a.C * a.Co < (1 << 29));
 }
 
 int conv_direct_range(const ConvArgs& a) {

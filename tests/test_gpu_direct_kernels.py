@@ -67,6 +67,8 @@ CASES = {
     "blocks-3": _cnn((11, 13, 3), ((48, 1), (68, 2), (68, 1), (68, 1, 1)), 4, (2, 1), 114),
     "ranges": _cnn((20, 20, 3), ((16, 1), (32, 1), (64, 2)), 12, (1, 2), 115),
     "ranges-wide": _cnn((8, 8, 3), ((384, 1), (392, 1), (384, 2)), 9, (1, 2), 118),
+    "image-1030x1020": _cnn((1030, 1020, 4), ((4, 1), (8, 2)), 1, (1,), 117),
+    "image-4096x2": _cnn((4096, 2, 4), ((12, 1), (16, 2), (16, 1)), 2, (1, 2), 119),
     "many-slots": _cnn((16, 16, 3), ((32, 1), (64, 2), (64, 1, 0)), 16, (1, 1, 1, 1, 1), 116),
 }
 
@@ -173,6 +175,25 @@ def test_weight_gradient_partials_fit_the_pixels(P):
         finally:
             ctx.close()
     assert torch.equal(out[0].view(torch.int32), out[1].view(torch.int32))
+
+
+def test_large_images_take_the_paired_backward(P):
+    """Layers whose channel counts are multiples of 4 run backward-data and
+    backward-weight in one launch whatever the size of their images."""
+    import torch
+    image, conv = (1030, 1020, 4), ((4, 1), (8, 2))
+    say(f"paired backward, image {image}")
+    d = image[0] * image[1] * image[2]
+    ctx = P.Context((d, 10), P.FP32, 1, 1, cnn=(image, conv))
+    try:
+        flat = torch.zeros(ctx.n_pad).cuda()
+        ctx.profile_begin(range(len(P.KERNEL_NAMES)))
+        ctx.local_steps(flat, torch.ones((2, d)).cuda(), torch.zeros(2, dtype=torch.int32).cuda(),
+                        [0, 2], 1, [1], 0.1, 1)
+        launches = {k: n for k, (_, n) in ctx.profile_end().items()}
+        assert launches["gemm_bwd_fused"] == 1, launches  # layer 2
+    finally:
+        ctx.close()
 
 
 WIDE = 65536  # the widest accepted layer
