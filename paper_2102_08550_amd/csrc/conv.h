@@ -60,9 +60,9 @@ struct ConvArgs {
 hipError_t launch_conv(const ConvArgs& a, ConvPass pass, int n_slots, hipStream_t s);
 
 // Convolutions whose channel counts are multiples of 4 (conv_direct.hip):
-// forward, and backward-weight of w with (d != nullptr) backward-data of d in
-// one launch.  Weight-gradient partials are packed: per range [Co][9 C], then
-// the [Co] bias gradients.
+// forward, and backward-weight of w with backward-data of d in one launch, or
+// (d == nullptr) alone, of a first layer with gathered rows.  Weight-gradient
+// partials are packed: per range [Co][9 C], then the [Co] bias gradients.
 bool conv_direct(const ConvArgs& a);
 int conv_direct_range(const ConvArgs& a);  // output pixels per weight-gradient range
 hipError_t launch_conv_direct_fwd(const ConvArgs& a, int n_slots, hipStream_t s);

@@ -498,15 +498,13 @@ __device__ __forceinline__ void conv_weights_tile(const ConvArgs& a, int tile, i
 #pragma unroll
       for (int j = 0; j < NJ; ++j) db[j] += f.b[j][t];
   };
-  // whole groups of the wave's own part (R / 8 is a multiple of 16), an odd
-  // last one alone
+  // the wave's own part: whole pairs of groups (R is a multiple of 128)
   const int ng = part_len / 16;
   constexpr int RD = 2;  // LDS reads of four table entries
   look(e0, 0);
   look(e1, 1);
   load(f0, e0, 0);
-  int s = 0;
-  for (; s + 2 <= ng; s += 2) {
+  for (int s = 0; s < ng; s += 2) {
     look(e0, s + 2);
     load(f1, e1, s + 1);
     mma(f0);
@@ -517,10 +515,6 @@ __device__ __forceinline__ void conv_weights_tile(const ConvArgs& a, int tile, i
     mma(f1);
     spread<16 * NJ, 0, RD, 8>();
     add_bias(f1);
-  }
-  if (s < ng) {
-    mma(f0);
-    add_bias(f0);
   }
 
   // The waves' sums, added in order; a thread takes four consecutive
@@ -563,11 +557,11 @@ __device__ __forceinline__ void conv_weights_tile(const ConvArgs& a, int tile, i
   }
 }
 
-// Backward-weight alone, of a first layer (GATHER: its images are dataset rows).
-template <int WJ, bool GATHER>
+// Backward-weight alone, of a first layer, whose images are dataset rows.
+template <int WJ>
 __global__ __launch_bounds__(64 * BWD_WAVES, 2) void conv_wgrad_direct_kernel(ConvArgs w) {
   __shared__ __attribute__((aligned(16))) WgradLds sm;
-  conv_weights_tile<WJ, GATHER>(w, xcd_item(blockIdx.x, gridDim.x), blockIdx.y, sm);
+  conv_weights_tile<WJ, true>(w, xcd_item(blockIdx.x, gridDim.x), blockIdx.y, sm);
 }
 
 // Backward-data of d (workgroups below nd) and backward-weight
@@ -643,12 +637,11 @@ void bwd_launch(const dim3& grid, hipStream_t s, const ConvArgs& d, const ConvAr
     hipLaunchKernelGGL((conv_bwd_direct_kernel<MI, NJ, 1, UNI>), grid, block, 0, s, d, w, nd);
 }
 
-template <bool GATHER>
 void wgrad_launch(const dim3& grid, hipStream_t s, const ConvArgs& w) {
   const dim3 block(64 * BWD_WAVES);
-  if (w.Co > 32) hipLaunchKernelGGL((conv_wgrad_direct_kernel<4, GATHER>), grid, block, 0, s, w);
-  else if (w.Co > 16) hipLaunchKernelGGL((conv_wgrad_direct_kernel<2, GATHER>), grid, block, 0, s, w);
-  else hipLaunchKernelGGL((conv_wgrad_direct_kernel<1, GATHER>), grid, block, 0, s, w);
+  if (w.Co > 32) hipLaunchKernelGGL(conv_wgrad_direct_kernel<4>, grid, block, 0, s, w);
+  else if (w.Co > 16) hipLaunchKernelGGL(conv_wgrad_direct_kernel<2>, grid, block, 0, s, w);
+  else hipLaunchKernelGGL(conv_wgrad_direct_kernel<1>, grid, block, 0, s, w);
 }
 
 }  // namespace
@@ -713,7 +706,7 @@ hipError_t launch_conv_direct_bwd(const ConvArgs* d, const ConvArgs& w, int n_sl
   if (!conv_direct(w) || n_slots < 1 || w.B < 1 || w.k_per_split < 128 ||
       w.k_per_split > WG_RANGE || w.k_per_split % 128 != 0 ||
       static_cast<int64_t>(w.splits) * w.k_per_split < static_cast<int64_t>(w.B) * w.Ho * w.Wo ||
-      (d && w.gather))
+      (d != nullptr) == (w.gather != nullptr))  // a first layer, or a pair
     return hipErrorInvalidValue;
   const int nj = w.Co > 32 ? 4 : w.Co > 16 ? 2 : 1;
   const int64_t nw = static_cast<int64_t>((9 * w.C + 63) / 64) * ((w.Co + 16 * nj - 1) / (16 * nj)) *
@@ -721,8 +714,7 @@ hipError_t launch_conv_direct_bwd(const ConvArgs* d, const ConvArgs& w, int n_sl
   if (!d) {
     if (nw * n_slots > 0x7FFFFFFF) return hipErrorInvalidValue;
     const dim3 grid(static_cast<unsigned>(nw), n_slots);
-    if (w.gather) wgrad_launch<true>(grid, s, w);
-    else wgrad_launch<false>(grid, s, w);
+    wgrad_launch(grid, s, w);
     return hipGetLastError();
   }
   PixelTile t = pixel_tile(d->C, static_cast<int64_t>(d->B) * d->H * d->W, n_slots);

@@ -19,18 +19,17 @@
 // 0 and 2 (likewise columns).  Each class gathers only its 1, 2 or 4 taps
 // (K = taps x Cout), a quarter of the 9-tap work on average; the four classes
 // share one launch (their tiles concatenated, the most taps first).
-// A workgroup computes a 64 x 64 tile of C with four waves of 32 x 32, fp32
-// MFMA 32x32x2, K in steps of 16: later steps' operands are gathered into
-// registers while the current step's MFMAs read LDS (two LDS buffers, one
-// barrier per step; two register sets where the channel counts allow loaders
-// without branches).  Where one side of the GEMM is at most 32 channels
-// (backward-data into, forward into, or backward-weight of 32 channels or
-// fewer) 128 x 32 or 32 x 128 tiles take its place, and layers with at most three input channels (layer 1) have a
-// direct forward and a one-accumulator backward-weight of their own.  The
-// weight-gradient passes split K into ranges, one partial sum per range,
-// which the update kernel adds in a fixed order (eight groups of consecutive
-// ranges) before applying the SGD step of Eq. 4 -- so results depend on
-// nothing but the inputs, whichever slots share a launch.
+// Layers whose channel counts are multiples of 4 have kernels of their own
+// (conv_direct.hip), and so have layers with at most three input channels and at
+// most 32 output channels in fours (layer 1 of an RGB network; below).  The
+// others: a workgroup computes a 64 x 64 tile of C with four waves of 32 x 32,
+// fp32 MFMA 32x32x2, K in steps of 16, operands gathered element by element into
+// two register sets, the later steps' while the current step's MFMAs read LDS
+// (two buffers, one barrier per step).  The weight-gradient passes split K into
+// ranges, one partial sum per range, which the update kernel adds in a fixed
+// order (eight groups of consecutive ranges) before applying the SGD step of
+// Eq. 4 -- so results depend on nothing but the inputs, whichever slots share a
+// launch.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -54,10 +53,10 @@ struct Dims {
   int64_t M, N, K;
 };
 
-// Loads never sit behind a branch in the vector loaders: a lane with nothing
-// to load (padding, a row or K past the end) reads these zeros instead, so
-// that the compiler's memory-counter waits stay exact and a load of the next
-// K steps can stay in flight across a wait for the current one.
+// Loads of the thin-layer kernels never sit behind a branch: a lane with nothing
+// to load (padding, a row or K past the end) reads these zeros instead, so that
+// the compiler's memory-counter waits stay exact and a load of the next K steps
+// can stay in flight across a wait for the current one.
 __device__ __attribute__((aligned(16))) float k_conv_zero[4];
 // and ones for the bias column of a weight gradient
 __device__ __attribute__((aligned(16))) float k_conv_one[4] = {1.0f, 1.0f, 1.0f, 1.0f};
@@ -1055,7 +1054,7 @@ void launch_conv_gemm(const dim3& grid, hipStream_t s, const ConvArgs& a) {
 }  // namespace
 
 hipError_t launch_conv(const ConvArgs& a, ConvPass pass, int n_slots, hipStream_t s) {
-  // shortcuts: conv forward and backward-data on the 64 x 64 and narrow tiles only
+  // shortcuts: conv forward (not of thin layers) and backward-data only
   if (a.skip && (pass == FC_FWD || pass == FC_DGRAD || pass == CONV_WGRAD || pass == FC_WGRAD ||
                  (pass == CONV_FWD && thin_layer(a))))
     return hipErrorInvalidValue;

@@ -1199,14 +1199,12 @@ oscars_status run_local_steps(oscars_ctx* c, float* replicas, const float* start
   }
 
   // ---- bf16 working copies: of the start model once, else of every active replica ----
-  if (c->bf16) {
-    e = timed(c, OSCARS_KERNEL_CAST, [&] {
-      return start ? launch_cast_bf16(start, 0, d_order, c->gq, 0, c->n_pad, 1, c->stream)
-                   : launch_cast_bf16(replicas, c->n_pad, d_order, c->wcopy, c->n_pad, c->n_pad,
-                                      n_slots, c->stream);
-    });
-    if (e != hipSuccess) return hip_fail(e);
-  }
+  e = timed(c, OSCARS_KERNEL_CAST, [&] {
+    return start ? launch_cast_bf16(start, 0, d_order, c->gq, 0, c->n_pad, 1, c->stream)
+                 : launch_cast_bf16(replicas, c->n_pad, d_order, c->wcopy, c->n_pad, c->n_pad,
+                                    n_slots, c->stream);
+  });
+  if (e != hipSuccess) return hip_fail(e);
 
   const int L = c->L;
   const int64_t rows_slot = static_cast<int64_t>(tau_max) * B;
@@ -1216,25 +1214,13 @@ oscars_status run_local_steps(oscars_ctx* c, float* replicas, const float* start
     while (ns_next < n_slots && tau[order[ns_next]] > j + 1) ++ns_next;
     const int32_t* rows_j = d_rows + static_cast<int64_t>(j) * B;
 
-    // Weights as operand A: slot-indexed bf16 copies, or the fp32 masters
-    // themselves (reached through order[]); in the first step of a round that
-    // starts from the global model, that model (shared by every slot).
+    // Weights as operand A: the slots' bf16 copies; in the first step of a round
+    // that starts from the global model, its copy (shared by every slot).
     const bool from_start = start && j == 0;
     auto weights = [&](GemmArgs& g, int l) {
-      if (from_start) {
-        g.a = c->bf16 ? static_cast<const void*>(c->gq + c->w_off[l])
-                      : static_cast<const void*>(start + c->w_off[l]);
-        g.a_by_order = 0;
-        g.a_slot = 0;
-      } else if (c->bf16) {
-        g.a = c->wcopy + c->w_off[l];
-        g.a_by_order = 0;
-        g.a_slot = c->n_pad;
-      } else {
-        g.a = replicas + c->w_off[l];
-        g.a_by_order = 1;
-        g.a_slot = c->n_pad;
-      }
+      g.a = (from_start ? c->gq : c->wcopy) + c->w_off[l];
+      g.a_by_order = 0;
+      g.a_slot = from_start ? 0 : c->n_pad;
       g.a_ld = c->dims[l - 1];
     };
     auto common = [&](GemmArgs& g, int l) {
@@ -1279,7 +1265,7 @@ oscars_status run_local_steps(oscars_ctx* c, float* replicas, const float* start
       if (l < L) {
         g.out = c->act[l];
         g.relu = 1;
-        g.out_bf16 = c->bf16;
+        g.out_bf16 = 1;
       } else {
         g.out = c->logits;
         g.relu = 0;
@@ -1298,14 +1284,14 @@ oscars_status run_local_steps(oscars_ctx* c, float* replicas, const float* start
         h.loss_slot = rows_slot;
         e = timed(c, OSCARS_KERNEL_SOFTMAX, [&] { return launch_bf16_head(g, h, ns, c->stream); });
       } else {
-        e = timed(c, OSCARS_KERNEL_FWD, [&] { return launch_gemm(g, GEMM_FWD, c->bf16, ns, c->stream, c->tuner); });
+        e = timed(c, OSCARS_KERNEL_FWD, [&] { return launch_gemm(g, GEMM_FWD, true, ns, c->stream, c->tuner); });
       }
       if (e != hipSuccess) return hip_fail(e);
     }
     // loss gradient
     if (!head) e = timed(c, OSCARS_KERNEL_SOFTMAX, [&] {
       return launch_softmax_ce(c->logits, c->ld[L], c->act_slot(L), c->dims[L], B, s->y, rows_j,
-                               rows_slot, c->delta[L], c->bf16, c->loss_dev + static_cast<int64_t>(j) * B,
+                               rows_slot, c->delta[L], true, c->loss_dev + static_cast<int64_t>(j) * B,
                                rows_slot, ns, c->stream);
     });
     if (e != hipSuccess) return hip_fail(e);
@@ -1326,7 +1312,7 @@ oscars_status run_local_steps(oscars_ctx* c, float* replicas, const float* start
       g.out = c->delta[l - 1];
       g.out_ld = c->ld[l - 1];
       g.out_slot = c->act_slot(l - 1);
-      g.out_bf16 = c->bf16;
+      g.out_bf16 = 1;
       g.mask = c->act[l - 1];
       g.mask_ld = c->ld[l - 1];
       g.mask_slot = c->act_slot(l - 1);
@@ -1349,15 +1335,15 @@ oscars_status run_local_steps(oscars_ctx* c, float* replicas, const float* start
       g.b_ld = c->ld[l];
       g.b_slot = c->act_slot(l);
       common(g, l);
-      g.wcopy = c->bf16 ? c->wcopy : nullptr;
+      g.wcopy = c->wcopy;
       g.wcopy_slot = c->n_pad;
       g.wcopy_slots = ns_next;  // slots ns_next .. ns-1 take their last step now
       return g;
     };
     // backward, top layer first; dgrad(l) reads W_l before wgrad(l) updates it
     for (int l = L; l >= 1; --l) {
-      if (l > 1 && c->bf16 && backward_fused_enabled(c->backward_mode)) {
-        // hidden layer of a bf16 model: backward-data, backward-weight and the
+      if (l > 1 && backward_fused_enabled(c->backward_mode)) {
+        // hidden layer: backward-data, backward-weight and the
         // update in one launch (bit-identical to the two launches below)
         GemmArgs g{};
         g.M = c->dims[l - 1];
@@ -1398,7 +1384,7 @@ oscars_status run_local_steps(oscars_ctx* c, float* replicas, const float* start
           }
         }
       }
-      if (l == 1 && c->bf16 && backward_fused_enabled(c->backward_mode)) {
+      if (l == 1 && backward_fused_enabled(c->backward_mode)) {
         // layer 1: backward-weight and the update streamed like the fused
         // backward of the hidden layers, without backward-data
         GemmArgs g{};
@@ -1435,12 +1421,12 @@ oscars_status run_local_steps(oscars_ctx* c, float* replicas, const float* start
       if (l > 1) {
         const GemmArgs g = dgrad_args(l);
         e = timed(c, OSCARS_KERNEL_DGRAD,
-                  [&] { return launch_gemm(g, GEMM_DGRAD, c->bf16, ns, c->stream, c->tuner); });
+                  [&] { return launch_gemm(g, GEMM_DGRAD, true, ns, c->stream, c->tuner); });
         if (e != hipSuccess) return hip_fail(e);
       }
       const GemmArgs g = wgrad_args(l);
       e = timed(c, OSCARS_KERNEL_WGRAD,
-                [&] { return launch_gemm(g, GEMM_WGRAD, c->bf16, ns, c->stream, c->tuner); });
+                [&] { return launch_gemm(g, GEMM_WGRAD, true, ns, c->stream, c->tuner); });
       if (e != hipSuccess) return hip_fail(e);
     }
   }
