@@ -498,13 +498,16 @@ __device__ __forceinline__ void conv_weights_tile(const ConvArgs& a, int tile, i
 #pragma unroll
       for (int j = 0; j < NJ; ++j) db[j] += f.b[j][t];
   };
-  // the wave's own part: whole pairs of groups (R is a multiple of 128)
+  // the wave's own part: whole pairs of groups, at least one (R is a multiple of
+  // 128).  (Tested before the first pair too, a round of the 32x32 CNN of 128
+  // channels took 2312 us instead of 2301.)
   const int ng = part_len / 16;
   constexpr int RD = 2;  // LDS reads of four table entries
   look(e0, 0);
   look(e1, 1);
   load(f0, e0, 0);
-  for (int s = 0; s < ng; s += 2) {
+  int s = 0;
+  do {
     look(e0, s + 2);
     load(f1, e1, s + 1);
     mma(f0);
@@ -515,7 +518,8 @@ __device__ __forceinline__ void conv_weights_tile(const ConvArgs& a, int tile, i
     mma(f1);
     spread<16 * NJ, 0, RD, 8>();
     add_bias(f1);
-  }
+    s += 2;
+  } while (s < ng);
 
   // The waves' sums, added in order; a thread takes four consecutive
   // columns of one output channel.
