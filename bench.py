@@ -33,6 +33,19 @@ MFMA_PEAK_TFLOPS = {"bf16": 2500.0, "fp32": 157.3}
 PMC_FILE = os.path.join(ROOT, "profiles", "pmc_traffic.json")
 
 
+def mlp_head_fused(cfg):
+    """Whether the library runs the last layer's forward and the softmax of a
+    local step of an MLP as one launch (fp32: and the last layer's
+    backward-data): up to 64 classes; bf16 not layer 1, nor, where split-K takes
+    its place (batches above 128), a layer deeper than the 8 (above 32 classes:
+    4) chunks of 1024 inputs of one turn."""
+    classes, depth = cfg.dims[-1], cfg.dims[-2]
+    if cfg.dtype != "bf16":
+        return classes <= 64
+    return (classes <= 64 and len(cfg.dims) > 2
+            and (cfg.batch <= 128 or depth <= 1024 * (4 if classes > 32 else 8)))
+
+
 def gemm_work(cfg, tau, fused_path=None):
     """Algorithmic FLOPs and bytes of every launch of one round (oscars_round),
     per kind.  Bytes: each operand read once, each result written once (weights
@@ -42,11 +55,15 @@ def gemm_work(cfg, tau, fused_path=None):
     global model).  A hidden layer whose backward is fused (backward-data +
     backward-weight + update in one launch; fused_path(l, ns), else every
     hidden layer of a bf16 model with batches up to 256) counts both products
-    and the update's bytes plus the delta written for the layer below."""
+    and the update's bytes plus the delta written for the layer below.  Where
+    the classifier head is one launch (mlp_head_fused) its products are
+    softmax_ce's; it writes no logits and, fp32, reads the last hidden
+    activations once, as operand and mask."""
     import numpy as np
     es = 2 if cfg.dtype == "bf16" else 4
     B, dims = cfg.batch, cfg.dims
     L = len(dims) - 1
+    head = mlp_head_fused(cfg)
     if fused_path is None:
         fused_path = lambda l, ns: cfg.dtype == "bf16" and B <= 256
     work = {"gemm_fwd": [0.0, 0.0], "gemm_dgrad": [0.0, 0.0], "gemm_wgrad_update": [0.0, 0.0],
@@ -62,22 +79,27 @@ def gemm_work(cfg, tau, fused_path=None):
         ns_next = int((tau > j + 1).sum())  # workers whose bf16 copy is refreshed
         for l in range(1, L + 1):
             i, o = dims[l - 1], dims[l]
-            out_es = es if l < L else 4
-            work["gemm_fwd"][0] += ns * 2.0 * B * o * i
-            work["gemm_fwd"][1] += ns * (es * o * i + 4 * o + es * B * i + out_es * B * o)
+            in_head = head and l == L
+            out_es = 0 if in_head else es if l < L else 4
+            fwd = work["softmax_ce" if in_head else "gemm_fwd"]
+            fwd[0] += ns * 2.0 * B * o * i
+            fwd[1] += ns * (es * o * i + 4 * o + es * B * i + out_es * B * o)
             update = (ns * (8.0 * (o * i + o) + es * B * o + es * B * i)
                       + (ns_next * 2.0 * o * i if es == 2 else 0.0))
             if l > 1 and fused_path(l, ns):
                 work["gemm_bwd_fused"][0] += ns * 4.0 * B * o * i
                 work["gemm_bwd_fused"][1] += update + ns * es * B * i
                 continue
-            if l > 1:
+            if l > 1 and in_head and cfg.dtype != "bf16":
+                work["softmax_ce"][0] += ns * 2.0 * B * o * i
+                work["softmax_ce"][1] += ns * es * B * i  # the delta below
+            elif l > 1:
                 work["gemm_dgrad"][0] += ns * 2.0 * B * o * i
                 work["gemm_dgrad"][1] += ns * (es * o * i + es * B * o + 2 * es * B * i)
             work["gemm_wgrad_update"][0] += ns * 2.0 * B * o * i
             work["gemm_wgrad_update"][1] += update
         C = dims[-1]
-        work["softmax_ce"][1] += ns * B * (4 * C + es * C)
+        work["softmax_ce"][1] += ns * B * ((0 if head else 4 * C) + es * C)
     return work
 
 
@@ -119,8 +141,8 @@ def cnn_work(cfg, tau, fused_path=None):
             # a shortcut layer also reads its block's input (the shape of its output)
             work["gemm_fwd"][1] += ns * (act_in + wts + act_out * (2 if skips[l] else 1))
             # backward-data and backward-weight of conv layer l + 1 in one launch
-            # (fused_path, the library's choice: one or two replicas), booked as
-            # gemm_bwd_fused; the update stays with gemm_wgrad_update
+            # (fused_path, the library's choice: channel counts multiples of 4), booked
+            # as gemm_bwd_fused; the update stays with gemm_wgrad_update
             pair = l > 0 and fused_path is not None and fused_path(l + 1, ns)
             dk = "gemm_bwd_fused" if pair else "gemm_dgrad"
             wk = "gemm_bwd_fused" if pair else "gemm_wgrad_update"

@@ -61,3 +61,27 @@ def test_traffic_accepts_a_mix_of_nearly_the_same_bytes(tmp_path, monkeypatch):
     far = lambda m: 1000.0 if m == ours else 1200.0  # noqa: E731
     assert bench.pmc_traffic("gemm_bwd_fused", "c5", 500.0, ours, close) == pytest.approx(550.0)
     assert bench.pmc_traffic("gemm_bwd_fused", "c5", 500.0, ours, far) is None
+
+
+@pytest.mark.parametrize("dims,dtype,batch,head", [
+    ((784, 10), "fp32", 32, True), ((784, 512, 64), "fp32", 64, True),
+    ((784, 512, 65), "fp32", 64, False), ((784, 10), "bf16", 32, False),
+    ((784, 512, 64), "bf16", 64, True), ((784, 512, 65), "bf16", 64, False),
+    ((64, 4096, 64), "bf16", 160, True), ((64, 4104, 64), "bf16", 160, False),
+    ((64, 4104, 64), "bf16", 128, True), ((64, 8192, 10), "bf16", 160, True),
+    ((64, 8200, 10), "bf16", 160, False)])
+def test_work_of_a_fused_head_is_booked_where_it_runs(dims, dtype, batch, head):
+    """The products of the last layer belong to the softmax launch where the
+    head is one launch; the round's products are the same either way."""
+    import types
+    cfg = types.SimpleNamespace(dims=dims, dtype=dtype, batch=batch, K=2)
+    work = bench.gemm_work(cfg, [1, 2], lambda l, ns: False)
+    macs = [o * i for i, o in zip(dims, dims[1:])]
+    flops = 3 * 2.0 * batch  # three local steps, of one layer's multiply-adds
+    assert bench.mlp_head_fused(cfg) == head
+    in_head = (2 if dtype == "fp32" and len(dims) > 2 else 1) * macs[-1] if head else 0
+    assert work["softmax_ce"][0] == flops * in_head
+    assert work["gemm_fwd"][0] == flops * (sum(macs) - (macs[-1] if head else 0))
+    assert sum(w[0] for w in work.values()) == flops * (3 * sum(macs) - macs[0])
+    # the head moves its weights, at least
+    assert (work["softmax_ce"][1] > 3 * macs[-1] * (2 if dtype == "bf16" else 4)) == head

@@ -360,3 +360,31 @@ def test_update_tiles_give_the_same_bits(P, batch):
                                flat[k * n:(k + 1) * n].view(torch.int32)), k
     finally:
         ctx.close()
+
+@pytest.mark.parametrize("dims,dtype,batch", [
+    ((24, 10), "fp32", 9), ((24, 40, 10), "fp32", 9), ((24, 40, 32, 65), "fp32", 9),
+    ((24, 10), "bf16", 9), ((24, 40, 32, 10), "bf16", 9), ((24, 4104, 64), "bf16", 130)])
+def test_bench_books_work_on_the_launches_that_run(P, dims, dtype, batch):
+    """Kinds of launches with products in the benchmark's count are the kinds
+    that a round launches."""
+    import torch
+
+    import bench
+    cfg = _mlp(dims, batch, (1, 2), 161, getattr(workload, dtype.upper()))
+    say(f"booked work {dims} {dtype}")
+    ds, init = workload.gen_dataset(cfg), workload.gen_init(cfg)
+    x = ds.x.view(np.int16) if dtype == "bf16" else ds.x
+    ctx = P.Context(cfg.dims, getattr(P, dtype.upper()), cfg.K, batch)
+    try:
+        ctx.set_backward(P.BACKWARDS["separate"])
+        flat = torch.from_numpy(np.tile(ctx.pack(init), cfg.K)).cuda()
+        ctx.profile_begin(range(len(P.KERNEL_NAMES)))
+        ctx.local_steps(flat, torch.from_numpy(np.ascontiguousarray(x)).cuda(),
+                        torch.from_numpy(ds.y.astype(np.int32)).cuda(),
+                        P.shard_offsets(cfg.n_rows, cfg.K), 5, cfg.tau_given, 0.05, batch)
+        launches = {k: n for k, (_, n) in ctx.profile_end().items()}
+        work = bench.gemm_work(cfg, cfg.tau_given, lambda l, ns: False)
+        for kind in ("gemm_fwd", "gemm_dgrad", "gemm_wgrad_update", "gemm_bwd_fused"):
+            assert (work[kind][0] > 0) == (launches[kind] > 0), (kind, launches)
+    finally:
+        ctx.close()
