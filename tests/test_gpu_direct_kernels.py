@@ -10,8 +10,11 @@ against the oracle on the same seeded inputs.
 * Convolutions: a gathered first layer on the direct kernels (4 and 16
   channels), K groups within one tap (channels a multiple of 16) and across taps
   (4, 12, 20), 1 to 3 output-channel blocks, stride 2 on odd sizes, several
-  pixel ranges with a ragged last one, pixels beyond one tile of every kind.
-* Evaluation over several passes with a ragged last one, MLP and CNN.
+  pixel ranges with a ragged last one, pixels beyond one tile of every kind
+  (16-channel layers by 64 pixels with many replicas), images of more than 2^20
+  pixels, the tallest ones, weights that keep the ranges long.
+* Evaluation over several passes with a ragged last one, MLP (fp32 and bf16, with
+  buffers of its own and without, the softmax in the head and apart) and CNN.
 
 The tolerance is FP32_TOL (BF16_TOL) of the trajectory tests: these are sums of the same
 lengths (K up to 2304, pixels up to 4800) in fp32, whose order alone differs."""
@@ -69,6 +72,7 @@ CASES = {
     "ranges-wide": _cnn((8, 8, 3), ((384, 1), (392, 1), (384, 2)), 9, (1, 2), 118),
     "image-1030x1020": _cnn((1030, 1020, 4), ((4, 1), (8, 2)), 1, (1,), 117),
     "image-4096x2": _cnn((4096, 2, 4), ((12, 1), (16, 2), (16, 1)), 2, (1, 2), 119),
+    "tiles-16x64": _cnn((32, 32, 3), ((16, 1), (16, 1), (32, 2)), 128, (1,) * 8, 120),
     "many-slots": _cnn((16, 16, 3), ((32, 1), (64, 2), (64, 1, 0)), 16, (1, 1, 1, 1, 1), 116),
 }
 
@@ -107,6 +111,53 @@ def test_evaluation_passes_match_oracle(P, rows):
             ev.x.astype(np.float64), ev.y)
         assert abs(loss - ref_loss) <= FP32_TOL * abs(ref_loss)
         assert abs(hits - ref_hits) <= int((np.asarray(gaps) < 1e-4).sum())  # rounding decides these
+    finally:
+        ctx.close()
+
+
+# Several passes: bf16 rows (two passes of 8192 and a ragged third), more
+# activations of the local steps than a pass of its own would have (their rows
+# are the pass), the softmax apart (65 classes and more), and convolutions (K x
+# max_batch images per pass, in slots of one or several rows).
+EVALUATIONS = {
+    "bf16": (_mlp((40, 72, 48, 17), 16, (1, 1), 171, workload.BF16), [8192, 2 * 8192 + 70]),
+    "bf16-classes-130": (_mlp((264, 136, 130), 16, (1, 1), 172, workload.BF16), [8192 + 1]),
+    "own-rows": (_mlp((24, 40, 17), 1024, (1,) * 9, 173), [9216, 9216 + 70]),
+    "own-rows-bf16": (_mlp((24, 40, 72), 1024, (1,) * 9, 174, workload.BF16), [9216 + 70]),
+    "classes-65": (_mlp((40, 72, 65), 16, (1, 1), 175), [8191, 8192 + 70]),
+    "one-layer-100": (_mlp((40, 100), 16, (1, 1), 176), [8192 + 70]),
+    "cnn": (_cnn((9, 7, 3), ((8, 1), (12, 2)), 16, (1, 1, 1), 177), [1, 47, 48, 49, 130]),
+}
+
+
+@pytest.mark.parametrize("name", EVALUATIONS)
+def test_evaluation_paths_match_oracle(P, name):
+    import torch
+    cfg, sizes = EVALUATIONS[name]
+    say(f"evaluate {name}")
+    init = workload.gen_init(cfg)
+    bf16 = cfg.dtype == workload.BF16
+    ref = [(W.astype(np.float64), b.astype(np.float64)) for W, b in init]
+    cnn = (cfg.image, cfg.conv) if cfg.image else None
+    ctx = P.Context(cfg.dims, P.BF16 if bf16 else P.FP32, cfg.K, cfg.batch, cnn=cnn)
+    try:
+        flat = torch.from_numpy(ctx.pack(init)).cuda()
+        for rows in sizes:
+            ev = workload.gen_eval_set(cfg, rows)
+            x = torch.from_numpy(np.ascontiguousarray(ev.x.view(np.int16) if bf16 else ev.x)).cuda()
+            y = torch.from_numpy(ev.y.astype(np.int32)).cuda()
+            loss, hits = ctx.evaluate(flat, x, y)
+            assert ctx.evaluate(flat, x, y, noalloc=True) == (loss, hits)
+            x64 = ev.x_f32().astype(np.float64)
+            if cnn:
+                ref_loss, ref_hits = oracle.cnn.evaluate(ref, x64, ev.y, cfg.image, cfg.strides,
+                                                         cfg.skips)
+                near = 1
+            else:
+                ref_loss, ref_hits, gap = oracle.mlp.evaluate(ref, x64, ev.y, bf16)
+                near = int((gap < (1e-2 if bf16 else 1e-4)).sum())  # rounding decides these
+            assert abs(loss - ref_loss) <= (BF16_TOL if bf16 else FP32_TOL) * abs(ref_loss), rows
+            assert abs(hits - ref_hits) <= near, rows
     finally:
         ctx.close()
 
@@ -360,6 +411,7 @@ def test_update_tiles_give_the_same_bits(P, batch):
                                flat[k * n:(k + 1) * n].view(torch.int32)), k
     finally:
         ctx.close()
+
 
 @pytest.mark.parametrize("dims,dtype,batch", [
     ((24, 10), "fp32", 9), ((24, 40, 10), "fp32", 9), ((24, 40, 32, 65), "fp32", 9),
