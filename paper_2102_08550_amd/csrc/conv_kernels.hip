@@ -23,9 +23,10 @@
 // (conv_direct.hip), and so have layers with at most three input channels and at
 // most 32 output channels in fours (layer 1 of an RGB network; below).  The
 // others: a workgroup computes a 64 x 64 tile of C with four waves of 32 x 32,
-// fp32 MFMA 32x32x2, K in steps of 16, operands gathered element by element into
-// two register sets, the later steps' while the current step's MFMAs read LDS
-// (two buffers, one barrier per step).  The weight-gradient passes split K into
+// fp32 MFMA 32x32x2, K in steps of 16, operands gathered (four channels of one tap
+// at a time where they are in fours, else element by element) into two register
+// sets, the later steps' while the current step's MFMAs read LDS (two buffers, one
+// barrier per step).  The weight-gradient passes split K into
 // ranges, one partial sum per range, which the update kernel adds in a fixed
 // order (eight groups of consecutive ranges) before applying the SGD step of
 // Eq. 4 -- so results depend on nothing but the inputs, whichever slots share a
@@ -44,6 +45,23 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 // A compile-time integer passed as an argument (static register indices).
 template <int U> struct Pi { static constexpr int value = U; };
+
+// Schedule of a K step with N MFMAs: each MFMA followed by a share of the step's
+// other work (its next operands' LDS reads, gather address arithmetic, LDS
+// stores, global loads), which then issues while the matrix core runs.  Left
+// alone the compiler issues the MFMAs back to back and the rest after them; with
+// one or two waves per SIMD nothing else hides that work.
+template <int N>
+__device__ __forceinline__ void interleave() {
+#pragma unroll
+  for (int u = 0; u < N; ++u) {
+    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // one MFMA
+    __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);  // LDS reads
+    __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);  // VALU
+    __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);  // LDS write
+    __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);  // global load
+  }
+}
 
 constexpr int CT = 64;       // tile rows and columns
 constexpr int CK = 16;       // K per step
@@ -254,13 +272,20 @@ struct ConvLoader {
       off = (i * a.Wo + j) * a.Co;
       return true;
     };
-    int t2 = t, o2 = o;
-    for (int e = 0; e < 4; ++e) {
+    if ((a.Co & 3) == 0) {  // four channels of one tap
+      f32x4 v = {0.0f, 0.0f, 0.0f, 0.0f};
       int off = 0;
-      ra[e] = (am && k + e < kend && tap(t2, off)) ? arow[off + o2] : 0.0f;
-      if (++o2 == a.Co) {
-        o2 = 0;
-        ++t2;
+      if (am && k < kend && tap(t, off)) v = *reinterpret_cast<const f32x4*>(arow + off + o);
+      for (int e = 0; e < 4; ++e) ra[e] = v[e];
+    } else {
+      int t2 = t, o2 = o;
+      for (int e = 0; e < 4; ++e) {
+        int off = 0;
+        ra[e] = (am && k + e < kend && tap(t2, off)) ? arow[off + o2] : 0.0f;
+        if (++o2 == a.Co) {
+          o2 = 0;
+          ++t2;
+        }
       }
     }
   }
@@ -374,10 +399,11 @@ __host__ __device__ inline int dgrad_class_at(int i) { return i == 0 ? 3 : i == 
 
 // One tile of the GEMM.
 template <int PASS>
-__global__ __launch_bounds__(256) void conv_gemm_kernel(ConvArgs a) {
+__device__ __forceinline__ void conv_gemm_tile(ConvArgs a, int tile, float* lds) {
   constexpr bool WG = PASS == CONV_WGRAD || PASS == FC_WGRAD;
-  __shared__ __attribute__((aligned(16))) float As[2][CK][CLD], Bs[2][CK][CLD];
-  int tile = blockIdx.x;
+  typedef float Stage[2][CK][CLD];
+  Stage& As = *reinterpret_cast<Stage*>(lds);
+  Stage& Bs = *reinterpret_cast<Stage*>(lds + 2 * CK * CLD);
   int split = 0;
   if constexpr (PASS == CONV_DGRAD) {
     if (a.stride == 2 && a.cls < 0) {
@@ -420,7 +446,11 @@ __global__ __launch_bounds__(256) void conv_gemm_kernel(ConvArgs a) {
   float ra[2][4], rb[2][4];
   auto load = [&](int k0, auto P) {
     constexpr int p = decltype(P)::value;
-    ld.fetch(k0 + lk, ra[p], rb[p]);
+    // (In a loop of one pass the gathers' tests become selects; without it
+    // backward-data had 93 more branches: 113 to 226 channels, stride 2, 7 x 8
+    // images, batch 34, two replicas 712 against 606 us per round of backward-data.)
+#pragma unroll
+    for (int q = 0; q < 1; ++q) ld.fetch(k0 + q * CK + lk, ra[p], rb[p]);
   };
   auto stash = [&](auto P) {
     constexpr int p = decltype(P)::value;  // register set p into LDS buffer p
@@ -457,6 +487,7 @@ __global__ __launch_bounds__(256) void conv_gemm_kernel(ConvArgs a) {
                                                    Bs[p][2 * u + h][wn * 32 + r], acc, 0, 0, 0);
     }
     stash(Pi<p ^ 1>());
+    if constexpr (decltype(MUL)::value) interleave<CK / 2>();
     __syncthreads();
   };
   auto steps = [&](auto MUL) {
@@ -506,6 +537,12 @@ __global__ __launch_bounds__(256) void conv_gemm_kernel(ConvArgs a) {
       a.part[z * a.part_slot + (static_cast<int64_t>(split) * M + row) * N + col] = v;
     }
   }
+}
+
+template <int PASS>
+__global__ __launch_bounds__(256) void conv_gemm_kernel(ConvArgs a) {
+  __shared__ __attribute__((aligned(16))) float lds[4 * CK * CLD];
+  conv_gemm_tile<PASS>(a, blockIdx.x, lds);
 }
 
 // ---------------------------------------------------------------------------

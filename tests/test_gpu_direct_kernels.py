@@ -12,7 +12,8 @@ against the oracle on the same seeded inputs.
   (4, 12, 20), 1 to 3 output-channel blocks, stride 2 on odd sizes, several
   pixel ranges with a ragged last one, pixels beyond one tile of every kind
   (16-channel layers by 64 pixels with many replicas), images of more than 2^20
-  pixels, the tallest ones, weights that keep the ranges long.
+  pixels, the tallest ones, weights that keep the ranges long; and the general
+  kernels' 16-byte loads where one side's channels are in fours.
 * Evaluation over several passes with a ragged last one, MLP (fp32 and bf16, with
   buffers of its own and without, the softmax in the head and apart) and CNN.
 
@@ -72,6 +73,7 @@ CASES = {
     "ranges-wide": _cnn((8, 8, 3), ((384, 1), (392, 1), (384, 2)), 9, (1, 2), 118),
     "image-1030x1020": _cnn((1030, 1020, 4), ((4, 1), (8, 2)), 1, (1,), 117),
     "image-4096x2": _cnn((4096, 2, 4), ((12, 1), (16, 2), (16, 1)), 2, (1, 2), 119),
+    "fours-on-one-side": _cnn((11, 9, 4), ((10, 1), (12, 2), (7, 1), (8, 2), (6, 1)), 5, (2, 1), 122),
     "tiles-16x64": _cnn((32, 32, 3), ((16, 1), (16, 1), (32, 2)), 128, (1,) * 8, 120),
     "many-slots": _cnn((16, 16, 3), ((32, 1), (64, 2), (64, 1, 0)), 16, (1, 1, 1, 1, 1), 116),
 }
