@@ -519,6 +519,11 @@ __device__ __forceinline__ void update_tile(const F32UpdateArgs& u, const F32Upd
     w[i] = *reinterpret_cast<const f32x4*>(win + y.w_off + static_cast<int64_t>(n < y.N ? n : 0) * y.M +
                                            (col_in ? m0 + 4 * wc : 0));
   }
+  float bias[T];  // and the biases: loaded where they are used, their latency was the wave's end
+  if constexpr (BIAS) {
+#pragma unroll
+    for (int j = 0; j < T; ++j) bias[j] = win[y.b_off + min(n0 + T * c16 + j, y.N - 1)];
+  }
   for (int s = 0; s < ns; s += 2) {
     load(1, s + 1);
     load_index(0, s + 2);
@@ -539,7 +544,7 @@ __device__ __forceinline__ void update_tile(const F32UpdateArgs& u, const F32Upd
       db[j] += __shfl_xor(db[j], 16);
       db[j] += __shfl_xor(db[j], 32);
       const int n = n0 + T * c16 + j;
-      if (gq == 0 && n < y.N) wout[y.b_off + n] = fmaf(-u.lr, db[j], win[y.b_off + n]);
+      if (gq == 0 && n < y.N) wout[y.b_off + n] = fmaf(-u.lr, db[j], bias[j]);
     }
   }
   // Chunk c of row r at c ^ (r / T) (no bank conflicts either way); LDS
