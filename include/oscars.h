@@ -356,8 +356,8 @@ oscars_status oscars_profile_end(oscars_ctx* ctx, double* ms, int64_t* launches)
 /* Tiling of the forward and backward-data GEMMs of one context (a tuning and
  * testing aid).  Every tiling sums each output in the same order (bf16
  * models: K in chunks of 1024 summed left to right; fp32 models: four
- * interleaved slices of K added in order), so results are bit-identical
- * whatever the tiling; only the speed differs.
+ * interleaved slices of K, each in runs of 1024 products, added in order),
+ * so results are bit-identical whatever the tiling; only the speed differs.
  *   OSCARS_TILING_AUTO (default): the launches of each GEMM configuration
  *     (layer shape, batch, number of active replicas) in the process are
  *     tuned online: while the configuration is being tuned, each launch runs
