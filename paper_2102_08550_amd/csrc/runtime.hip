@@ -189,10 +189,12 @@ bool f32_head(const oscars_ctx* c) { return !c->bf16 && c->dims[c->L] <= F32_HEA
 
 hipError_t alloc_eval(oscars_ctx* c) {
   const int64_t have = static_cast<int64_t>(c->K) * c->max_batch;
-  int64_t ld = 64;
+  int64_t ld = 0;
   for (int l = 1; l < c->L; ++l) ld = std::max(ld, c->ld[l]);
   const int64_t act = ld * static_cast<int64_t>(c->esize);
   const int64_t logits = f32_head(c) ? 0 : c->ld[c->L] * 4;
+  c->eval_rows = std::max(have, kEvalRows);
+  if (act + logits == 0) return hipSuccess;  // one layer, the head: nothing between
   const int64_t rows = std::min(kEvalRows, kEvalBytes / (2 * act + logits));
   c->eval_rows = have;
   if (rows <= have) return hipSuccess;
@@ -377,9 +379,14 @@ oscars_status oscars_create(oscars_ctx** out, const oscars_model* m, int32_t K, 
   if (e == hipSuccess && c->bf16)  // act[0]: the gathered batch rows of the current step
     e = dev_alloc(c, static_cast<size_t>(K) * c->act_slot(0) * c->esize, &c->act[0]);
   for (int l = 1; l <= c->L && e == hipSuccess; ++l) {
-    const size_t n = static_cast<size_t>(K) * c->act_slot(l);
-    if (l < c->L) e = dev_alloc(c, n * c->esize, &c->act[l]);
-    if (e == hipSuccess) e = dev_alloc(c, n * c->esize, &c->delta[l]);
+    // one allocation per layer: act, then delta (whole rows of 64 elements)
+    const size_t bytes = static_cast<size_t>(K) * c->act_slot(l) * c->esize;
+    const bool act = l < c->L;  // the last layer's outputs are the logits
+    e = dev_alloc(c, act ? 2 * bytes : bytes, &c->delta[l]);
+    if (act && e == hipSuccess) {
+      c->act[l] = c->delta[l];
+      c->delta[l] = static_cast<char*>(c->act[l]) + bytes;
+    }
   }
   if (e == hipSuccess) {
     void* p = nullptr;

@@ -128,6 +128,7 @@ EVALUATIONS = {
     "own-rows-bf16": (_mlp((24, 40, 72), 1024, (1,) * 9, 174, workload.BF16), [9216 + 70]),
     "classes-65": (_mlp((40, 72, 65), 16, (1, 1), 175), [8191, 8192 + 70]),
     "one-layer-100": (_mlp((40, 100), 16, (1, 1), 176), [8192 + 70]),
+    "one-layer-head": (_mlp((40, 10), 16, (1, 1), 178), [8192 + 70]),
     "cnn": (_cnn((9, 7, 3), ((8, 1), (12, 2)), 16, (1, 1, 1), 177), [1, 47, 48, 49, 130]),
 }
 
